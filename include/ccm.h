@@ -190,17 +190,24 @@ int ccm_matvec(const ccm_desc *a, const void *x, int32_t xdtype, int64_t *y, voi
  * matrices), re-encoded at the width of its exact range (Eq. 1, or two's
  * complement for a negative minimum).  CCM_E_OVERFLOW iff
  * K * max|A| * max|B| >= 2^63 (max|M| = max(|min|, |max|) from the headers;
- * an O(1) conservative bound), so every entry fits in int64.  Fields of at most 8 bits whose values fit int8 go
- * through int8 MFMA tiles with exact integer accumulation; others through an
- * exact int64 path.
- *   scratch_bytes: device scratch the two calls need (dense C at 4 or 8 bytes
- *     per entry; on the int8 path also A and B^T decoded to int8, K padded
- *     to a multiple of 128).
+ * an O(1) conservative bound), so every entry fits in int64.  Products run
+ * on the int8 matrix cores with exact integer accumulation, operands wider
+ * than a byte as several base-256 digits per value; K of 2^17 or more (unless
+ * every value fits int8 and K * max|A| * max|B| < 2^31) goes through an exact
+ * int64 path.
+ *   scratch_bytes: device scratch the two calls take (dense C at 4 or 8 bytes
+ *     per entry, the operands' digits with K padded to a multiple of 128, and
+ *     8 bytes per row and column).
+ *   scratch_least: the smallest scratch they accept.  Where it is less than
+ *     scratch_bytes (values outside int8), a scratch between the two, or one
+ *     off a 16-byte boundary, gives the same result through the int64 path,
+ *     slower.
  *   plan: computes C into scratch and its exact range, fills out (payload
  *     NULL).  Blocking.
  *   op: packs the scratch into out->payload.  Async.
  * The scratch must not be modified between the two calls. */
 uint64_t ccm_matmul_scratch_bytes(const ccm_desc *a, const ccm_desc *b);
+uint64_t ccm_matmul_scratch_least(const ccm_desc *a, const ccm_desc *b);
 int ccm_matmul_plan(const ccm_desc *a, const ccm_desc *b, ccm_desc *out, void *scratch,
                     uint64_t scratch_bytes, void *stream);
 int ccm_matmul(const ccm_desc *a, const ccm_desc *b, const ccm_desc *out,

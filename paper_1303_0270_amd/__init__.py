@@ -371,6 +371,13 @@ def matmul_scratch_bytes(a: CMatrix, b: CMatrix) -> int:
     return int(lib.ccm_matmul_scratch_bytes(ctypes.byref(a.desc), ctypes.byref(b.desc)))
 
 
+def matmul_scratch_least(a: CMatrix, b: CMatrix) -> int:
+    """The smallest scratch the C calls accept (slower for operands outside int8)."""
+    _row_major(a, "matmul")
+    _row_major(b, "matmul")
+    return int(lib.ccm_matmul_scratch_least(ctypes.byref(a.desc), ctypes.byref(b.desc)))
+
+
 def matmul_plan(a: CMatrix, b: CMatrix, scratch: torch.Tensor | None = None, stream=None):
     """Range pass of C = A B: computes C into scratch and returns (C, scratch), C
     allocated at its final width but not yet packed."""

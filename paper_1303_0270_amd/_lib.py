@@ -91,6 +91,7 @@ SIGNATURES = {
     "ccm_scale": (ctypes.c_int, [_dp, _i64, _dp, _vp]),
     "ccm_matvec": (ctypes.c_int, [_dp, _vp, _i32, _vp, _vp]),
     "ccm_matmul_scratch_bytes": (_u64, [_dp, _dp]),
+    "ccm_matmul_scratch_least": (_u64, [_dp, _dp]),
     "ccm_matmul_plan": (ctypes.c_int, [_dp, _dp, _dp, _vp, _u64, _vp]),
     "ccm_matmul": (ctypes.c_int, [_dp, _dp, _dp, _vp, _u64, _vp]),
     "ccm_async_ws_bytes": (_u64, []),

@@ -497,31 +497,48 @@ int ccm_matvec(const ccm_desc *a, const void *x, int32_t xdtype, int64_t *y, voi
 }
 
 // Scratch layout of a matmul: dense C (int32 when the bound allows, else
-// int64), rounded up to 256 bytes, then -- on the int8 MFMA path -- A and
-// B^T decoded to int8.  The MFMA path is taken when both operands' values
-// fit int8 and the bound K*max|A|*max|B| < 2^31 keeps int32 sums exact.
+// int64), rounded up to 256 bytes, then the operands' digits for the matrix
+// cores.  A scratch of `least` bytes is enough for the product (for operands
+// whose values fit int8, with the bound K*max|A|*max|B| < 2^31, that includes
+// their digits); `total` is what the matrix-core path takes.
 struct MatmulPlan {
-  int out32, use_i8;
-  uint64_t c_bytes, total;
+  int out32, i8;
+  uint64_t c_bytes, least, total;
 };
+
+// Digits past this size are not asked for (products of a few hundred thousand
+// rows and columns, whose scratch the caller sized for C alone).
+constexpr uint64_t kMaxDigitBytes = 16ull << 30;
 
 static bool matmul_layout(const ccm_desc *a, const ccm_desc *b, MatmulPlan *p) {
   unsigned __int128 bound = 0;
   if (!matmul_bound(a, b, &bound)) return false;
   p->out32 = bound < ((unsigned __int128)1 << 31) ? 1 : 0;
-  p->use_i8 = (p->out32 && fits_i8(a) && fits_i8(b)) ? 1 : 0;
+  p->i8 = (p->out32 && fits_i8(a) && fits_i8(b)) ? 1 : 0;
   const uint64_t c = (p->out32 ? 4u : 8u) * (uint64_t)a->rows * (uint64_t)b->cols;
   p->c_bytes = (c + 255u) / 256u * 256u;
-  p->total = p->c_bytes + (p->use_i8 ? ccm::matmul_i8_bytes(a->rows, a->cols, b->cols) : 0u);
+  uint64_t fast = ccm::matmul_fast_bytes(a->bits, a->is_signed, b->bits, b->is_signed, a->rows,
+                                         a->cols, b->cols, p->i8);
+  if (!p->i8 && fast > kMaxDigitBytes) fast = 0;
+  p->total = p->c_bytes + fast;
+  p->least = p->i8 ? p->total : p->c_bytes;
   return true;
 }
 
-uint64_t ccm_matmul_scratch_bytes(const ccm_desc *a, const ccm_desc *b) {
+static uint64_t matmul_bytes(const ccm_desc *a, const ccm_desc *b, bool least) {
   if (check_desc(a, false) != CCM_OK || check_desc(b, false) != CCM_OK) return 0;
   if (a->cols != b->rows) return 0;
   MatmulPlan p;
   if (!matmul_layout(a, b, &p)) return 0;
-  return p.total;
+  return least ? p.least : p.total;
+}
+
+uint64_t ccm_matmul_scratch_bytes(const ccm_desc *a, const ccm_desc *b) {
+  return matmul_bytes(a, b, false);
+}
+
+uint64_t ccm_matmul_scratch_least(const ccm_desc *a, const ccm_desc *b) {
+  return matmul_bytes(a, b, true);
 }
 
 static int matmul_common(const ccm_desc *a, const ccm_desc *b, uint64_t scratch_bytes,
@@ -533,8 +550,19 @@ static int matmul_common(const ccm_desc *a, const ccm_desc *b, uint64_t scratch_
   if (!shape_ok(a->rows, b->cols)) return CCM_E_INVAL;
   if (!matmul_layout(a, b, p)) return CCM_E_OVERFLOW;
   if (!scratch) return CCM_E_INVAL;
-  if (scratch_bytes < p->total) return CCM_E_NOMEM;
+  if (scratch_bytes < p->least) return CCM_E_NOMEM;
   return CCM_OK;
+}
+
+// The digits' 16-byte copies need an aligned scratch; the int64 path does not.
+static hipError_t matmul_run(const ccm_desc *a, const ccm_desc *b, const MatmulPlan &p,
+                             void *scratch, uint64_t scratch_bytes, ccm::RangeSlot *slot,
+                             hipStream_t s) {
+  const bool digits = scratch_bytes >= p.total && (p.i8 || (uintptr_t)scratch % 16 == 0);
+  return ccm::launch_matmul((const uint32_t *)a->payload, a->bits, a->is_signed,
+                            (const uint32_t *)b->payload, b->bits, b->is_signed, a->rows, a->cols,
+                            b->cols, p.i8, p.out32, scratch, p.c_bytes,
+                            digits ? p.total : p.c_bytes, slot, s);
 }
 
 int ccm_matmul_plan(const ccm_desc *a, const ccm_desc *b, ccm_desc *out, void *scratch,
@@ -549,9 +577,7 @@ int ccm_matmul_plan(const ccm_desc *a, const ccm_desc *b, ccm_desc *out, void *s
   rc = device_ctx(&c);
   if (rc != CCM_OK) return rc;
   CCM_HIP(ccm::launch_range_init(c->slot, s));
-  CCM_HIP(ccm::launch_matmul((const uint32_t *)a->payload, a->bits, a->is_signed,
-                             (const uint32_t *)b->payload, b->bits, b->is_signed, a->rows,
-                             a->cols, b->cols, mp.use_i8, mp.out32, scratch, c->slot, s));
+  CCM_HIP(matmul_run(a, b, mp, scratch, scratch_bytes, c->slot, s));
   ccm::RangeSlot r;
   rc = read_slot(c, s, &r);
   if (rc != CCM_OK) return rc;
@@ -654,9 +680,7 @@ int ccm_matmul_async(const ccm_desc *a, const ccm_desc *b, void *payload,
   if (payload_bytes < ccm_payload_capacity(a->rows, b->cols, max_bits)) return CCM_E_NOMEM;
   hipStream_t s = (hipStream_t)stream;
   CCM_HIP(ccm::launch_range_init(slots, s));
-  CCM_HIP(ccm::launch_matmul((const uint32_t *)a->payload, a->bits, a->is_signed,
-                             (const uint32_t *)b->payload, b->bits, b->is_signed, a->rows,
-                             a->cols, b->cols, mp.use_i8, mp.out32, scratch, slots, s));
+  CCM_HIP(matmul_run(a, b, mp, scratch, scratch_bytes, slots, s));
   CCM_HIP(ccm::launch_result_finalize(slots, a->rows, b->cols, 0, res, s));
   CCM_HIP(ccm::launch_compress_dev(scratch, mp.out32 ? CCM_I32 : CCM_I64,
                                    (uint64_t)a->rows * (uint64_t)b->cols, max_bits,

@@ -417,18 +417,17 @@ hipError_t launch_sum_splits(const int64_t *part, int64_t splits, int64_t cols, 
 hipError_t launch_compress_cm(const void *dense, int dtype, int64_t rows, int64_t cols,
                               int bits, uint32_t *out, uint64_t cap32, hipStream_t s);
 
-// matmul into dense scratch (int32 if out32 else int64) with its range.
+// matmul into dense scratch (int32 if out32 else int64) with its range.  The
+// scratch holds C in its first c_bytes; with matmul_fast_bytes more (0: not
+// for this product) the operands' digits go there and the product runs on the
+// matrix cores, otherwise it runs in int64 on the vector units.  i8: both
+// operands' values fit int8 and K*max|A|*max|B| < 2^31.
+uint64_t matmul_fast_bytes(int abits, int asgn, int bbits, int bsgn, int64_t M, int64_t K,
+                           int64_t N, int i8);
 hipError_t launch_matmul(const uint32_t *aw, int abits, int asgn, const uint32_t *bw,
-                         int bbits, int bsgn, int64_t M, int64_t K, int64_t N, int use_i8,
-                         int out32, void *scratch, RangeSlot *slot, hipStream_t s);
-
-// int8 MFMA matmul (operands whose values fit int8, K*max|A|*max|B| < 2^31):
-// The int8 MFMA path decodes A (M x K) and B^T (N x K) into int8 scratch,
-// K padded to a multiple of 128: matmul_i8_bytes bytes.
-uint64_t matmul_i8_bytes(int64_t M, int64_t K, int64_t N);
-hipError_t launch_matmul_i8(const uint32_t *aw, int abits, int asgn, const uint32_t *bw,
-                            int bbits, int bsgn, int64_t M, int64_t K, int64_t N, int out32,
-                            void *scratch_c, int8_t *scratch_i8, RangeSlot *slot, hipStream_t s);
+                         int bbits, int bsgn, int64_t M, int64_t K, int64_t N, int i8, int out32,
+                         void *scratch, uint64_t c_bytes, uint64_t scratch_bytes, RangeSlot *slot,
+                         hipStream_t s);
 
 // Method 2 (variable length blocks): stream, index and shape of one matrix.
 struct VlbView {

@@ -44,7 +44,7 @@ import numpy as np
 import torch
 
 from . import (CMatrix, Pending, generate, lib, matmul_async, matmul_capacity,
-               matmul_scratch_bytes, matvec)
+               matmul_scratch_bytes, matmul_scratch_least, matvec)
 from .batch import BATCH_MAX_COLS, DynBatch
 
 
@@ -78,13 +78,13 @@ class _Launch:
 
 def request_footprint(req: Request, pool) -> int:
     """Device bytes a request holds while in flight: x and y, or B, the
-    result at the width the operand headers bound, the matmul scratch and
-    the result's workspace."""
+    result at the width the operand headers bound, the least matmul scratch
+    and the result's workspace."""
     a = pool[req.mat]
     if req.kind == "mv":
         return 4 * a.cols + 8 * a.rows
     b = req.b
-    return (b.payload.numel() + matmul_capacity(a, b) + matmul_scratch_bytes(a, b) +
+    return (b.payload.numel() + matmul_capacity(a, b) + matmul_scratch_least(a, b) +
             int(lib.ccm_async_ws_bytes()))
 
 
