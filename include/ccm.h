@@ -40,8 +40,8 @@
  *     that write a payload write every byte of that capacity.
  *   - `stream` is a hipStream_t passed as void* (NULL = the null stream).
  *     Calls marked "async" only enqueue work on it; calls marked "blocking"
- *     synchronize it before returning.  Inputs must stay valid until the
- *     enqueued work completes.
+ *     wait until the work they report on is done.  Inputs must stay valid
+ *     until the enqueued work completes.
  *   - The library keeps a few bytes of device memory per device for blocking
  *     reductions (taken under a lock) and the batch objects' metadata.
  *

@@ -32,48 +32,82 @@ int dev_err(hipError_t e, const char *where) {
     if (e_ != hipSuccess) return dev_err(e_, #call);    \
   } while (0)
 
-// Blocking reductions share one device slot and one pinned host mirror per
-// device, used under a lock (each use ends with a stream synchronize).
+// Blocking reductions share one set of device slots and one pinned host
+// record per device, used under a lock (each use waits for its record).
 struct DeviceCtx {
   ccm::RangeSlot *slot = nullptr;
-  ccm::RangeSlot *host = nullptr;
-  int64_t *one = nullptr;    // single-element get
+  ccm::RangeHost *host = nullptr;
+  uint32_t *full = nullptr;
+  uint32_t seq = 0;
+  bool armed = false;        // the slots hold nothing
   uint64_t *sums = nullptr;  // spread sum pairs (method choice)
+  uint64_t *words = nullptr; // pinned copies of other results
 };
 std::mutex g_mu;
 std::vector<DeviceCtx> g_ctx;
 
-int device_ctx(DeviceCtx **out) {
+// Refused under stream capture, as a wait for the stream is.
+int device_ctx(hipStream_t s, DeviceCtx **out) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (s && hipStreamIsCapturing(s, &cs) != hipSuccess) {
+    (void)hipGetLastError();
+    cs = hipStreamCaptureStatusNone;
+  }
+  if (cs != hipStreamCaptureStatusNone) return CCM_E_DEVICE;
   int dev = 0;
   CCM_HIP(hipGetDevice(&dev));
   if ((size_t)dev >= g_ctx.size()) g_ctx.resize((size_t)dev + 1);
   DeviceCtx &c = g_ctx[(size_t)dev];
   if (!c.slot) {
-    void *p = nullptr;
-    CCM_HIP(hipMalloc(&p, ccm::kRangeBytes + 256 + ccm::kSumBytes));
-    c.slot = (ccm::RangeSlot *)p;
-    c.one = (int64_t *)((char *)p + ccm::kRangeBytes);
+    void *h = nullptr, *p = nullptr;
+    CCM_HIP(hipHostMalloc(&h, 64 + ccm::kSumBytes, hipHostMallocDefault));
+    hipError_t e = hipMalloc(&p, ccm::kRangeBytes + 256 + ccm::kSumBytes);
+    if (e != hipSuccess) {
+      (void)hipHostFree(h);
+      return dev_err(e, "hipMalloc");
+    }
+    std::memset(h, 0, 64);
+    c.host = (ccm::RangeHost *)h;
+    c.words = (uint64_t *)((char *)h + 64);
+    c.full = (uint32_t *)((char *)p + ccm::kRangeBytes);
     c.sums = (uint64_t *)((char *)p + ccm::kRangeBytes + 256);
-    void *h = nullptr;
-    CCM_HIP(hipHostMalloc(&h, ccm::kRangeBytes + 64 + ccm::kSumBytes, hipHostMallocDefault));
-    c.host = (ccm::RangeSlot *)h;
+    c.slot = (ccm::RangeSlot *)p;
   }
   *out = &c;
   return CCM_OK;
 }
 
-// Copies the spread range slots back and folds them into one result.
-int read_slot(DeviceCtx *c, hipStream_t s, ccm::RangeSlot *res) {
-  CCM_HIP(hipMemcpyAsync(c->host, c->slot, ccm::kRangeBytes, hipMemcpyDeviceToHost, s));
-  CCM_HIP(hipStreamSynchronize(s));
-  ccm::RangeSlot r = c->host[0];
-  for (int i = 1; i < ccm::kRangeSpread; ++i) {
-    const ccm::RangeSlot &t = c->host[ccm::kRangeStride * i];
-    r.vmin = t.vmin < r.vmin ? t.vmin : r.vmin;
-    r.vmax = t.vmax > r.vmax ? t.vmax : r.vmax;
-    r.flag |= t.flag;
+// The sink of the next blocking pass on s.  `armed` is false from here until
+// the pass's record has been read: a pass that failed in between leaves the
+// next one to arm the slots itself.
+int next_sink(DeviceCtx *c, hipStream_t s, ccm::RangeSink *sink) {
+  if (!c->armed) CCM_HIP(ccm::launch_range_init(c->slot, c->full, s));
+  c->armed = false;
+  if (++c->seq == 0) c->seq = 1;
+  *sink = ccm::RangeSink{c->slot, c->host, c->full, c->seq};
+  return CCM_OK;
+}
+
+bool record_ready(const DeviceCtx *c) {
+  return __atomic_load_n(&c->host->seq, __ATOMIC_ACQUIRE) == c->seq;
+}
+
+// Waits for the pass's record.  Where the kernel that publishes it wrote no
+// other device memory -- a pass that only read is done once every block has
+// folded, a pass that published from a kernel of its own has ended before that
+// one began -- short passes are polled for (a stream wait takes 5 us more).
+// Long ones, and passes that store results beside their range (`wrote`), are
+// waited for through the stream.
+int read_range(DeviceCtx *c, hipStream_t s, bool wrote, ccm::RangeHost *res) {
+  constexpr int kPolls = 1 << 13;  // some hundred us
+  bool ready = false;
+  for (int i = 0; !wrote && i < kPolls && !(ready = record_ready(c)); ++i) __builtin_ia32_pause();
+  if (!ready) {
+    CCM_HIP(hipStreamSynchronize(s));
+    if (!record_ready(c)) return CCM_E_DEVICE;
   }
-  *res = r;
+  *res = *c->host;
+  c->armed = true;
   return CCM_OK;
 }
 
@@ -249,12 +283,14 @@ int ccm_range(const void *dense, int32_t dtype, int64_t n, int64_t *vmin, int64_
   hipStream_t s = (hipStream_t)stream;
   std::lock_guard<std::mutex> lk(g_mu);
   DeviceCtx *c = nullptr;
-  int rc = device_ctx(&c);
+  int rc = device_ctx(s, &c);
   if (rc != CCM_OK) return rc;
-  CCM_HIP(ccm::launch_range_init(c->slot, s));
-  CCM_HIP(ccm::launch_range_dense(dense, dtype, (uint64_t)n, c->slot, s));
-  ccm::RangeSlot r;
-  rc = read_slot(c, s, &r);
+  ccm::RangeSink sink;
+  rc = next_sink(c, s, &sink);
+  if (rc != CCM_OK) return rc;
+  CCM_HIP(ccm::launch_range_dense(dense, dtype, (uint64_t)n, sink, s));
+  ccm::RangeHost r;
+  rc = read_range(c, s, false, &r);
   if (rc != CCM_OK) return rc;
   *vmin = r.vmin;
   *vmax = r.vmax;
@@ -297,14 +333,17 @@ int ccm_get(const ccm_desc *a, int64_t i, int64_t j, int64_t *value, void *strea
   hipStream_t s = (hipStream_t)stream;
   std::lock_guard<std::mutex> lk(g_mu);
   DeviceCtx *c = nullptr;
-  rc = device_ctx(&c);
+  rc = device_ctx(s, &c);
+  if (rc != CCM_OK) return rc;
+  ccm::RangeSink sink;
+  rc = next_sink(c, s, &sink);
   if (rc != CCM_OK) return rc;
   CCM_HIP(ccm::launch_get_one((const uint32_t *)a->payload, (uint64_t)(i * a->cols + j), a->bits,
-                              a->is_signed, c->one, s));
-  int64_t *h = (int64_t *)((char *)c->host + ccm::kRangeBytes);
-  CCM_HIP(hipMemcpyAsync(h, c->one, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-  CCM_HIP(hipStreamSynchronize(s));
-  *value = *h;
+                              a->is_signed, sink.host, sink.seq, s));
+  ccm::RangeHost r;
+  rc = read_range(c, s, false, &r);
+  if (rc != CCM_OK) return rc;
+  *value = r.vmin;
   return CCM_OK;
 }
 
@@ -350,13 +389,15 @@ int ccm_add_plan(const ccm_desc *a, const ccm_desc *b, ccm_desc *out, void *stre
   hipStream_t s = (hipStream_t)stream;
   std::lock_guard<std::mutex> lk(g_mu);
   DeviceCtx *c = nullptr;
-  rc = device_ctx(&c);
+  rc = device_ctx(s, &c);
   if (rc != CCM_OK) return rc;
-  CCM_HIP(ccm::launch_range_init(c->slot, s));
+  ccm::RangeSink sink;
+  rc = next_sink(c, s, &sink);
+  if (rc != CCM_OK) return rc;
   CCM_HIP(ccm::launch_ewise_range(ccm::EW_ADD, operand(a), operand(b), 0, nelem(a),
-                                  add_class(a, b), c->slot, s));
-  ccm::RangeSlot r;
-  rc = read_slot(c, s, &r);
+                                  add_class(a, b), sink, s));
+  ccm::RangeHost r;
+  rc = read_range(c, s, false, &r);
   if (rc != CCM_OK) return rc;
   if (r.flag) return CCM_E_OVERFLOW;
   return fill_desc(a->rows, a->cols, r.vmin, r.vmax, out);
@@ -415,19 +456,21 @@ int ccm_add_onepass(const ccm_desc *a, const ccm_desc *b, ccm_desc *out, void *s
   hipStream_t s = (hipStream_t)stream;
   std::lock_guard<std::mutex> lk(g_mu);
   DeviceCtx *c = nullptr;
-  rc = device_ctx(&c);
+  rc = device_ctx(s, &c);
   if (rc != CCM_OK) return rc;
   ccm_desc bound, exact;
   int64_t lo, hi;
-  ccm::RangeSlot r;
+  ccm::RangeHost r;
+  ccm::RangeSink sink;
+  rc = next_sink(c, s, &sink);
+  if (rc != CCM_OK) return rc;
   if (n > 0 && add_bound(a, b, &lo, &hi) &&
       fill_desc(a->rows, a->cols, lo, hi, &bound) == CCM_OK) {
     // one pass: pack at the bounded width, learn the exact range meanwhile
-    CCM_HIP(ccm::launch_range_init(c->slot, s));
     CCM_HIP(ccm::launch_add_pack_range(operand(a), operand(b), n, vclass, bound.bits,
                                        (uint32_t *)payload, ccm::cap_words32(n, bound.bits),
-                                       c->slot, s));
-    rc = read_slot(c, s, &r);
+                                       sink, s));
+    rc = read_range(c, s, false, &r);  // published from a kernel of its own
     if (rc != CCM_OK) return rc;
     rc = fill_desc(a->rows, a->cols, r.vmin, r.vmax, &exact);
     if (rc != CCM_OK) return rc;
@@ -444,9 +487,8 @@ int ccm_add_onepass(const ccm_desc *a, const ccm_desc *b, ccm_desc *out, void *s
     return CCM_OK;
   }
   // a bound past int64: the range pass first (it detects overflow), then the pack
-  CCM_HIP(ccm::launch_range_init(c->slot, s));
-  CCM_HIP(ccm::launch_ewise_range(ccm::EW_ADD, operand(a), operand(b), 0, n, vclass, c->slot, s));
-  rc = read_slot(c, s, &r);
+  CCM_HIP(ccm::launch_ewise_range(ccm::EW_ADD, operand(a), operand(b), 0, n, vclass, sink, s));
+  rc = read_range(c, s, false, &r);
   if (rc != CCM_OK) return rc;
   if (r.flag) return CCM_E_OVERFLOW;
   rc = fill_desc(a->rows, a->cols, r.vmin, r.vmax, &exact);
@@ -556,13 +598,13 @@ static int matmul_common(const ccm_desc *a, const ccm_desc *b, uint64_t scratch_
 
 // The digits' 16-byte copies need an aligned scratch; the int64 path does not.
 static hipError_t matmul_run(const ccm_desc *a, const ccm_desc *b, const MatmulPlan &p,
-                             void *scratch, uint64_t scratch_bytes, ccm::RangeSlot *slot,
+                             void *scratch, uint64_t scratch_bytes, ccm::RangeSink sink,
                              hipStream_t s) {
   const bool digits = scratch_bytes >= p.total && (p.i8 || (uintptr_t)scratch % 16 == 0);
   return ccm::launch_matmul((const uint32_t *)a->payload, a->bits, a->is_signed,
                             (const uint32_t *)b->payload, b->bits, b->is_signed, a->rows, a->cols,
                             b->cols, p.i8, p.out32, scratch, p.c_bytes,
-                            digits ? p.total : p.c_bytes, slot, s);
+                            digits ? p.total : p.c_bytes, sink, s);
 }
 
 int ccm_matmul_plan(const ccm_desc *a, const ccm_desc *b, ccm_desc *out, void *scratch,
@@ -574,12 +616,14 @@ int ccm_matmul_plan(const ccm_desc *a, const ccm_desc *b, ccm_desc *out, void *s
   hipStream_t s = (hipStream_t)stream;
   std::lock_guard<std::mutex> lk(g_mu);
   DeviceCtx *c = nullptr;
-  rc = device_ctx(&c);
+  rc = device_ctx(s, &c);
   if (rc != CCM_OK) return rc;
-  CCM_HIP(ccm::launch_range_init(c->slot, s));
-  CCM_HIP(matmul_run(a, b, mp, scratch, scratch_bytes, c->slot, s));
-  ccm::RangeSlot r;
-  rc = read_slot(c, s, &r);
+  ccm::RangeSink sink;
+  rc = next_sink(c, s, &sink);
+  if (rc != CCM_OK) return rc;
+  CCM_HIP(matmul_run(a, b, mp, scratch, scratch_bytes, sink, s));
+  ccm::RangeHost r;
+  rc = read_range(c, s, true, &r);
   if (rc != CCM_OK) return rc;
   return fill_desc(a->rows, b->cols, r.vmin, r.vmax, out);
 }
@@ -629,19 +673,20 @@ int ccm_add_async(const ccm_desc *a, const ccm_desc *b, void *payload, uint64_t 
   uint32_t *out = (uint32_t *)payload;
   ccm_desc bound;
   int64_t lo, hi;
-  CCM_HIP(ccm::launch_range_init(slots, s));
+  CCM_HIP(ccm::launch_range_init(slots, nullptr, s));
+  const ccm::RangeSink sink{slots, nullptr, nullptr, 0};
   if (add_bound(a, b, &lo, &hi) && fill_desc(a->rows, a->cols, lo, hi, &bound) == CCM_OK) {
     // pack at the bounded width while the exact range folds into the slots;
     // the device then repacks only if the exact width is narrower
     CCM_HIP(ccm::launch_add_pack_range(operand(a), operand(b), n, vclass, bound.bits, out,
-                                       ccm::cap_words32(n, bound.bits), slots, s));
+                                       ccm::cap_words32(n, bound.bits), sink, s));
     CCM_HIP(ccm::launch_result_finalize(slots, a->rows, a->cols, 0, res, s));
     CCM_HIP(ccm::launch_ewise_pack_dev(ccm::EW_ADD, operand(a), operand(b), 0, n, vclass,
                                        bound.bits, bound.bits, out, res, s));
     return CCM_OK;
   }
   // a bound past int64: the range pass (which flags overflow), then the pack
-  CCM_HIP(ccm::launch_ewise_range(ccm::EW_ADD, operand(a), operand(b), 0, n, vclass, slots, s));
+  CCM_HIP(ccm::launch_ewise_range(ccm::EW_ADD, operand(a), operand(b), 0, n, vclass, sink, s));
   CCM_HIP(ccm::launch_result_finalize(slots, a->rows, a->cols, 1, res, s));
   CCM_HIP(ccm::launch_ewise_pack_dev(ccm::EW_ADD, operand(a), operand(b), 0, n, vclass, 64, 0,
                                      out, res, s));
@@ -679,8 +724,9 @@ int ccm_matmul_async(const ccm_desc *a, const ccm_desc *b, void *payload,
   if (!matmul_max_bits(a, b, &max_bits)) return CCM_E_OVERFLOW;
   if (payload_bytes < ccm_payload_capacity(a->rows, b->cols, max_bits)) return CCM_E_NOMEM;
   hipStream_t s = (hipStream_t)stream;
-  CCM_HIP(ccm::launch_range_init(slots, s));
-  CCM_HIP(matmul_run(a, b, mp, scratch, scratch_bytes, slots, s));
+  CCM_HIP(ccm::launch_range_init(slots, nullptr, s));
+  const ccm::RangeSink sink{slots, nullptr, nullptr, 0};
+  CCM_HIP(matmul_run(a, b, mp, scratch, scratch_bytes, sink, s));
   CCM_HIP(ccm::launch_result_finalize(slots, a->rows, b->cols, 0, res, s));
   CCM_HIP(ccm::launch_compress_dev(scratch, mp.out32 ? CCM_I32 : CCM_I64,
                                    (uint64_t)a->rows * (uint64_t)b->cols, max_bits,
@@ -722,13 +768,15 @@ int ccm_generate_plan(int64_t rows, int64_t cols, int64_t lo, int64_t hi, uint64
   hipStream_t s = (hipStream_t)stream;
   std::lock_guard<std::mutex> lk(g_mu);
   DeviceCtx *c = nullptr;
-  int rc = device_ctx(&c);
+  int rc = device_ctx(s, &c);
   if (rc != CCM_OK) return rc;
-  CCM_HIP(ccm::launch_range_init(c->slot, s));
+  ccm::RangeSink sink;
+  rc = next_sink(c, s, &sink);
+  if (rc != CCM_OK) return rc;
   CCM_HIP(ccm::launch_gen_range((uint64_t)rows * (uint64_t)cols, lo, span, seed, stream_id,
-                                c->slot, s));
-  ccm::RangeSlot r;
-  rc = read_slot(c, s, &r);
+                                sink, s));
+  ccm::RangeHost r;
+  rc = read_range(c, s, false, &r);
   if (rc != CCM_OK) return rc;
   return fill_desc(rows, cols, r.vmin, r.vmax, out);
 }
@@ -765,14 +813,16 @@ int ccm_method_plan(const void *dense, int32_t dtype, int64_t rows, int64_t cols
   hipStream_t s = (hipStream_t)stream;
   std::lock_guard<std::mutex> lk(g_mu);
   DeviceCtx *c = nullptr;
-  int rc = device_ctx(&c);
+  int rc = device_ctx(s, &c);
   if (rc != CCM_OK) return rc;
-  CCM_HIP(ccm::launch_range_init(c->slot, s));
-  CCM_HIP(ccm::launch_method_stats(dense, dtype, n, c->slot, c->sums, s));
-  uint64_t *hs = (uint64_t *)((char *)c->host + ccm::kRangeBytes + 64);
+  ccm::RangeSink sink;
+  rc = next_sink(c, s, &sink);
+  if (rc != CCM_OK) return rc;
+  CCM_HIP(ccm::launch_method_stats(dense, dtype, n, sink, c->sums, s));
+  uint64_t *hs = c->words;
   CCM_HIP(hipMemcpyAsync(hs, c->sums, ccm::kSumBytes, hipMemcpyDeviceToHost, s));
-  ccm::RangeSlot r;
-  rc = read_slot(c, s, &r);  // synchronizes the stream
+  ccm::RangeHost r;
+  rc = read_range(c, s, true, &r);  // synchronizes the stream
   if (rc != CCM_OK) return rc;
   uint64_t su = 0, ss = 0;
   for (int i = 0; i < ccm::kRangeSpread; ++i) {
@@ -875,12 +925,14 @@ int ccm_float_absmax(const void *v, int32_t dtype, int64_t n, double *absmax, vo
   hipStream_t s = (hipStream_t)stream;
   std::lock_guard<std::mutex> lk(g_mu);
   DeviceCtx *c = nullptr;
-  int rc = device_ctx(&c);
+  int rc = device_ctx(s, &c);
   if (rc != CCM_OK) return rc;
-  CCM_HIP(ccm::launch_range_init(c->slot, s));
-  CCM_HIP(ccm::launch_float_absmax(v, dtype, (uint64_t)n, c->slot, s));
-  ccm::RangeSlot r;
-  rc = read_slot(c, s, &r);
+  ccm::RangeSink sink;
+  rc = next_sink(c, s, &sink);
+  if (rc != CCM_OK) return rc;
+  CCM_HIP(ccm::launch_float_absmax(v, dtype, (uint64_t)n, sink, s));
+  ccm::RangeHost r;
+  rc = read_range(c, s, false, &r);
   if (rc != CCM_OK) return rc;
   if (r.vmax >= 0x7FF0000000000000ll) return CCM_E_RANGE;  // NaN or infinity
   double a;
@@ -910,12 +962,14 @@ int ccm_quantize(const void *v, int32_t dtype, int64_t n, int32_t frac_bits, voi
   hipStream_t s = (hipStream_t)stream;
   std::lock_guard<std::mutex> lk(g_mu);
   DeviceCtx *c = nullptr;
-  int rc = device_ctx(&c);
+  int rc = device_ctx(s, &c);
   if (rc != CCM_OK) return rc;
-  CCM_HIP(ccm::launch_range_init(c->slot, s));
-  CCM_HIP(ccm::launch_quantize(v, dtype, (uint64_t)n, frac_bits, q, qdtype, c->slot, s));
-  ccm::RangeSlot r;
-  rc = read_slot(c, s, &r);
+  ccm::RangeSink sink;
+  rc = next_sink(c, s, &sink);
+  if (rc != CCM_OK) return rc;
+  CCM_HIP(ccm::launch_quantize(v, dtype, (uint64_t)n, frac_bits, q, qdtype, sink, s));
+  ccm::RangeHost r;
+  rc = read_range(c, s, q != nullptr, &r);
   if (rc != CCM_OK) return rc;
   if (r.flag) return CCM_E_RANGE;
   if (r.vmax == INT64_MAX) return CCM_E_OVERFLOW;
@@ -1071,15 +1125,17 @@ int ccm_vlb_compress_plan(const void *dense, int32_t dtype, int64_t rows, int64_
   uint32_t *grp = (uint32_t *)((char *)index + vlb_grp_offset(rows));
   std::lock_guard<std::mutex> lk(g_mu);
   DeviceCtx *c = nullptr;
-  rc = device_ctx(&c);
+  rc = device_ctx(s, &c);
   if (rc != CCM_OK) return rc;
-  CCM_HIP(ccm::launch_range_init(c->slot, s));
-  CCM_HIP(ccm::launch_vlb_sizes(dense, dtype, rows, cols, k, lo < 0 ? 1 : 0, grp, c->slot, s));
+  ccm::RangeSink sink;
+  rc = next_sink(c, s, &sink);
+  if (rc != CCM_OK) return rc;
+  CCM_HIP(ccm::launch_vlb_sizes(dense, dtype, rows, cols, k, lo < 0 ? 1 : 0, grp, sink, s));
   CCM_HIP(ccm::launch_vlb_scan(rows, cols, grp, row_bit, s));
-  uint64_t *h = (uint64_t *)((char *)c->host + ccm::kRangeBytes);
+  uint64_t *h = c->words;
   CCM_HIP(hipMemcpyAsync(h, row_bit + rows, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
-  ccm::RangeSlot gr;
-  rc = read_slot(c, s, &gr);  // synchronizes the stream
+  ccm::RangeHost gr;
+  rc = read_range(c, s, true, &gr);  // synchronizes the stream
   if (rc != CCM_OK) return rc;
   out->rows = rows;
   out->cols = cols;
@@ -1120,13 +1176,16 @@ int ccm_vlb_get(const ccm_vlb_desc *a, int64_t i, int64_t j, int64_t *value, voi
   hipStream_t s = (hipStream_t)stream;
   std::lock_guard<std::mutex> lk(g_mu);
   DeviceCtx *c = nullptr;
-  rc = device_ctx(&c);
+  rc = device_ctx(s, &c);
   if (rc != CCM_OK) return rc;
-  CCM_HIP(ccm::launch_vlb_get(vlb_view(a), i, j, c->one, s));
-  int64_t *h = (int64_t *)((char *)c->host + ccm::kRangeBytes);
-  CCM_HIP(hipMemcpyAsync(h, c->one, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-  CCM_HIP(hipStreamSynchronize(s));
-  *value = *h;
+  ccm::RangeSink sink;
+  rc = next_sink(c, s, &sink);
+  if (rc != CCM_OK) return rc;
+  CCM_HIP(ccm::launch_vlb_get(vlb_view(a), i, j, sink.host, sink.seq, s));
+  ccm::RangeHost r;
+  rc = read_range(c, s, false, &r);
+  if (rc != CCM_OK) return rc;
+  *value = r.vmin;
   return CCM_OK;
 }
 

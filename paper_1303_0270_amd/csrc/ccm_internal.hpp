@@ -265,27 +265,77 @@ struct alignas(32) RangeSlot {
   int64_t vmin;
   int64_t vmax;
   int32_t flag;
-  int32_t pad;
+  uint32_t done;  // blocks that have folded into this slot
 };
 
 // A range result lives in kRangeSpread slots, one 128-byte line apart: block
 // i folds into slot i % kRangeSpread, so a few thousand blocks do not
 // serialize on one address (same-address device atomics cost tens of ns
-// each); the host folds the slots after the copy back.
+// each).
 constexpr int kRangeSpread = 64;
 constexpr int kRangeStride = 4;  // RangeSlot units per slot (128 bytes)
 constexpr size_t kRangeBytes = sizeof(RangeSlot) * kRangeStride * kRangeSpread;
 static_assert(sizeof(RangeSlot) * kRangeStride == 128, "one range slot per 128-byte line");
+
+// A folded range in host memory (pinned, written by the device): valid once
+// seq holds the number of the launch that was to write it.
+struct RangeHost {
+  int64_t vmin;
+  int64_t vmax;
+  int32_t flag;
+  uint32_t seq;
+};
+
+// Where a range pass folds: the slots, and for a pass the host waits for
+// (host not null) the record its last block writes, re-arming the slots for
+// the next pass.  `full` counts the slots whose blocks have all folded.  The
+// host then waits for one kernel and reads 24 bytes; with a kernel before to
+// initialise the slots and a copy of all of them after it the same wait took
+// 18 us where this takes 7 (a one-block pass).
+struct RangeSink {
+  RangeSlot *slot;
+  RangeHost *host;
+  uint32_t *full;
+  uint32_t seq;
+};
 
 // Spread 64-bit sums (pairs), laid out like the range slots: pair i at
 // uint64 offset 2 * kSumStride * i (128 bytes apart).
 constexpr int kSumStride = 8;
 constexpr size_t kSumBytes = sizeof(uint64_t) * 2 * kSumStride * kRangeSpread;
 
+// One wave (all 64 lanes): folds the slots, re-arms them, writes the record.
+// The slots are read and written past the caches that are not coherent across
+// the chip's dies (agent scope), and the record's number is released after
+// everything else, so a pass launched on any stream once the host has seen the
+// number finds armed slots.
+__device__ inline void range_publish(const RangeSink &sk) {
+  const int lane = threadIdx.x & 63;
+  RangeSlot *r = sk.slot + kRangeStride * lane;
+  int64_t lo = __hip_atomic_load(&r->vmin, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  int64_t hi = __hip_atomic_load(&r->vmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int fl = __hip_atomic_load(&r->flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(&r->vmin, INT64_MAX, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(&r->vmax, INT64_MIN, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(&r->flag, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(&r->done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (lane == 0) __hip_atomic_store(sk.full, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  lo = wave_min(lo);
+  hi = wave_max(hi);
+  const int f = __any(fl) ? 1 : 0;
+  __threadfence_system();  // every lane's stores, before the number
+  if (lane == 0) {
+    __hip_atomic_store(&sk.host->vmin, lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&sk.host->vmax, hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&sk.host->flag, f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&sk.host->seq, sk.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
+
 // Block-wide (min, max, flag) folded into the block's slot of a spread range
-// result with one atomic each per block.  Every thread of the block must call
-// it.
-__device__ inline void block_range_commit(int64_t lo, int64_t hi, int flag, RangeSlot *slot) {
+// result with one atomic each per block; with a host record, the last block
+// to fold publishes the result.  Every thread of the block must call it.
+__device__ inline void block_range_commit(int64_t lo, int64_t hi, int flag, const RangeSink &sk) {
   __shared__ int64_t s_lo[16], s_hi[16];
   __shared__ int s_flag[16];
   lo = wave_min(lo);
@@ -298,8 +348,11 @@ __device__ inline void block_range_commit(int64_t lo, int64_t hi, int flag, Rang
     s_flag[wave] = wf;
   }
   __syncthreads();
+  if (threadIdx.x >= 64) return;
+  bool last = false;
   if (threadIdx.x == 0) {
-    slot += kRangeStride * ((blockIdx.x + blockIdx.y * gridDim.x) % kRangeSpread);
+    const uint32_t nb = gridDim.x * gridDim.y, id = blockIdx.x + blockIdx.y * gridDim.x;
+    RangeSlot *slot = sk.slot + kRangeStride * (id % kRangeSpread);
     const int nw = (blockDim.x + 63) >> 6;
     for (int w = 1; w < nw; ++w) {
       lo = s_lo[w] < lo ? s_lo[w] : lo;
@@ -310,22 +363,36 @@ __device__ inline void block_range_commit(int64_t lo, int64_t hi, int flag, Rang
     atomicMin((long long *)&slot->vmin, (long long)lo);
     atomicMax((long long *)&slot->vmax, (long long)hi);
     if (f) atomicOr(&slot->flag, 1);
+    if (sk.host) {
+      // this block's atomics have been carried out before it counts itself
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      const uint32_t share = nb / kRangeSpread + (id % kRangeSpread < nb % kRangeSpread ? 1 : 0);
+      if (atomicAdd(&slot->done, 1u) + 1 == share)
+        last = atomicAdd(sk.full, 1u) + 1 == (nb < kRangeSpread ? nb : kRangeSpread);
+    }
   }
+  if (sk.host && __any(last)) range_publish(sk);
 }
 
 // ---------------------------------------------------------------------------
 // Launchers (each returns the launch's hipError_t)
 // ---------------------------------------------------------------------------
 
-hipError_t launch_range_init(RangeSlot *slot, hipStream_t s);
-hipError_t launch_range_dense(const void *dense, int dtype, uint64_t n, RangeSlot *slot,
+// Arms the slots (and, for passes the host waits for, their count of full
+// slots; full may be null).
+hipError_t launch_range_init(RangeSlot *slot, uint32_t *full, hipStream_t s);
+// Folds and publishes the slots of a pass that cannot do it itself (one
+// block per 256 groups: too many to count).
+hipError_t launch_range_publish(RangeSink sink, hipStream_t s);
+hipError_t launch_range_dense(const void *dense, int dtype, uint64_t n, RangeSink sink,
                               hipStream_t s);
 hipError_t launch_compress(const void *dense, int dtype, uint64_t n, int bits, uint32_t *out,
                            uint64_t cap32, hipStream_t s);
 hipError_t launch_decompress(const uint32_t *w, uint64_t n, int bits, int sgn, int64_t *out,
                              hipStream_t s);
-hipError_t launch_get_one(const uint32_t *w, uint64_t e, int bits, int sgn, int64_t *out,
-                          hipStream_t s);
+// one element into the host record's vmin
+hipError_t launch_get_one(const uint32_t *w, uint64_t e, int bits, int sgn, RangeHost *host,
+                          uint32_t seq, hipStream_t s);
 hipError_t launch_gather(const uint32_t *w, int64_t rows, int64_t cols, int bits, int sgn,
                          const int64_t *ii, const int64_t *jj, int64_t n, int64_t *out,
                          int32_t *bad, hipStream_t s);
@@ -342,15 +409,15 @@ struct PackedOperand {
   int sgn;
 };
 hipError_t launch_ewise_range(int op, PackedOperand a, PackedOperand b, int64_t scalar,
-                              uint64_t n, int vclass, RangeSlot *slot, hipStream_t s);
+                              uint64_t n, int vclass, RangeSink sink, hipStream_t s);
 hipError_t launch_ewise_pack(int op, PackedOperand a, PackedOperand b, int64_t scalar,
                              uint64_t n, int vclass, int out_bits, uint32_t *out, uint64_t cap32,
                              hipStream_t s);
 // A + B packed at out_bits (at most 32 for the 32-bit classes) while the
-// exact extremes of the sums fold into slot, which the caller initialised.
+// exact extremes of the sums fold into slot, armed by the caller.
 // The caller guarantees that no sum leaves int64 (the headers bound them).
 hipError_t launch_add_pack_range(PackedOperand a, PackedOperand b, uint64_t n, int vclass,
-                                 int out_bits, uint32_t *out, uint64_t cap32, RangeSlot *slot,
+                                 int out_bits, uint32_t *out, uint64_t cap32, RangeSink sink,
                                  hipStream_t s);
 
 hipError_t launch_fill_i64(int64_t *p, uint64_t n, int64_t v, hipStream_t s);
@@ -358,11 +425,11 @@ hipError_t launch_fill_i64(int64_t *p, uint64_t n, int64_t v, hipStream_t s);
 // slot's vmax; q = RNE(v 2^f) as int64 or int32 (q null: not written) with
 // q's range in slot (flag:
 // NaN or infinity; vmax INT64_MAX: some |v 2^f| >= 2^62 or q outside the
-// output type); out = q 2^-f (slots initialised by launch_range_init)
-hipError_t launch_float_absmax(const void *v, int dtype, uint64_t n, RangeSlot *slot,
+// output type); out = q 2^-f (armed slots)
+hipError_t launch_float_absmax(const void *v, int dtype, uint64_t n, RangeSink sink,
                                hipStream_t s);
 hipError_t launch_quantize(const void *v, int dtype, uint64_t n, int frac_bits, void *q,
-                           int qdtype, RangeSlot *slot, hipStream_t s);
+                           int qdtype, RangeSink sink, hipStream_t s);
 hipError_t launch_dequantize(const int64_t *q, uint64_t n, int frac_bits, int dtype, void *out,
                              hipStream_t s);
 // packs RNE(v 2^f) at `bits` straight from n floats (values checked before)
@@ -426,7 +493,7 @@ uint64_t matmul_fast_bytes(int abits, int asgn, int bbits, int bsgn, int64_t M, 
                            int64_t N, int i8);
 hipError_t launch_matmul(const uint32_t *aw, int abits, int asgn, const uint32_t *bw,
                          int bbits, int bsgn, int64_t M, int64_t K, int64_t N, int i8, int out32,
-                         void *scratch, uint64_t c_bytes, uint64_t scratch_bytes, RangeSlot *slot,
+                         void *scratch, uint64_t c_bytes, uint64_t scratch_bytes, RangeSink sink,
                          hipStream_t s);
 
 // Method 2 (variable length blocks): stream, index and shape of one matrix.
@@ -443,9 +510,9 @@ struct VlbView {
 };
 uint64_t vlb_ngr(int64_t cols);
 // pass 1: grp[i][g] = bits of group g of row i (sum of k + b_e); the largest
-// folds into slot's vmax (slot initialised by launch_range_init)
+// folds into slot's vmax (armed slots)
 hipError_t launch_vlb_sizes(const void *dense, int dtype, int64_t rows, int64_t cols, int k,
-                            int sgn, uint32_t *grp, RangeSlot *slot, hipStream_t s);
+                            int sgn, uint32_t *grp, RangeSink sink, hipStream_t s);
 // pass 2: counts -> offsets within rows, row starts and the total in row_bit
 hipError_t launch_vlb_scan(int64_t rows, int64_t cols, uint32_t *grp, uint64_t *row_bit,
                            hipStream_t s);
@@ -453,14 +520,15 @@ hipError_t launch_vlb_scan(int64_t rows, int64_t cols, uint32_t *grp, uint64_t *
 hipError_t launch_vlb_pack(const void *dense, int dtype, const VlbView &a, uint32_t *out,
                            uint64_t cap32, uint64_t nbits, hipStream_t s);
 hipError_t launch_vlb_decode(const VlbView &a, int64_t *out, hipStream_t s);
-hipError_t launch_vlb_get(const VlbView &a, int64_t i, int64_t j, int64_t *out, hipStream_t s);
+hipError_t launch_vlb_get(const VlbView &a, int64_t i, int64_t j, RangeHost *host, uint32_t seq,
+                          hipStream_t s);
 hipError_t launch_vlb_matvec(const VlbView &a, const void *x, int xdtype, int64_t *y,
                              hipStream_t s);
 
-// One pass for the method choice: (min, max) into slot (initialised by
-// launch_range_init) and, into the spread pairs `sums`, the sums of the
+// One pass for the method choice: (min, max) into the sink's slots (
+// armed) and, into the spread pairs `sums`, the sums of the
 // unsigned and of the two's complement element widths (zeroed here).
-hipError_t launch_method_stats(const void *dense, int dtype, uint64_t n, RangeSlot *slot,
+hipError_t launch_method_stats(const void *dense, int dtype, uint64_t n, RangeSink sink,
                                uint64_t *sums, hipStream_t s);
 
 // synthetic data
@@ -468,7 +536,7 @@ hipError_t launch_fill_uniform(void *dense, int dtype, uint64_t n, int64_t lo, u
                                uint64_t seed, uint64_t stream_id, uint64_t start,
                                hipStream_t s);
 hipError_t launch_gen_range(uint64_t n, int64_t lo, uint64_t span, uint64_t seed,
-                            uint64_t stream_id, RangeSlot *slot, hipStream_t s);
+                            uint64_t stream_id, RangeSink sink, hipStream_t s);
 hipError_t launch_gen_pack(uint64_t n, int64_t lo, uint64_t span, uint64_t seed,
                            uint64_t stream_id, int bits, uint32_t *out, uint64_t cap32,
                            hipStream_t s);

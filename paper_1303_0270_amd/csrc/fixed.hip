@@ -27,7 +27,7 @@ __device__ __forceinline__ int64_t abs_bits(double v) {
 
 template <typename F>
 __global__ __launch_bounds__(kFxThreads) void k_float_absmax(const F *__restrict__ v, uint64_t n,
-                                                             RangeSlot *slot) {
+                                                             RangeSink sink) {
   int64_t hi = 0;
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -46,7 +46,7 @@ __global__ __launch_bounds__(kFxThreads) void k_float_absmax(const F *__restrict
     const int64_t b = abs_bits((double)v[i]);
     hi = b > hi ? b : hi;
   }
-  block_range_commit(INT64_MAX, hi, 0, slot);
+  block_range_commit(INT64_MAX, hi, 0, sink);
 }
 
 // q = RNE(v 2^f) with the range of q folded into slot.  A NaN or infinity
@@ -58,7 +58,7 @@ __global__ __launch_bounds__(kFxThreads) void k_float_absmax(const F *__restrict
 template <typename F, typename Q>
 __global__ __launch_bounds__(kFxThreads) void k_quantize(const F *__restrict__ v, uint64_t n,
                                                          int f, Q *__restrict__ q,
-                                                         RangeSlot *slot) {
+                                                         RangeSink sink) {
   int64_t lo = INT64_MAX, hi = INT64_MIN;
   int bad = 0;
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(kFxThreads) void k_quantize(const F *__restrict__ v
     for (int u = 0; u < 4; ++u) one(t[u], i + u * stride);
   }
   for (; i < n; i += stride) one(v[i], i);
-  block_range_commit(lo, hi, bad, slot);
+  block_range_commit(lo, hi, bad, sink);
 }
 
 template <typename F>
@@ -174,30 +174,30 @@ unsigned fx_grid(uint64_t n) {
 
 }  // namespace
 
-hipError_t launch_float_absmax(const void *v, int dtype, uint64_t n, RangeSlot *slot,
+hipError_t launch_float_absmax(const void *v, int dtype, uint64_t n, RangeSink sink,
                                hipStream_t s) {
   if (dtype == CCM_F64)
-    k_float_absmax<double><<<fx_grid(n), kFxThreads, 0, s>>>((const double *)v, n, slot);
+    k_float_absmax<double><<<fx_grid(n), kFxThreads, 0, s>>>((const double *)v, n, sink);
   else
-    k_float_absmax<float><<<fx_grid(n), kFxThreads, 0, s>>>((const float *)v, n, slot);
+    k_float_absmax<float><<<fx_grid(n), kFxThreads, 0, s>>>((const float *)v, n, sink);
   return hipGetLastError();
 }
 
 hipError_t launch_quantize(const void *v, int dtype, uint64_t n, int frac_bits, void *q,
-                           int qdtype, RangeSlot *slot, hipStream_t s) {
+                           int qdtype, RangeSink sink, hipStream_t s) {
   const unsigned g = fx_grid(n);
   if (dtype == CCM_F64 && qdtype == CCM_I64)
     k_quantize<double, int64_t><<<g, kFxThreads, 0, s>>>((const double *)v, n, frac_bits,
-                                                         (int64_t *)q, slot);
+                                                         (int64_t *)q, sink);
   else if (dtype == CCM_F64)
     k_quantize<double, int32_t><<<g, kFxThreads, 0, s>>>((const double *)v, n, frac_bits,
-                                                         (int32_t *)q, slot);
+                                                         (int32_t *)q, sink);
   else if (qdtype == CCM_I64)
     k_quantize<float, int64_t><<<g, kFxThreads, 0, s>>>((const float *)v, n, frac_bits,
-                                                        (int64_t *)q, slot);
+                                                        (int64_t *)q, sink);
   else
     k_quantize<float, int32_t><<<g, kFxThreads, 0, s>>>((const float *)v, n, frac_bits,
-                                                        (int32_t *)q, slot);
+                                                        (int32_t *)q, sink);
   return hipGetLastError();
 }
 

@@ -21,7 +21,7 @@ constexpr int kTM = 64, kTN = 64, kTK = 32, kThreads = 256;
 template <typename ET, typename OT>
 __global__ __launch_bounds__(kThreads) void k_gemm_generic(
     const uint32_t *__restrict__ aw, int abits, int asgn, const uint32_t *__restrict__ bw,
-    int bbits, int bsgn, int64_t M, int64_t K, int64_t N, OT *__restrict__ C, RangeSlot *slot) {
+    int bbits, int bsgn, int64_t M, int64_t K, int64_t N, OT *__restrict__ C, RangeSink sink) {
   __shared__ ET As[kTK][kTM + 1];  // As[k][m]
   __shared__ ET Bs[kTK][kTN + 1];  // Bs[k][n]
   const int64_t m0 = (int64_t)blockIdx.y * kTM, n0 = (int64_t)blockIdx.x * kTN;
@@ -75,20 +75,20 @@ __global__ __launch_bounds__(kThreads) void k_gemm_generic(
       }
     }
   }
-  block_range_commit(lo, hi, 0, slot);
+  block_range_commit(lo, hi, 0, sink);
 }
 
 template <typename ET>
 hipError_t launch_generic(const uint32_t *aw, int abits, int asgn, const uint32_t *bw,
                           int bbits, int bsgn, int64_t M, int64_t K, int64_t N, int out32,
-                          void *scratch, RangeSlot *slot, hipStream_t s) {
+                          void *scratch, RangeSink sink, hipStream_t s) {
   dim3 grid((unsigned)((N + kTN - 1) / kTN), (unsigned)((M + kTM - 1) / kTM));
   if (out32)
     k_gemm_generic<ET, int32_t><<<grid, kThreads, 0, s>>>(aw, abits, asgn, bw, bbits, bsgn, M,
-                                                          K, N, (int32_t *)scratch, slot);
+                                                          K, N, (int32_t *)scratch, sink);
   else
     k_gemm_generic<ET, int64_t><<<grid, kThreads, 0, s>>>(aw, abits, asgn, bw, bbits, bsgn, M,
-                                                          K, N, (int64_t *)scratch, slot);
+                                                          K, N, (int64_t *)scratch, sink);
   return hipGetLastError();
 }
 
@@ -468,7 +468,7 @@ LimbLayout limb_layout(int abits, int asgn, int bbits, int bsgn, int64_t M, int6
 
 hipError_t launch_limbs(const uint32_t *aw, int abits, int asgn, const uint32_t *bw, int bbits,
                         int bsgn, int64_t M, int64_t K, int64_t N, int out32, void *C,
-                        char *extra, RangeSlot *slot, hipStream_t s) {
+                        char *extra, RangeSink sink, hipStream_t s) {
   const LimbLayout p = limb_layout(abits, asgn, bbits, bsgn, M, K, N);
   int8_t *a8 = (int8_t *)extra, *b8 = (int8_t *)extra + p.b_at;
   int64_t *cadd = p.alpha ? (int64_t *)(extra + p.cadd_at) : nullptr;
@@ -499,7 +499,7 @@ hipError_t launch_limbs(const uint32_t *aw, int abits, int asgn, const uint32_t 
       g.cadd = first ? cadd : nullptr;
       g.shift = 8 * (i0 + j0);
       g.accumulate = first ? 0 : 1;
-      g.slot = last ? slot : nullptr;
+      g.sink = last ? sink : RangeSink{};
       e = limb::launch_pass(g, la, lb, out32, s);
       if (e != hipSuccess) return e;
     }
@@ -535,20 +535,20 @@ uint64_t matmul_fast_bytes(int abits, int asgn, int bbits, int bsgn, int64_t M, 
 
 hipError_t launch_matmul(const uint32_t *aw, int abits, int asgn, const uint32_t *bw,
                          int bbits, int bsgn, int64_t M, int64_t K, int64_t N, int i8, int out32,
-                         void *scratch, uint64_t c_bytes, uint64_t scratch_bytes, RangeSlot *slot,
+                         void *scratch, uint64_t c_bytes, uint64_t scratch_bytes, RangeSink sink,
                          hipStream_t s) {
   const uint64_t fast = matmul_fast_bytes(abits, asgn, bbits, bsgn, M, K, N, i8);
   if (fast && scratch_bytes >= c_bytes && scratch_bytes - c_bytes >= fast)
     return launch_limbs(aw, abits, asgn, bw, bbits, bsgn, M, K, N, out32, scratch,
-                        (char *)scratch + c_bytes, slot, s);
+                        (char *)scratch + c_bytes, sink, s);
   // Operands that fit in 32 bits are staged as int32 (products stay exact in
   // int64); wider ones as int64.
   const bool narrow = (abits < 32 || (abits == 32 && asgn)) && (bbits < 32 || (bbits == 32 && bsgn));
   if (narrow)
     return launch_generic<int32_t>(aw, abits, asgn, bw, bbits, bsgn, M, K, N, out32, scratch,
-                                   slot, s);
+                                   sink, s);
   return launch_generic<int64_t>(aw, abits, asgn, bw, bbits, bsgn, M, K, N, out32, scratch,
-                                 slot, s);
+                                 sink, s);
 }
 
 }  // namespace ccm

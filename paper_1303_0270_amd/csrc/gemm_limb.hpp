@@ -87,7 +87,7 @@ struct GemmArgs {
   const int64_t *radd, *cadd;    // per row / column addends (null: none)
   int shift;                     // 8 (first limb of A's chunk + first of B's)
   int accumulate;                // add to C instead of storing
-  RangeSlot *slot;               // exact range of C (null: not the last pass)
+  RangeSink sink;                // exact range of C (null slots: not the last pass)
 };
 
 //   * Block = WGM x WGN waves; each wave owns FM x FN MFMA blocks of 32 x 32
@@ -277,7 +277,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm_limb(GemmArgs p) {
       }
       __builtin_amdgcn_sched_barrier(0);  // one row at a time: no copies of all accumulators
     }
-  if (p.slot) block_range_commit((int64_t)lo, (int64_t)hi, 0, p.slot);
+  if (p.sink.slot) block_range_commit((int64_t)lo, (int64_t)hi, 0, p.sink);
 }
 
 template <int LA, int LB, int FM, int FN, int WGM, int WGN, typename OT, bool CORR>

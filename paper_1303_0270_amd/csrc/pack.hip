@@ -20,19 +20,24 @@ constexpr int kTileThreads = 128;           // lanes per block in the tile kerne
 constexpr int kTileElems = kTileThreads * kGroup;
 constexpr int kPad = kGroup + 1;            // LDS row pitch (elements) of a lane's group
 
-__global__ void k_range_init(RangeSlot *slot) {
+__global__ void k_range_init(RangeSlot *slot, uint32_t *full) {
   if (threadIdx.x < kRangeSpread) {
     RangeSlot *r = slot + kRangeStride * threadIdx.x;
     r->vmin = INT64_MAX;
     r->vmax = INT64_MIN;
     r->flag = 0;
-    r->pad = 0;
+    r->done = 0;
   }
+  if (full && threadIdx.x == 0) *full = 0;
+}
+
+__global__ __launch_bounds__(kRangeSpread) void k_range_publish(RangeSink sink) {
+  range_publish(sink);
 }
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_range_dense(const T *__restrict__ d, uint64_t n,
-                                                     RangeSlot *slot, int aligned16) {
+                                                     RangeSink sink, int aligned16) {
   constexpr int PER = 16 / sizeof(T);  // elements per 16-byte load
   constexpr int UNR = 4;
   int64_t lo = INT64_MAX, hi = INT64_MIN;
@@ -75,7 +80,7 @@ __global__ __launch_bounds__(256) void k_range_dense(const T *__restrict__ d, ui
     lo = x < lo ? x : lo;
     hi = x > hi ? x : hi;
   }
-  block_range_commit(lo, hi, 0, slot);
+  block_range_commit(lo, hi, 0, sink);
 }
 
 // dense (n values) -> packed words [0, cap32): lane g writes words [g*b, g*b+b).
@@ -180,8 +185,10 @@ __global__ void k_gather(const uint32_t *__restrict__ wds, int64_t rows, int64_t
 }
 
 __global__ void k_get_one(const uint32_t *__restrict__ wds, uint64_t e, int bits, int sgn,
-                          int64_t *out) {
-  *out = value_at(wds, e, bits, sgn);
+                          RangeHost *host, uint32_t seq) {
+  __hip_atomic_store(&host->vmin, value_at(wds, e, bits, sgn), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(&host->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // One elementwise result value; returns overflow in *ovf.
@@ -202,7 +209,7 @@ __device__ __forceinline__ int64_t ewise_value(int op, int64_t a, int64_t b, int
 // atomics on the one result slot few).
 __global__ __launch_bounds__(256) void k_ewise_range(int op, PackedOperand a, PackedOperand b,
                                                      int64_t scalar, uint64_t n,
-                                                     RangeSlot *slot) {
+                                                     RangeSink sink) {
   int64_t lo = INT64_MAX, hi = INT64_MIN;
   int ovf = 0;
   const uint64_t ngroups = (n + kGroup - 1) / kGroup;
@@ -221,7 +228,7 @@ __global__ __launch_bounds__(256) void k_ewise_range(int op, PackedOperand a, Pa
       }
     }
   }
-  block_range_commit(lo, hi, ovf, slot);
+  block_range_commit(lo, hi, ovf, sink);
 }
 
 // The range commit for packing grids (one block per 256 groups, so tens of
@@ -340,7 +347,7 @@ __device__ __forceinline__ void ewise_group32(const PackedOperand &a, const Pack
 template <int OP, typename VT>
 __global__ __launch_bounds__(256) void k_ewise_range32(PackedOperand a, PackedOperand b,
                                                        int64_t scalar, uint64_t n,
-                                                       RangeSlot *slot) {
+                                                       RangeSink sink) {
   VT lo = std::numeric_limits<VT>::max(), hi = std::numeric_limits<VT>::min();
   const VT sc = (VT)scalar;
   const uint64_t nfull = n / kGroup;
@@ -362,7 +369,7 @@ __global__ __launch_bounds__(256) void k_ewise_range32(PackedOperand a, PackedOp
       hi = (VT)vc[i] > hi ? (VT)vc[i] : hi;
     }
   }
-  block_range_commit((int64_t)lo, (int64_t)hi, 0, slot);
+  block_range_commit((int64_t)lo, (int64_t)hi, 0, sink);
 }
 
 // Packing pass, 32-bit results: thread t of block x packs group 256 x + t
@@ -521,7 +528,7 @@ __global__ __launch_bounds__(256) void k_fill_uniform(T *d, uint64_t n, int64_t 
 
 __global__ __launch_bounds__(256) void k_gen_range(uint64_t n, int64_t lo, uint64_t span,
                                                    uint64_t seed, uint64_t sid,
-                                                   RangeSlot *slot) {
+                                                   RangeSink sink) {
   int64_t mn = INT64_MAX, mx = INT64_MIN;
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) {
@@ -529,7 +536,7 @@ __global__ __launch_bounds__(256) void k_gen_range(uint64_t n, int64_t lo, uint6
     mn = v < mn ? v : mn;
     mx = v > mx ? v : mx;
   }
-  block_range_commit(mn, mx, 0, slot);
+  block_range_commit(mn, mx, 0, sink);
 }
 
 __global__ __launch_bounds__(256) void k_gen_pack(uint64_t n, int64_t lo, uint64_t span,
@@ -558,19 +565,24 @@ inline unsigned grid_for(uint64_t work, unsigned per_block, unsigned cap = 1u <<
 
 }  // namespace
 
-hipError_t launch_range_init(RangeSlot *slot, hipStream_t s) {
-  k_range_init<<<1, kRangeSpread, 0, s>>>(slot);
+hipError_t launch_range_init(RangeSlot *slot, uint32_t *full, hipStream_t s) {
+  k_range_init<<<1, kRangeSpread, 0, s>>>(slot, full);
   return hipGetLastError();
 }
 
-hipError_t launch_range_dense(const void *dense, int dtype, uint64_t n, RangeSlot *slot,
+hipError_t launch_range_publish(RangeSink sink, hipStream_t s) {
+  k_range_publish<<<1, kRangeSpread, 0, s>>>(sink);
+  return hipGetLastError();
+}
+
+hipError_t launch_range_dense(const void *dense, int dtype, uint64_t n, RangeSink sink,
                               hipStream_t s) {
   const unsigned grid = grid_for(n, 256 * 16, 4096);
   const int al = ((uintptr_t)dense % 16) == 0;
   if (dtype == CCM_I64)
-    k_range_dense<int64_t><<<grid, 256, 0, s>>>((const int64_t *)dense, n, slot, al);
+    k_range_dense<int64_t><<<grid, 256, 0, s>>>((const int64_t *)dense, n, sink, al);
   else
-    k_range_dense<int32_t><<<grid, 256, 0, s>>>((const int32_t *)dense, n, slot, al);
+    k_range_dense<int32_t><<<grid, 256, 0, s>>>((const int32_t *)dense, n, sink, al);
   return hipGetLastError();
 }
 
@@ -605,26 +617,26 @@ hipError_t launch_gather(const uint32_t *w, int64_t rows, int64_t cols, int bits
   return hipGetLastError();
 }
 
-hipError_t launch_get_one(const uint32_t *w, uint64_t e, int bits, int sgn, int64_t *out,
-                          hipStream_t s) {
-  k_get_one<<<1, 1, 0, s>>>(w, e, bits, sgn, out);
+hipError_t launch_get_one(const uint32_t *w, uint64_t e, int bits, int sgn, RangeHost *host,
+                          uint32_t seq, hipStream_t s) {
+  k_get_one<<<1, 1, 0, s>>>(w, e, bits, sgn, host, seq);
   return hipGetLastError();
 }
 
 hipError_t launch_ewise_range(int op, PackedOperand a, PackedOperand b, int64_t scalar,
-                              uint64_t n, int vclass, RangeSlot *slot, hipStream_t s) {
+                              uint64_t n, int vclass, RangeSink sink, hipStream_t s) {
   const uint64_t ngroups = (n + kGroup - 1) / kGroup;
   const unsigned grid = grid_for(ngroups, 256, 2048);
   if (vclass == EW_I32 && op == EW_ADD)
-    k_ewise_range32<EW_ADD, int32_t><<<grid, 256, 0, s>>>(a, b, scalar, n, slot);
+    k_ewise_range32<EW_ADD, int32_t><<<grid, 256, 0, s>>>(a, b, scalar, n, sink);
   else if (vclass == EW_I32)
-    k_ewise_range32<EW_SCALE, int32_t><<<grid, 256, 0, s>>>(a, b, scalar, n, slot);
+    k_ewise_range32<EW_SCALE, int32_t><<<grid, 256, 0, s>>>(a, b, scalar, n, sink);
   else if (vclass == EW_U32 && op == EW_ADD)
-    k_ewise_range32<EW_ADD, uint32_t><<<grid, 256, 0, s>>>(a, b, scalar, n, slot);
+    k_ewise_range32<EW_ADD, uint32_t><<<grid, 256, 0, s>>>(a, b, scalar, n, sink);
   else if (vclass == EW_U32)
-    k_ewise_range32<EW_SCALE, uint32_t><<<grid, 256, 0, s>>>(a, b, scalar, n, slot);
+    k_ewise_range32<EW_SCALE, uint32_t><<<grid, 256, 0, s>>>(a, b, scalar, n, sink);
   else
-    k_ewise_range<<<grid, 256, 0, s>>>(op, a, b, scalar, n, slot);
+    k_ewise_range<<<grid, 256, 0, s>>>(op, a, b, scalar, n, sink);
   return hipGetLastError();
 }
 
@@ -653,7 +665,7 @@ hipError_t launch_ewise_pack(int op, PackedOperand a, PackedOperand b, int64_t s
 }
 
 hipError_t launch_add_pack_range(PackedOperand a, PackedOperand b, uint64_t n, int vclass,
-                                 int out_bits, uint32_t *out, uint64_t cap32, RangeSlot *slot,
+                                 int out_bits, uint32_t *out, uint64_t cap32, RangeSink sink,
                                  hipStream_t s) {
   if (out_bits < 1 || out_bits > 64 || (vclass != EW_I64 && out_bits > 32))
     return hipErrorInvalidValue;
@@ -664,10 +676,10 @@ hipError_t launch_add_pack_range(PackedOperand a, PackedOperand b, uint64_t n, i
     switch (a.bits * 2 + (a.sgn ? 1 : 0)) {
 #define CCM_ADD_SAME(bb)                                                                       \
   case 2 * bb:                                                                                 \
-    k_add_same<bb, false><<<grid, 256, 0, s>>>(a.w, b.w, n, out, cap32, slot);                 \
+    k_add_same<bb, false><<<grid, 256, 0, s>>>(a.w, b.w, n, out, cap32, sink.slot);            \
     break;                                                                                     \
   case 2 * bb + 1:                                                                             \
-    k_add_same<bb, true><<<grid, 256, 0, s>>>(a.w, b.w, n, out, cap32, slot);                  \
+    k_add_same<bb, true><<<grid, 256, 0, s>>>(a.w, b.w, n, out, cap32, sink.slot);             \
     break;
       CCM_ADD_SAME(1) CCM_ADD_SAME(2) CCM_ADD_SAME(3) CCM_ADD_SAME(4) CCM_ADD_SAME(5)
       CCM_ADD_SAME(6) CCM_ADD_SAME(7) CCM_ADD_SAME(8) CCM_ADD_SAME(9) CCM_ADD_SAME(10)
@@ -676,14 +688,15 @@ hipError_t launch_add_pack_range(PackedOperand a, PackedOperand b, uint64_t n, i
       default:
         return hipErrorInvalidValue;
     }
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess || !sink.host ? e : launch_range_publish(sink, s);
   }
   if (vclass == EW_I32)
     k_ewise_pack32<EW_ADD, int32_t, true>
-        <<<grid, 256, lds, s>>>(a, b, 0, n, out_bits, out, cap32, slot);
+        <<<grid, 256, lds, s>>>(a, b, 0, n, out_bits, out, cap32, sink.slot);
   else if (vclass == EW_U32)
     k_ewise_pack32<EW_ADD, uint32_t, true>
-        <<<grid, 256, lds, s>>>(a, b, 0, n, out_bits, out, cap32, slot);
+        <<<grid, 256, lds, s>>>(a, b, 0, n, out_bits, out, cap32, sink.slot);
   else {
     // 64 KB of output staging at 64 bits, next to the range commit's static LDS
     static const bool lds_set =
@@ -691,9 +704,10 @@ hipError_t launch_add_pack_range(PackedOperand a, PackedOperand b, uint64_t n, i
                             hipFuncAttributeMaxDynamicSharedMemorySize, 256 * 64 * 4) ==
         hipSuccess;
     (void)lds_set;
-    k_ewise_pack<true><<<grid, 256, lds, s>>>(EW_ADD, a, b, 0, n, out_bits, out, cap32, slot);
+    k_ewise_pack<true><<<grid, 256, lds, s>>>(EW_ADD, a, b, 0, n, out_bits, out, cap32, sink.slot);
   }
-  return hipGetLastError();
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess || !sink.host ? e : launch_range_publish(sink, s);
 }
 
 // Groups a packing grid must cover for every width up to max_bits (the
@@ -780,8 +794,8 @@ hipError_t launch_fill_uniform(void *dense, int dtype, uint64_t n, int64_t lo, u
 }
 
 hipError_t launch_gen_range(uint64_t n, int64_t lo, uint64_t span, uint64_t seed,
-                            uint64_t stream_id, RangeSlot *slot, hipStream_t s) {
-  k_gen_range<<<grid_for(n, 256 * 16, 2048), 256, 0, s>>>(n, lo, span, seed, stream_id, slot);
+                            uint64_t stream_id, RangeSink sink, hipStream_t s) {
+  k_gen_range<<<grid_for(n, 256 * 16, 2048), 256, 0, s>>>(n, lo, span, seed, stream_id, sink);
   return hipGetLastError();
 }
 

@@ -32,7 +32,7 @@ __global__ void k_sums_init(uint64_t *sums) {
 
 template <typename T>
 __global__ __launch_bounds__(kSelThreads) void k_method_stats(const T *__restrict__ d, uint64_t n,
-                                                              RangeSlot *slot, uint64_t *sums,
+                                                              RangeSink sink, uint64_t *sums,
                                                               int aligned16) {
   constexpr int PER = 16 / sizeof(T);
   int64_t lo = INT64_MAX, hi = INT64_MIN;
@@ -70,7 +70,7 @@ __global__ __launch_bounds__(kSelThreads) void k_method_stats(const T *__restric
     s_su[threadIdx.x >> 6] = su;
     s_ss[threadIdx.x >> 6] = ss;
   }
-  block_range_commit(lo, hi, 0, slot);  // ends with a barrier-protected fold
+  block_range_commit(lo, hi, 0, sink);  // ends with a barrier-protected fold
   __syncthreads();
   if (threadIdx.x == 0) {
     uint64_t a = 0, b = 0;
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(kSelThreads) void k_method_stats(const T *__restric
 
 }  // namespace
 
-hipError_t launch_method_stats(const void *dense, int dtype, uint64_t n, RangeSlot *slot,
+hipError_t launch_method_stats(const void *dense, int dtype, uint64_t n, RangeSink sink,
                                uint64_t *sums, hipStream_t s) {
   k_sums_init<<<1, 2 * kRangeSpread * kSumStride, 0, s>>>(sums);
   hipError_t e = hipGetLastError();
@@ -96,10 +96,10 @@ hipError_t launch_method_stats(const void *dense, int dtype, uint64_t n, RangeSl
   g = g < 1 ? 1 : (g > 2048 ? 2048 : g);
   const int al = ((uintptr_t)dense % 16) == 0;
   if (dtype == CCM_I64)
-    k_method_stats<int64_t><<<(unsigned)g, kSelThreads, 0, s>>>((const int64_t *)dense, n, slot,
+    k_method_stats<int64_t><<<(unsigned)g, kSelThreads, 0, s>>>((const int64_t *)dense, n, sink,
                                                                 sums, al);
   else
-    k_method_stats<int32_t><<<(unsigned)g, kSelThreads, 0, s>>>((const int32_t *)dense, n, slot,
+    k_method_stats<int32_t><<<(unsigned)g, kSelThreads, 0, s>>>((const int32_t *)dense, n, sink,
                                                                 sums, al);
   return hipGetLastError();
 }

@@ -71,7 +71,7 @@ template <typename T>
 __global__ __launch_bounds__(kVThreads) void k_vlb_sizes(const T *__restrict__ dense, int64_t rows,
                                                          int64_t cols, int64_t ngr, int k, int sgn,
                                                          uint32_t *__restrict__ grp,
-                                                         RangeSlot *slot) {
+                                                         RangeSink sink) {
   const uint64_t total = (uint64_t)rows * (uint64_t)ngr * kVG;
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   // group gi = (row i, group g of the row), advanced by the grid step with
@@ -115,7 +115,7 @@ __global__ __launch_bounds__(kVThreads) void k_vlb_sizes(const T *__restrict__ d
     }
   }
   // the longest group (sizes the staging buffers of the matvec kernel)
-  block_range_commit(0, (int64_t)gmax, 0, slot);
+  block_range_commit(0, (int64_t)gmax, 0, sink);
 }
 
 // ---- pass 2: scans ----------------------------------------------------------
@@ -325,13 +325,14 @@ __global__ __launch_bounds__(kVThreads) void k_vlb_decode(const uint32_t *__rest
 
 __global__ void k_vlb_get(const uint32_t *__restrict__ w, const uint64_t *__restrict__ row_bit,
                           const uint32_t *__restrict__ grp, int64_t ngr, int64_t i, int64_t j,
-                          int k, int sgn, int64_t *__restrict__ out) {
+                          int k, int sgn, RangeHost *host, uint32_t seq) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
   const int64_t g = j / kVG;
   uint64_t p = row_bit[i] + grp[(uint64_t)i * (uint64_t)ngr + (uint64_t)g];
   int64_t v = 0;
   for (int64_t l = g * kVG; l <= j; ++l) v = vlb_read(w, &p, k, sgn);
-  *out = v;
+  __hip_atomic_store(&host->vmin, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(&host->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ---- matvec ------------------------------------------------------------------
@@ -766,15 +767,15 @@ unsigned vgrid(uint64_t work, uint64_t per_block, unsigned cap) {
 uint64_t vlb_ngr(int64_t cols) { return ((uint64_t)cols + kVG - 1) / kVG; }
 
 hipError_t launch_vlb_sizes(const void *dense, int dtype, int64_t rows, int64_t cols, int k,
-                            int sgn, uint32_t *grp, RangeSlot *slot, hipStream_t s) {
+                            int sgn, uint32_t *grp, RangeSink sink, hipStream_t s) {
   const int64_t ngr = (int64_t)vlb_ngr(cols);
   const unsigned grid = vgrid((uint64_t)rows * (uint64_t)ngr * kVG, kVThreads * 4, 4096);
   if (dtype == CCM_I64)
     k_vlb_sizes<int64_t><<<grid, kVThreads, 0, s>>>((const int64_t *)dense, rows, cols, ngr, k,
-                                                    sgn, grp, slot);
+                                                    sgn, grp, sink);
   else
     k_vlb_sizes<int32_t><<<grid, kVThreads, 0, s>>>((const int32_t *)dense, rows, cols, ngr, k,
-                                                    sgn, grp, slot);
+                                                    sgn, grp, sink);
   return hipGetLastError();
 }
 
@@ -819,8 +820,9 @@ hipError_t launch_vlb_decode(const VlbView &a, int64_t *out, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_vlb_get(const VlbView &a, int64_t i, int64_t j, int64_t *out, hipStream_t s) {
-  k_vlb_get<<<1, 64, 0, s>>>(a.w, a.row_bit, a.grp, a.ngr, i, j, a.k, a.sgn, out);
+hipError_t launch_vlb_get(const VlbView &a, int64_t i, int64_t j, RangeHost *host, uint32_t seq,
+                          hipStream_t s) {
+  k_vlb_get<<<1, 64, 0, s>>>(a.w, a.row_bit, a.grp, a.ngr, i, j, a.k, a.sgn, host, seq);
   return hipGetLastError();
 }
 
