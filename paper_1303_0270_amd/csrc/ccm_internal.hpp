@@ -351,7 +351,8 @@ __device__ inline void block_range_commit(int64_t lo, int64_t hi, int flag, cons
   if (threadIdx.x >= 64) return;
   bool last = false;
   if (threadIdx.x == 0) {
-    const uint32_t nb = gridDim.x * gridDim.y, id = blockIdx.x + blockIdx.y * gridDim.x;
+    const uint32_t nb = gridDim.x * gridDim.y * gridDim.z;
+    const uint32_t id = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
     RangeSlot *slot = sk.slot + kRangeStride * (id % kRangeSpread);
     const int nw = (blockDim.x + 63) >> 6;
     for (int w = 1; w < nw; ++w) {

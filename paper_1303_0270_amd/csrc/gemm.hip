@@ -123,20 +123,6 @@ __device__ __forceinline__ int64_t stacked_row(int64_t row, int i, int64_t rows,
   return c0 * limb_rows(rows, L.n) + ((row >> 5) * lc + (i - c0)) * 32 + (row & 31);
 }
 
-// Byte j of four 32-bit values as one word (value q in byte q).
-template <int J>
-__device__ __forceinline__ uint32_t bytes4(const uint32_t *v) {
-  constexpr uint32_t sel = 0x0c0c0000u | ((uint32_t)(J + 4) << 8) | (uint32_t)J;
-  const uint32_t lo = __builtin_amdgcn_perm(v[1], v[0], sel);
-  const uint32_t hi = __builtin_amdgcn_perm(v[3], v[2], sel);
-  return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
-}
-
-// XOR that turns four top bytes (i == L - 1) or lower bytes into digits.
-__device__ __forceinline__ uint32_t digit_flip(int bits, int sgn, int i, int L) {
-  return i < L - 1 || (!sgn && bits % 8 == 0) ? 0x80808080u : 0u;
-}
-
 // The digits of a group of 32 fields of B <= 32 bits starting at stream bit
 // `bit`, `lim` of them real (the others 0): o[i][q] = digit i of fields
 // 4q..4q+3.
@@ -152,21 +138,7 @@ __device__ __forceinline__ void group_digits(const uint32_t *__restrict__ w, uin
   for (int q = 0; q <= B; ++q) ww[q] = w[w0 + q < cap ? w0 + q : cap - 1];
 #pragma unroll
   for (int q = 0; q < B; ++q) ww[q] = __builtin_amdgcn_alignbit(ww[q + 1], ww[q], sh);
-  uint32_t v[32];
-  if (sgn) {
-#pragma unroll
-    for (int i = 0; i < 32; ++i) v[i] = codec::field32<B, true>(ww, i);
-  } else {
-#pragma unroll
-    for (int i = 0; i < 32; ++i) v[i] = codec::field32<B, false>(ww, i);
-  }
-#pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    o[0][q] = bytes4<0>(v + 4 * q) ^ digit_flip(B, sgn, 0, L);
-    if constexpr (L > 1) o[1][q] = bytes4<1>(v + 4 * q) ^ digit_flip(B, sgn, 1, L);
-    if constexpr (L > 2) o[2][q] = bytes4<2>(v + 4 * q) ^ digit_flip(B, sgn, 2, L);
-    if constexpr (L > 3) o[3][q] = bytes4<3>(v + 4 * q) ^ digit_flip(B, sgn, 3, L);
-  }
+  limb::words_digits<B>(ww, sgn, o);
   if (lim < 32) {
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
@@ -178,10 +150,7 @@ __device__ __forceinline__ void group_digits(const uint32_t *__restrict__ w, uin
   }
 }
 
-// Sum of the four signed bytes of a word, added to acc.
-__device__ __forceinline__ int sum4(uint32_t w, int acc) {
-  return __builtin_amdgcn_sdot4((int)w, 0x01010101, acc, false);
-}
+using limb::sum4;
 
 // The block's sum of one value per thread, in thread 0.
 __device__ __forceinline__ int64_t block_sum(int64_t v) {
@@ -194,6 +163,14 @@ __device__ __forceinline__ int64_t block_sum(int64_t v) {
   return t;
 }
 
+// The column addends (null: none) start at zero; the kernel that adds to them
+// runs after this one.
+__device__ __forceinline__ void zero_cadd(int64_t *__restrict__ cadd, int64_t N) {
+  if (!cadd) return;
+  for (int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x; n < N; n += (int64_t)gridDim.x * 256)
+    cadd[n] = 0;
+}
+
 // Digits of A: one block per row, lane j takes columns 32j..32j+31 (one
 // group's worth of fields, re-aligned with a funnel shift when the row starts
 // inside a word).  radd (may be null): radd[row] = beta times the sum of the
@@ -202,9 +179,11 @@ template <int B>
 __global__ __launch_bounds__(256) void k_digit_rows(const uint32_t *__restrict__ w, uint64_t cap,
                                                     int sgn, int64_t M, int64_t K, int64_t ldk,
                                                     Limbs L, int8_t *__restrict__ out,
-                                                    uint64_t beta, int64_t *__restrict__ radd) {
+                                                    uint64_t beta, int64_t *__restrict__ radd,
+                                                    int64_t *__restrict__ cadd, int64_t N) {
   constexpr int LB = (B + 7) / 8;
   const int64_t row = blockIdx.x;
+  zero_cadd(cadd, N);
   uint64_t sum = 0;
   for (int64_t c = 32 * (int64_t)threadIdx.x; c < ldk; c += 32 * 256) {
     uint32_t o[LB][8];
@@ -242,8 +221,10 @@ __global__ __launch_bounds__(256) void k_digit_rows_wide(const uint32_t *__restr
                                                          int sgn, int64_t M, int64_t K,
                                                          int64_t ldk, Limbs L,
                                                          int8_t *__restrict__ out, uint64_t beta,
-                                                         int64_t *__restrict__ radd) {
+                                                         int64_t *__restrict__ radd,
+                                                         int64_t *__restrict__ cadd, int64_t N) {
   const int64_t row = blockIdx.x;
+  zero_cadd(cadd, N);
   uint64_t sum = 0;
   for (int64_t c = 4 * (int64_t)threadIdx.x; c < ldk; c += 4 * 256) {
     uint64_t v[4];
@@ -256,7 +237,7 @@ __global__ __launch_bounds__(256) void k_digit_rows_wide(const uint32_t *__restr
     for (int i = 0; i < L.n; ++i) {
       uint32_t o = 0;
       for (int q = 0; q < 4; ++q) o |= (uint32_t)((v[q] >> (8 * i)) & 0xff) << (8 * q);
-      o = (o ^ digit_flip(bits, sgn, i, L.n)) & live;
+      o = (o ^ limb::digit_flip(bits, sgn, i, L.n)) & live;
       *reinterpret_cast<uint32_t *>(out + stacked_row(row, i, M, L) * ldk + c) = o;
       sum += (uint64_t)(int64_t)sum4(o, 0) << (8 * i);
     }
@@ -364,7 +345,7 @@ __global__ __launch_bounds__(256) void k_digit_cols_wide(const uint32_t *__restr
   const int64_t n = nb + nl;
   uint64_t sum = 0;
   for (int i = 0; i < L.n; ++i) {
-    const uint8_t flip = (uint8_t)digit_flip(bits, sgn, i, L.n);
+    const uint8_t flip = (uint8_t)limb::digit_flip(bits, sgn, i, L.n);
     for (int q = t; q < kCtK * kCtN; q += 256) {
       const int kl = q / kCtN, c = q % kCtN;
       const int64_t k = kb + kl, nn = nb + c;
@@ -384,17 +365,19 @@ __global__ __launch_bounds__(256) void k_digit_cols_wide(const uint32_t *__restr
 
 hipError_t launch_digit_rows(const uint32_t *w, int bits, int sgn, int64_t M, int64_t K,
                              int64_t ldk, Limbs L, int8_t *out, uint64_t beta, int64_t *radd,
-                             hipStream_t s) {
+                             int64_t *cadd, int64_t N, hipStream_t s) {
   const uint64_t cap = cap_words32((uint64_t)M * (uint64_t)K, bits);
   switch (bits) {
-#define CCM_DIGIT_ROWS(b)                                                                     \
-  case b:                                                                                     \
-    k_digit_rows<b><<<(unsigned)M, 256, 0, s>>>(w, cap, sgn, M, K, ldk, L, out, beta, radd);  \
+#define CCM_DIGIT_ROWS(b)                                                                    \
+  case b:                                                                                    \
+    k_digit_rows<b><<<(unsigned)M, 256, 0, s>>>(w, cap, sgn, M, K, ldk, L, out, beta, radd,  \
+                                                cadd, N);                                    \
     break;
     CCM_WIDTH_CASES_32(CCM_DIGIT_ROWS)
 #undef CCM_DIGIT_ROWS
     default:
-      k_digit_rows_wide<<<(unsigned)M, 256, 0, s>>>(w, bits, sgn, M, K, ldk, L, out, beta, radd);
+      k_digit_rows_wide<<<(unsigned)M, 256, 0, s>>>(w, bits, sgn, M, K, ldk, L, out, beta, radd,
+                                                    cadd, N);
   }
   return hipGetLastError();
 }
@@ -404,10 +387,6 @@ hipError_t launch_digit_cols(const uint32_t *w, int bits, int sgn, int64_t K, in
                              int64_t *cadd, hipStream_t s) {
   const uint64_t cap = cap_words32((uint64_t)K * (uint64_t)N, bits);
   const dim3 grid((unsigned)((N + kCtN - 1) / kCtN), (unsigned)(ldk / kCtK));
-  if (cadd) {
-    const hipError_t e = launch_fill_i64(cadd, (uint64_t)N, 0, s);
-    if (e != hipSuccess) return e;
-  }
   switch (bits) {
 #define CCM_DIGIT_COLS(b)                                                                     \
   case b:                                                                                     \
@@ -466,6 +445,112 @@ LimbLayout limb_layout(int abits, int asgn, int bbits, int bsgn, int64_t M, int6
   return p;
 }
 
+// Up to 256 columns, A is cheaper read packed once per group of columns (64 of
+// them for A of three or four digits, 128 below; the second reading comes from
+// the caches in part) than decoded to digits once.  us a product at 10000 x
+// 10000, N = 256 / 257 (this form / digits): 6 x 4 bits 115 / 157, 8 x 6 133 /
+// 205, 12 x 6 157 / 260, 20 x 6 295 / 402, 28 x 6 422 / 550; N = 33 (before: the
+// digits, and the int64 path): 17 x 6 88 / 285 / 2290.
+constexpr int64_t kNarrowCols = 256;
+
+bool narrow_b(int abits, int bbits, int bsgn, int64_t N) {
+  return abits <= 31 && bbits <= 8 && limb::digit_offset(bbits, bsgn) == 0 && N <= kNarrowCols;
+}
+
+// The narrow-B product: digits of B^T, the partial sums of the parts of K.
+struct SkinnyLayout {
+  int nb;  // 32-column blocks (0: not for this product)
+  int splits;
+  int64_t ldk, kper;
+  uint64_t part_at, total;
+};
+
+// A block takes as many columns of C as fit 128 accumulator registers a wave (L
+// digits of A by nb blocks of 16).  `room` bounds the
+// scratch (0: unbounded).
+SkinnyLayout skinny_layout(int abits, int asgn, int bbits, int bsgn, int64_t M, int64_t K,
+                           int64_t N, uint64_t room) {
+  SkinnyLayout p = {};
+  const int la = limb::limbs_of(abits);
+  if (!narrow_b(abits, bbits, bsgn, N)) return p;
+  p.nb = N <= 32 ? 1 : N <= 64 || la > 2 ? 2 : 4;
+  const int64_t groups = (N + 32 * p.nb - 1) / (32 * p.nb);
+  p.ldk = padded_k(K);
+  p.part_at = up256((uint64_t)N * (uint64_t)p.ldk);
+  // parts of K until the blocks fill the chip once (two blocks per CU where
+  // the LDS holds them)
+  const int64_t rows = (M + limb::kSkRows - 1) / limb::kSkRows * groups, nk = p.ldk / limb::kBK;
+  const int64_t slots = 4 * limb::sk_stage(abits, p.nb) <= 158 * 1024 ? 512 : 256;
+  int64_t splits = rows < slots ? slots / rows : 1;
+  splits = splits < nk ? splits : nk;
+  const uint64_t one = 8u * (uint64_t)M * (uint64_t)N;
+  if (room) {
+    const uint64_t fit = room > p.part_at ? (room - p.part_at) / one : 0;
+    if ((uint64_t)splits > fit) splits = fit < 2 ? 1 : (int64_t)fit;
+  }
+  p.kper = (nk + splits - 1) / splits;
+  p.splits = (int)((nk + p.kper - 1) / p.kper);
+  p.total = p.part_at + (p.splits > 1 ? up256((uint64_t)p.splits * one) : 0u);
+  return p;
+}
+
+// C = the sum over the parts, and C's range.
+template <typename OT>
+__global__ __launch_bounds__(256) void k_sum_parts(const int64_t *__restrict__ part, int splits,
+                                                   uint64_t mn, OT *__restrict__ C,
+                                                   RangeSink sink) {
+  int64_t lo = INT64_MAX, hi = INT64_MIN;
+  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+  for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < mn; e += stride) {
+    uint64_t v = 0;
+    for (int q = 0; q < splits; ++q) v += (uint64_t)part[q * mn + e];
+    const int64_t x = (int64_t)(OT)v;
+    C[e] = (OT)x;
+    lo = x < lo ? x : lo;
+    hi = x > hi ? x : hi;
+  }
+  block_range_commit(lo, hi, 0, sink);
+}
+
+hipError_t launch_narrow(const SkinnyLayout &p, const uint32_t *aw, int abits, int asgn,
+                         const uint32_t *bw, int bbits, int bsgn, int64_t M, int64_t K, int64_t N,
+                         int out32, void *C, char *extra, RangeSink sink, hipStream_t s) {
+  limb::SkinnyArgs a;
+  hipError_t e = launch_digit_cols(bw, bbits, bsgn, K, N, p.ldk, Limbs{1, 1}, (int8_t *)extra, 0,
+                                   0, nullptr, s);
+  if (e != hipSuccess) return e;
+  a.aw = aw;
+  a.cap_bytes = 4u * cap_words32((uint64_t)M * (uint64_t)K, abits);
+  a.sgn = asgn;
+  a.M = M;
+  a.K = K;
+  a.N = N;
+  a.ldk = p.ldk;
+  a.Bt = (const int8_t *)extra;
+  a.kper = p.kper;
+  a.splits = p.splits;
+  a.part = (int64_t *)(extra + p.part_at);
+  a.alpha = limb::digit_offset(abits, asgn);
+  a.C = C;
+  a.out32 = out32;
+  a.sink = sink;
+  switch (limb::limbs_of(abits)) {
+    case 1: e = limb::launch_skinny_1(a, abits, p.nb, s); break;
+    case 2: e = limb::launch_skinny_2(a, abits, p.nb, s); break;
+    case 3: e = limb::launch_skinny_3(a, abits, p.nb, s); break;
+    default: e = limb::launch_skinny_4(a, abits, p.nb, s);
+  }
+  if (e != hipSuccess || p.splits == 1) return e;
+  const uint64_t mn = (uint64_t)M * (uint64_t)N;
+  const uint64_t blocks = (mn + 255) / 256;
+  const unsigned grid = (unsigned)(blocks < 2048 ? blocks : 2048);
+  if (out32)
+    k_sum_parts<int32_t><<<grid, 256, 0, s>>>(a.part, p.splits, mn, (int32_t *)C, sink);
+  else
+    k_sum_parts<int64_t><<<grid, 256, 0, s>>>(a.part, p.splits, mn, (int64_t *)C, sink);
+  return hipGetLastError();
+}
+
 hipError_t launch_limbs(const uint32_t *aw, int abits, int asgn, const uint32_t *bw, int bbits,
                         int bsgn, int64_t M, int64_t K, int64_t N, int out32, void *C,
                         char *extra, RangeSink sink, hipStream_t s) {
@@ -473,7 +558,8 @@ hipError_t launch_limbs(const uint32_t *aw, int abits, int asgn, const uint32_t 
   int8_t *a8 = (int8_t *)extra, *b8 = (int8_t *)extra + p.b_at;
   int64_t *cadd = p.alpha ? (int64_t *)(extra + p.cadd_at) : nullptr;
   int64_t *radd = p.beta ? (int64_t *)(extra + p.radd_at) : nullptr;
-  hipError_t e = launch_digit_rows(aw, abits, asgn, M, K, p.ldk, p.A, a8, p.beta, radd, s);
+  hipError_t e = launch_digit_rows(aw, abits, asgn, M, K, p.ldk, p.A, a8, p.beta, radd, cadd, N,
+                                   s);
   if (e != hipSuccess) return e;
   e = launch_digit_cols(bw, bbits, bsgn, K, N, p.ldk, p.B, b8, p.alpha, p.beta, cadd, s);
   if (e != hipSuccess) return e;
@@ -522,15 +608,37 @@ hipError_t launch_pass(const GemmArgs &p, int la, int lb, int out32, hipStream_t
 
 }  // namespace limb
 
+// Operands whose values fit int8 take no more scratch for a narrow B than for
+// a wide one.
+static SkinnyLayout narrow_layout(int abits, int asgn, int bbits, int bsgn, int64_t M, int64_t K,
+                                  int64_t N, int i8) {
+  const uint64_t room = i8 ? limb_layout(abits, asgn, bbits, bsgn, M, K, N).total : 0;
+  return skinny_layout(abits, asgn, bbits, bsgn, M, K, N, room);
+}
+
+// Products the one launch of the int64 path finishes before the digit kernels
+// and the GEMM would have run one after the other: few K chunks, one wave of
+// its 64 x 64 blocks.  us a product at 12 x 10 bits, int64 path / digits: 32^3
+// 36 / 47, 64^3 42 / 50, 128^3 51 / 51, 200^3 65 / 52.  A narrow B has one
+// kernel less to wait for: 6 x 4 bits 32^3 37 / 38, 64^3 43 / 41.
+static bool small_product(int abits, int bbits, int bsgn, int64_t M, int64_t K, int64_t N) {
+  return K <= 96 && M <= (1 << 20) && N <= (1 << 20) && M * N <= (1 << 20) &&
+         !narrow_b(abits, bbits, bsgn, N);
+}
+
 uint64_t matmul_fast_bytes(int abits, int asgn, int bbits, int bsgn, int64_t M, int64_t K,
                            int64_t N, int i8) {
   const int64_t ldk = padded_k(K);
+  if (small_product(abits, bbits, bsgn, M, K, N)) return 0;
   // int32 sums of K digit products, and the launches' grid limits
   if ((ldk >= (1 << 17) && !i8) || ldk / kCtK > 65535 || M > 0x7fffffffll ||
       (N + 63) / 64 > 0x7fffffffll)
     return 0;
-  const LimbLayout p = limb_layout(abits, asgn, bbits, bsgn, M, K, N);
-  return p.total;
+  if (!i8) {
+    const SkinnyLayout n = narrow_layout(abits, asgn, bbits, bsgn, M, K, N, i8);
+    if (n.nb) return n.total;
+  }
+  return limb_layout(abits, asgn, bbits, bsgn, M, K, N).total;
 }
 
 hipError_t launch_matmul(const uint32_t *aw, int abits, int asgn, const uint32_t *bw,
@@ -538,9 +646,16 @@ hipError_t launch_matmul(const uint32_t *aw, int abits, int asgn, const uint32_t
                          void *scratch, uint64_t c_bytes, uint64_t scratch_bytes, RangeSink sink,
                          hipStream_t s) {
   const uint64_t fast = matmul_fast_bytes(abits, asgn, bbits, bsgn, M, K, N, i8);
-  if (fast && scratch_bytes >= c_bytes && scratch_bytes - c_bytes >= fast)
-    return launch_limbs(aw, abits, asgn, bw, bbits, bsgn, M, K, N, out32, scratch,
-                        (char *)scratch + c_bytes, sink, s);
+  if (fast && scratch_bytes >= c_bytes && scratch_bytes - c_bytes >= fast) {
+    const SkinnyLayout n = narrow_layout(abits, asgn, bbits, bsgn, M, K, N, i8);
+    const bool aligned = (uintptr_t)aw % 16 == 0;  // 16-byte copies of the payload itself
+    if (n.nb && aligned)
+      return launch_narrow(n, aw, abits, asgn, bw, bbits, bsgn, M, K, N, out32, scratch,
+                           (char *)scratch + c_bytes, sink, s);
+    if (!n.nb || i8)  // otherwise the scratch is the narrow product's
+      return launch_limbs(aw, abits, asgn, bw, bbits, bsgn, M, K, N, out32, scratch,
+                          (char *)scratch + c_bytes, sink, s);
+  }
   // Operands that fit in 32 bits are staged as int32 (products stay exact in
   // int64); wider ones as int64.
   const bool narrow = (abits < 32 || (abits == 32 && asgn)) && (bbits < 32 || (bbits == 32 && bsgn));

@@ -22,14 +22,14 @@
 //
 // Bound by the matrix cores' issue (one limb each side: 468-480 us at 8192^3).
 // Against the int64 vector path (us for the whole product, plan and pack):
-// 12 x 10 bits, 1500 x 2000 x 1801: 82 against 539 (kernel 38); 17 x 6 bits,
-// 10000 x 10001 x 33: 285 against 2290 (kernel 126, decoding A 126).
+// 12 x 10 bits, 1500 x 2000 x 1801: 79 against 539 (kernel 38-42).
 #pragma once
 
 #include <limits>
 #include <type_traits>
 
 #include "ccm_internal.hpp"
+#include "group_codec.hpp"
 
 namespace ccm {
 namespace limb {
@@ -56,6 +56,48 @@ __host__ __device__ inline uint64_t digit_offset(int bits, int sgn) {
   for (int i = 0; i + 1 < L; ++i) a += 128ull << (8 * i);
   if (!sgn && bits % 8 == 0) a += 128ull << (8 * (L - 1));
   return a;
+}
+
+// Byte j of four 32-bit values as one word (value q in byte q).
+template <int J>
+__device__ __forceinline__ uint32_t bytes4(const uint32_t *v) {
+  constexpr uint32_t sel = 0x0c0c0000u | ((uint32_t)(J + 4) << 8) | (uint32_t)J;
+  const uint32_t lo = __builtin_amdgcn_perm(v[1], v[0], sel);
+  const uint32_t hi = __builtin_amdgcn_perm(v[3], v[2], sel);
+  return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+}
+
+// XOR that turns four top bytes (i == L - 1) or lower bytes into digits.
+__device__ __forceinline__ uint32_t digit_flip(int bits, int sgn, int i, int L) {
+  return i < L - 1 || (!sgn && bits % 8 == 0) ? 0x80808080u : 0u;
+}
+
+// The digits of 32 consecutive fields of B <= 32 bits, their words aligned:
+// o[i][q] = digit i of fields 4q..4q+3.
+template <int B>
+__device__ __forceinline__ void words_digits(const uint32_t *ww, int sgn,
+                                             uint32_t (&o)[(B + 7) / 8][8]) {
+  constexpr int L = (B + 7) / 8;
+  uint32_t v[32];
+  if (sgn) {
+#pragma unroll
+    for (int i = 0; i < 32; ++i) v[i] = codec::field32<B, true>(ww, i);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 32; ++i) v[i] = codec::field32<B, false>(ww, i);
+  }
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    o[0][q] = bytes4<0>(v + 4 * q) ^ digit_flip(B, sgn, 0, L);
+    if constexpr (L > 1) o[1][q] = bytes4<1>(v + 4 * q) ^ digit_flip(B, sgn, 1, L);
+    if constexpr (L > 2) o[2][q] = bytes4<2>(v + 4 * q) ^ digit_flip(B, sgn, 2, L);
+    if constexpr (L > 3) o[3][q] = bytes4<3>(v + 4 * q) ^ digit_flip(B, sgn, 3, L);
+  }
+}
+
+// Sum of the four signed bytes of a word, added to acc.
+__device__ __forceinline__ int sum4(uint32_t w, int acc) {
+  return __builtin_amdgcn_sdot4((int)w, 0x01010101, acc, false);
 }
 
 // 16-byte chunk c of tile row r sits at chunk position c ^ swz(r) of its
@@ -294,6 +336,33 @@ hipError_t launch_tile(const GemmArgs &p, hipStream_t s) {
   kern<<<(unsigned)ntile, 64 * WGM * WGN, lds, s>>>(p);
   return hipGetLastError();
 }
+
+// C = A B for a narrow right operand of one digit without offset
+// (gemm_skinny.hpp).
+constexpr int kSkRows = 128;  // rows of A per block
+// 16-byte chunks copied per row and step: the 16 B bytes of 128 fields, up to
+// 15 before them and the word after the last, rounded up to odd.
+constexpr int sk_chunks(int B) { return (B + 2) | 1; }
+constexpr int sk_insts(int B) { return (32 * sk_chunks(B) + 63) / 64; }
+constexpr int sk_stage(int B, int NB) { return 4 * sk_insts(B) * 1024 + NB * 32 * kBK; }
+struct SkinnyArgs {
+  const uint32_t *aw;
+  uint64_t cap_bytes;
+  int sgn;
+  int64_t M, K, N, ldk;
+  const int8_t *Bt;  // N digit rows
+  int64_t kper;
+  int splits;
+  int64_t *part;        // splits x M x N partial sums (splits > 1)
+  uint64_t alpha;       // what A's digits leave out
+  void *C;
+  int out32;
+  RangeSink sink;
+};
+hipError_t launch_skinny_1(const SkinnyArgs &p, int abits, int nb, hipStream_t s);
+hipError_t launch_skinny_2(const SkinnyArgs &p, int abits, int nb, hipStream_t s);
+hipError_t launch_skinny_3(const SkinnyArgs &p, int abits, int nb, hipStream_t s);
+hipError_t launch_skinny_4(const SkinnyArgs &p, int abits, int nb, hipStream_t s);
 
 // One pass over a chunk of la limbs of A and lb of B (la, lb <= 3, or 4 with
 // at most 2 on the other side); OT int32 (out32) or int64.

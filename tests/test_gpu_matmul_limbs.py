@@ -56,7 +56,9 @@ PAIRS = [(8, False, 8, False), (8, False, 8, True), (7, False, 8, False), (9, Fa
          (12, False, 27, True), (32, True, 20, False), (20, True, 32, False),
          (30, False, 24, True), (28, True, 27, True), (36, True, 18, False),
          (20, False, 35, True), (54, True, 2, False), (2, True, 57, True), (57, True, 1, False)]
-SHAPES = [(1, 1, 1), (31, 33, 32), (33, 129, 31), (97, 128, 130), (129, 127, 65), (260, 300, 200)]
+# K up to 96 takes the int64 path, longer products the matrix cores
+SHAPES = [(1, 1, 1), (31, 96, 32), (1, 97, 1), (33, 129, 31), (97, 128, 130), (129, 127, 65),
+          (260, 300, 200)]
 
 
 @pytest.mark.parametrize("ba,sa,bb,sb", PAIRS)
@@ -65,6 +67,20 @@ def test_product_of_digits(ba, sa, bb, sb):
     for M, K, N in SHAPES:
         if K * max(map(abs, bounds(ba, sa))) * max(map(abs, bounds(bb, sb))) < 1 << 63:
             assert_product(rand_matrix(rng, M, K, ba, sa), rand_matrix(rng, K, N, bb, sb))
+
+
+@pytest.mark.parametrize("ba", range(1, 33))
+def test_narrow_product_every_width(ba):
+    """A narrow B of one digit: every width of A (32 bits goes the other way)
+    in both signs, 1 to 129 columns, rows around a block and a wave, K around a
+    step and split into parts."""
+    rng = np.random.default_rng(3000 + ba)
+    shapes = [(1, 1, 1), (33, 63, 2), (127, 129, 31), (129, 128, 33), (70, 257, 64), (40, 1030, 65),
+              (130, 700, 128), (31, 64, 129)]
+    for i, (M, K, N) in enumerate(shapes):
+        sa, sb = bool((i + ba) % 2), bool(i % 3)
+        bb = (1, 8, 4, 7)[(i + ba) % 4] if sb else (1, 7, 3, 8)[(i + ba) % 4]
+        assert_product(rand_matrix(rng, M, K, ba, sa), rand_matrix(rng, K, N, bb, sb))
 
 
 @pytest.mark.parametrize("ba,sa,bb,sb", [(8, False, 8, False), (16, True, 8, True),
@@ -85,10 +101,21 @@ def test_many_tiles_and_small_scratch():
     """Several output tiles in both directions, and the same product through
     the least scratch the C call accepts and through one off a 16-byte
     boundary (the int64 path): the same bytes."""
-    c = ccm()
     rng = np.random.default_rng(77)
     A, B = rand_matrix(rng, 700, 260, 12, False), rand_matrix(rng, 260, 600, 10, True)
     ga, gb, want = assert_product(A, B)
+    least_scratch(ga, gb, want)
+
+
+def test_narrow_product_with_small_scratch():
+    """The narrow product through the least scratch and a misaligned one."""
+    rng = np.random.default_rng(78)
+    A, B = rand_matrix(rng, 300, 520, 17, False), rand_matrix(rng, 520, 33, 6, True)
+    least_scratch(*assert_product(A, B))
+
+
+def least_scratch(ga, gb, want):
+    c = ccm()
     least = c.matmul_scratch_least(ga, gb)
     full = c.matmul_scratch_bytes(ga, gb)
     assert least < full
