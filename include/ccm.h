@@ -131,6 +131,21 @@ int ccm_compress_plan(const void *dense, int32_t dtype, int64_t rows, int64_t co
  * set by the caller.  Async. */
 int ccm_compress(const void *dense, int32_t dtype, const ccm_desc *out, void *stream);
 
+/* Compression in one pass over dense, for large matrices: the same descriptor
+ * and payload as ccm_compress_plan and ccm_compress give.
+ *   guess: the width of a sample of dense (n values).  Blocking.
+ *   try: packs dense at that width into payload (device, caller-owned,
+ *     ccm_payload_capacity(rows, cols, bits) bytes) while its exact range is
+ *     reduced, and fills out.  When the whole matrix has that width,
+ *     out->payload is payload and the compression is complete; otherwise
+ *     out->payload is NULL, payload holds nothing of use, and the caller goes
+ *     on as after ccm_compress_plan, with a payload for out->bits and
+ *     ccm_compress.  bits at most 32 for CCM_I32, 63 unsigned.  Blocking. */
+int ccm_compress_guess(const void *dense, int32_t dtype, int64_t n, int32_t *bits,
+                       int32_t *is_signed, void *stream);
+int ccm_compress_try(const void *dense, int32_t dtype, int64_t rows, int64_t cols, int32_t bits,
+                     int32_t is_signed, void *payload, ccm_desc *out, void *stream);
+
 /* Decode every element into dense_out (device, rows*cols int64).  Async. */
 int ccm_decompress(const ccm_desc *a, int64_t *dense_out, void *stream);
 

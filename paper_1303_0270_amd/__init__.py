@@ -184,6 +184,32 @@ def from_serialized(blob: bytes, device="cuda") -> CMatrix:
     return m
 
 
+# Dense bytes from which compress packs in one pass at a guessed width: below,
+# the second pass reads from the caches and costs less than the wait for the
+# sample.  us a call, two passes / one, int64 at 12 bits: 64 MB 37 / 43, 128 MB
+# 64 / 61, 256 MB 111 / 89, 512 MB 240 / 147, 2 GB 873 / 502.
+_ONEPASS_BYTES = 160 << 20
+
+
+def _compress_onepass(t: torch.Tensor, code: int, s) -> CMatrix:
+    """One pass at the width of a sample; a second one when it was not the
+    width of the whole matrix."""
+    b, sg = ctypes.c_int32(), ctypes.c_int32()
+    check(lib.ccm_compress_guess(_ptr(t), code, t.numel(), ctypes.byref(b), ctypes.byref(sg), s),
+          "ccm_compress_guess")
+    d = Desc()
+    payload = torch.empty(payload_capacity(t.shape[0], t.shape[1], b.value), dtype=torch.uint8,
+                          device=t.device)
+    check(lib.ccm_compress_try(_ptr(t), code, t.shape[0], t.shape[1], b.value, sg.value,
+                               _ptr(payload), ctypes.byref(d), s), "ccm_compress_try")
+    if d.payload:
+        return CMatrix(d, payload)
+    del payload
+    m = CMatrix(d, device=t.device)
+    check(lib.ccm_compress(_ptr(t), code, ctypes.byref(m.desc), s), "ccm_compress")
+    return m
+
+
 def compress(dense: torch.Tensor, stream=None, order: str = "C") -> CMatrix:
     """SM-compress a 2-D int32/int64 device tensor (range pass, then packing),
     unravelled by row (order "C") or by column (order "F")."""
@@ -194,6 +220,8 @@ def compress(dense: torch.Tensor, stream=None, order: str = "C") -> CMatrix:
         raise ValueError("order must be 'C' or 'F'")
     code = _dtype_code(t)
     s = _stream(stream)
+    if order == "C" and t.numel() * t.element_size() >= _ONEPASS_BYTES:
+        return _compress_onepass(t, code, s)
     d = Desc()
     r, c = (t.shape[0], t.shape[1]) if order == "C" else (t.shape[1], t.shape[0])
     check(lib.ccm_compress_plan(_ptr(t), code, r, c, ctypes.byref(d), s), "ccm_compress_plan")

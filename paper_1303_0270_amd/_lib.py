@@ -90,6 +90,9 @@ SIGNATURES = {
     "ccm_scale_plan": (ctypes.c_int, [_dp, _i64, _dp]),
     "ccm_scale": (ctypes.c_int, [_dp, _i64, _dp, _vp]),
     "ccm_matvec": (ctypes.c_int, [_dp, _vp, _i32, _vp, _vp]),
+    "ccm_compress_guess": (ctypes.c_int, [_vp, _i32, _i64, ctypes.POINTER(_i32),
+                                          ctypes.POINTER(_i32), _vp]),
+    "ccm_compress_try": (ctypes.c_int, [_vp, _i32, _i64, _i64, _i32, _i32, _vp, _dp, _vp]),
     "ccm_matmul_scratch_bytes": (_u64, [_dp, _dp]),
     "ccm_matmul_scratch_least": (_u64, [_dp, _dp]),
     "ccm_matmul_plan": (ctypes.c_int, [_dp, _dp, _dp, _vp, _u64, _vp]),

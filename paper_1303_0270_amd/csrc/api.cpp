@@ -316,6 +316,53 @@ int ccm_compress(const void *dense, int32_t dtype, const ccm_desc *out, void *st
   return CCM_OK;
 }
 
+int ccm_compress_guess(const void *dense, int32_t dtype, int64_t n, int32_t *bits,
+                       int32_t *is_signed, void *stream) {
+  if (!dense || !bits || !is_signed || n < 1 || (dtype != CCM_I32 && dtype != CCM_I64))
+    return CCM_E_INVAL;
+  hipStream_t s = (hipStream_t)stream;
+  std::lock_guard<std::mutex> lk(g_mu);
+  DeviceCtx *c = nullptr;
+  int rc = device_ctx(s, &c);
+  if (rc != CCM_OK) return rc;
+  ccm::RangeSink sink;
+  rc = next_sink(c, s, &sink);
+  if (rc != CCM_OK) return rc;
+  CCM_HIP(ccm::launch_sample_range(dense, dtype, (uint64_t)n, sink, s));
+  ccm::RangeHost r;
+  rc = read_range(c, s, false, &r);
+  if (rc != CCM_OK) return rc;
+  return width_rule(r.vmin, r.vmax, bits, is_signed);
+}
+
+int ccm_compress_try(const void *dense, int32_t dtype, int64_t rows, int64_t cols, int32_t bits,
+                     int32_t is_signed, void *payload, ccm_desc *out, void *stream) {
+  if (!dense || !payload || !out || !shape_ok(rows, cols) ||
+      (dtype != CCM_I32 && dtype != CCM_I64) || bits < 1 || bits > (dtype == CCM_I32 ? 32 : 64) ||
+      (bits == 64 && !is_signed))
+    return CCM_E_INVAL;
+  const uint64_t n = (uint64_t)rows * (uint64_t)cols;
+  const int64_t top = (int64_t)((is_signed ? 1ull << (bits - 1) : 1ull << (bits % 64)) - 1u);
+  hipStream_t s = (hipStream_t)stream;
+  std::lock_guard<std::mutex> lk(g_mu);
+  DeviceCtx *c = nullptr;
+  int rc = device_ctx(s, &c);
+  if (rc != CCM_OK) return rc;
+  ccm::RangeSink sink;
+  rc = next_sink(c, s, &sink);
+  if (rc != CCM_OK) return rc;
+  CCM_HIP(ccm::launch_compress_range(dense, dtype, n, bits, is_signed ? -top - 1 : 0, top,
+                                     (uint32_t *)payload, ccm::cap_words32(n, bits), sink, s));
+  ccm::RangeHost r;
+  rc = read_range(c, s, false, &r);  // published from a kernel of its own
+  if (rc != CCM_OK) return rc;
+  rc = fill_desc(rows, cols, r.vmin, r.vmax, out);
+  // a narrower range than the guess packs narrower; the sign alone does not
+  // change a field
+  if (rc == CCM_OK && !r.flag && out->bits == bits) out->payload = payload;
+  return rc;
+}
+
 int ccm_decompress(const ccm_desc *a, int64_t *dense_out, void *stream) {
   int rc = check_desc(a, true);
   if (rc != CCM_OK) return rc;

@@ -288,7 +288,8 @@ struct RangeHost {
 
 // Where a range pass folds: the slots, and for a pass the host waits for
 // (host not null) the record its last block writes, re-arming the slots for
-// the next pass.  `full` counts the slots whose blocks have all folded.  The
+// the next pass.  full[0] counts the slots whose blocks have all folded, full[1]
+// is the stop word of a pass that packs at a guessed width.  The
 // host then waits for one kernel and reads 24 bytes; with a kernel before to
 // initialise the slots and a copy of all of them after it the same wait took
 // 18 us where this takes 7 (a one-block pass).
@@ -319,7 +320,7 @@ __device__ inline void range_publish(const RangeSink &sk) {
   __hip_atomic_store(&r->vmax, INT64_MIN, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __hip_atomic_store(&r->flag, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __hip_atomic_store(&r->done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (lane == 0) __hip_atomic_store(sk.full, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (lane < 2) __hip_atomic_store(sk.full + lane, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   lo = wave_min(lo);
   hi = wave_max(hi);
   const int f = __any(fl) ? 1 : 0;
@@ -389,6 +390,14 @@ hipError_t launch_range_dense(const void *dense, int dtype, uint64_t n, RangeSin
                               hipStream_t s);
 hipError_t launch_compress(const void *dense, int dtype, uint64_t n, int bits, uint32_t *out,
                            uint64_t cap32, hipStream_t s);
+// The range of a sample of the dense values; packing at a guessed width (dense
+// int32: at most 32) with the exact range, [glo, ghi] being what the guess
+// holds (the record's flag: some value did not fit and the payload is void).
+hipError_t launch_sample_range(const void *dense, int dtype, uint64_t n, RangeSink sink,
+                               hipStream_t s);
+hipError_t launch_compress_range(const void *dense, int dtype, uint64_t n, int bits, int64_t glo,
+                                 int64_t ghi, uint32_t *out, uint64_t cap32, RangeSink sink,
+                                 hipStream_t s);
 hipError_t launch_decompress(const uint32_t *w, uint64_t n, int bits, int sgn, int64_t *out,
                              hipStream_t s);
 // one element into the host record's vmin

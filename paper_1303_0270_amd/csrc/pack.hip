@@ -28,7 +28,7 @@ __global__ void k_range_init(RangeSlot *slot, uint32_t *full) {
     r->flag = 0;
     r->done = 0;
   }
-  if (full && threadIdx.x == 0) *full = 0;
+  if (full && threadIdx.x < 2) full[threadIdx.x] = 0;
 }
 
 __global__ __launch_bounds__(kRangeSpread) void k_range_publish(RangeSink sink) {
