@@ -507,6 +507,20 @@ int ccm_vlb_matvec(const ccm_vlb_desc *a, const void *x, int32_t xdtype, int64_t
  * CCM_E_RANGE if any value is NaN or infinite.  Blocking. */
 int ccm_float_absmax(const void *v, int32_t dtype, int64_t n, double *absmax, void *stream);
 
+/* Exact (min, max) of n device floats, and of a sample of them.  CCM_E_RANGE
+ * if any value (any sampled value) is NaN or infinite.  Blocking. */
+int ccm_float_range(const void *v, int32_t dtype, int64_t n, double *vmin, double *vmax,
+                    void *stream);
+int ccm_float_sample(const void *v, int32_t dtype, int64_t n, double *vmin, double *vmax,
+                     void *stream);
+
+/* Host only: the exact range of q = round-half-to-even(v * 2^frac_bits) over
+ * values with the exact range [vmin, vmax] (rounding keeps order), so a range
+ * pass over the floats is all a fixed-point compression plan needs.
+ * CCM_E_OVERFLOW if some |v 2^f| >= 2^62.  |frac_bits| <= 1200. */
+int ccm_quantized_range(double vmin, double vmax, int32_t frac_bits, int64_t *qmin,
+                        int64_t *qmax);
+
 /* Host only: f = sig_bits - 1 - e with 2^e <= absmax < 2^(e+1); 0 for
  * absmax 0.  CCM_E_INVAL unless 1 <= sig_bits <= 62 and absmax is finite
  * and >= 0. */
@@ -523,6 +537,11 @@ int ccm_float_frac_bits(double absmax, int32_t sig_bits, int32_t *frac_bits);
 int ccm_quantize(const void *v, int32_t dtype, int64_t n, int32_t frac_bits, void *q,
                  int32_t qdtype, int64_t *qmin, int64_t *qmax, void *stream);
 
+/* q as ccm_quantize writes it, for values checked before (finite, every q
+ * inside qdtype).  Async. */
+int ccm_quantize_checked(const void *v, int32_t dtype, int64_t n, int32_t frac_bits, void *q,
+                         int32_t qdtype, void *stream);
+
 /* Pack q = round-half-to-even(v * 2^frac_bits) of rows*cols device floats
  * straight into out->payload at out->bits (Method 1's packing, no int64
  * copy of q).  `out` must describe exactly these quantized values: its
@@ -530,6 +549,22 @@ int ccm_quantize(const void *v, int32_t dtype, int64_t n, int32_t frac_bits, voi
  * NaN, infinities and overflow).  Async. */
 int ccm_compress_fx(const void *v, int32_t dtype, int32_t frac_bits, const ccm_desc *out,
                     void *stream);
+
+/* ccm_compress_fx in one pass, for large matrices: packs at bits (guessed from
+ * ccm_float_sample's range) into payload (device, caller-owned, capacity at
+ * bits) while the exact range of v is reduced into *vmin, *vmax.  *fits: 1 when
+ * every q fits the guess; the payload is then complete if the exact range's
+ * width and fraction bits are the guessed ones too, otherwise it holds nothing
+ * of use.  CCM_E_RANGE if any value is NaN or infinite.  Blocking. */
+int ccm_compress_fx_try(const void *v, int32_t dtype, int32_t frac_bits, int64_t rows,
+                        int64_t cols, int32_t bits, int32_t is_signed, void *payload,
+                        double *vmin, double *vmax, int32_t *fits, void *stream);
+
+/* Every element of a fixed-point matrix as q * 2^-frac_bits, converted as
+ * ccm_decompress and ccm_dequantize would, into rows*cols device floats.
+ * Async. */
+int ccm_decompress_fx(const ccm_desc *a, int32_t frac_bits, int32_t dtype, void *out,
+                      void *stream);
 
 /* out[i] = q[i] * 2^-frac_bits converted as described above, into device
  * floats of dtype CCM_F32 or CCM_F64.  |frac_bits| <= 2400.  Async. */

@@ -765,12 +765,61 @@ def _keep(t: torch.Tensor, stream) -> None:
         t.record_stream(stream)
 
 
-def _frac_bits_of(v: torch.Tensor, sig_bits, frac_bits, stream) -> int:
-    if (sig_bits is None) == (frac_bits is None):
-        raise ValueError("give exactly one of sig_bits and frac_bits")
+def _float_extremes(v: torch.Tensor, stream, sample: bool = False) -> tuple[float, float]:
+    lo, hi = ctypes.c_double(), ctypes.c_double()
+    fn, name = ((lib.ccm_float_sample, "ccm_float_sample") if sample
+                else (lib.ccm_float_range, "ccm_float_range"))
+    check(fn(_ptr(v), _float_code(v), v.numel(), ctypes.byref(lo), ctypes.byref(hi),
+             _stream(stream)), name)
+    return lo.value, hi.value
+
+
+def _frac_bits_for(lo: float, hi: float, sig_bits, frac_bits) -> int:
     if frac_bits is not None:
         return int(frac_bits)
-    return float_frac_bits(float_absmax(v, stream), sig_bits)
+    return float_frac_bits(max(abs(lo), abs(hi)), sig_bits)
+
+
+def _one_of(sig_bits, frac_bits) -> None:
+    if (sig_bits is None) == (frac_bits is None):
+        raise ValueError("give exactly one of sig_bits and frac_bits")
+
+
+def _quantized_desc(t: torch.Tensor, lo: float, hi: float, f: int) -> Desc:
+    """Descriptor (no payload) of the 2-D floats t, of range [lo, hi], at f fraction bits."""
+    qlo, qhi = ctypes.c_int64(), ctypes.c_int64()
+    check(lib.ccm_quantized_range(lo, hi, f, ctypes.byref(qlo), ctypes.byref(qhi)),
+          "ccm_quantized_range")
+    b, sgn = width(qlo.value, qhi.value)
+    d = Desc()
+    d.rows, d.cols, d.vmin, d.vmax = t.shape[0], t.shape[1], qlo.value, qhi.value
+    d.bits, d.is_signed, d.words = b, 1 if sgn else 0, words(t.shape[0], t.shape[1], b)
+    return d
+
+
+def _compress_float_onepass(t: torch.Tensor, sig_bits, frac_bits, stream):
+    """(matrix or None, lo, hi): packed in one pass at the scale and width of a
+    sample, None when they are not those of the whole matrix."""
+    try:
+        lo, hi = _float_extremes(t, stream, sample=True)
+        g = _frac_bits_for(lo, hi, sig_bits, frac_bits)
+        d = _quantized_desc(t, lo, hi, g)
+    except CcmError:  # the whole matrix decides which error it is, if any
+        return (None, *_float_extremes(t, stream))
+    payload = torch.empty(payload_capacity(d.rows, d.cols, d.bits), dtype=torch.uint8,
+                          device=t.device)
+    vlo, vhi, fits = ctypes.c_double(), ctypes.c_double(), ctypes.c_int32()
+    check(lib.ccm_compress_fx_try(_ptr(t), _float_code(t), g, d.rows, d.cols, d.bits, d.is_signed,
+                                  _ptr(payload), ctypes.byref(vlo), ctypes.byref(vhi),
+                                  ctypes.byref(fits), _stream(stream)), "ccm_compress_fx_try")
+    lo, hi = vlo.value, vhi.value
+    if fits.value and _frac_bits_for(lo, hi, sig_bits, frac_bits) == g:
+        exact = _quantized_desc(t, lo, hi, g)
+        if exact.bits == d.bits:
+            m = CMatrix(exact, payload)
+            m.frac_bits = g
+            return m, lo, hi
+    return None, lo, hi
 
 
 def compress_float(dense: torch.Tensor, sig_bits: int | None = None,
@@ -778,20 +827,21 @@ def compress_float(dense: torch.Tensor, sig_bits: int | None = None,
     """A 2-D float32/float64 device tensor in fixed point: quantized at
     frac_bits (or at the fraction bits that keep sig_bits significant bits of
     its largest magnitude) and SM-packed like an integer matrix: one pass
-    yields the quantized values' exact range, a second packs them straight
-    from the floats."""
+    yields the floats' exact range, which gives the quantized values' (rounding
+    keeps order), a second packs them straight from the floats.  Large matrices
+    are packed in the first pass already, as compress does."""
     t = _device_tensor(dense, "dense")
     if t.dim() != 2:
         raise ValueError("2-D tensor expected")
-    f = _frac_bits_of(t, sig_bits, frac_bits, stream)
-    lo, hi = ctypes.c_int64(), ctypes.c_int64()
-    check(lib.ccm_quantize(_ptr(t), _float_code(t), t.numel(), f, None, I64, ctypes.byref(lo),
-                           ctypes.byref(hi), _stream(stream)), "ccm_quantize")
-    b, sgn = width(lo.value, hi.value)
-    d = Desc()
-    d.rows, d.cols, d.vmin, d.vmax = t.shape[0], t.shape[1], lo.value, hi.value
-    d.bits, d.is_signed, d.words = b, 1 if sgn else 0, words(t.shape[0], t.shape[1], b)
-    m = CMatrix(d, device=t.device)
+    _one_of(sig_bits, frac_bits)
+    if t.numel() * t.element_size() >= _ONEPASS_BYTES:
+        m, lo, hi = _compress_float_onepass(t, sig_bits, frac_bits, stream)
+        if m is not None:
+            return m
+    else:
+        lo, hi = _float_extremes(t, stream)
+    f = _frac_bits_for(lo, hi, sig_bits, frac_bits)
+    m = CMatrix(_quantized_desc(t, lo, hi, f), device=t.device)
     check(lib.ccm_compress_fx(_ptr(t), _float_code(t), f, ctypes.byref(m.desc),
                               _stream(stream)), "ccm_compress_fx")
     _keep(t, stream)
@@ -800,14 +850,21 @@ def compress_float(dense: torch.Tensor, sig_bits: int | None = None,
 
 
 def decompress_float(m: CMatrix, dtype=torch.float64, stream=None) -> torch.Tensor:
-    """The fixed-point matrix as floats: q decoded, then q 2^-frac_bits."""
+    """The fixed-point matrix as floats, q 2^-frac_bits."""
     if m.frac_bits is None:
         raise CcmError(E_INVAL, "decompress_float: not a fixed-point matrix")
-    q = decompress(m, stream=stream)
-    out = torch.empty(q.shape, dtype=dtype, device=q.device)
-    q = q.contiguous()
-    dequantize(q, m.frac_bits, dtype, out=out, stream=stream)
-    _keep(q, stream)
+    out = torch.empty((m.desc.rows, m.desc.cols), dtype=dtype, device=m.payload.device)
+    check(lib.ccm_decompress_fx(ctypes.byref(m.desc), m.frac_bits, _float_code(out), _ptr(out),
+                                _stream(stream)), "ccm_decompress_fx")
+    return out if m.order == "C" else _transposed(out, stream)
+
+
+def _transposed(t: torch.Tensor, stream) -> torch.Tensor:
+    """A contiguous transpose, made on `stream` after its work on t."""
+    out = torch.empty((t.shape[1], t.shape[0]), dtype=t.dtype, device=t.device)
+    with torch.cuda.stream(stream):  # None: the current one
+        out.copy_(t.t())
+    _keep(t, stream)
     return out
 
 
@@ -820,14 +877,22 @@ def matvec_float(m: CMatrix, x: torch.Tensor, x_sig_bits: int | None = None,
     if m.frac_bits is None:
         raise CcmError(E_INVAL, "matvec_float: not a fixed-point matrix")
     t = _device_tensor(x, "x")
-    g = _frac_bits_of(t, x_sig_bits, x_frac_bits, stream)
+    _one_of(x_sig_bits, x_frac_bits)
+    lo, hi = _float_extremes(t, stream)
+    g = _frac_bits_for(lo, hi, x_sig_bits, x_frac_bits)
+    xlo, xhi = ctypes.c_int64(), ctypes.c_int64()
+    check(lib.ccm_quantized_range(lo, hi, g, ctypes.byref(xlo), ctypes.byref(xhi)),
+          "ccm_quantized_range")
+    amax = max(abs(m.vmin), abs(m.vmax))
+    if m.cols * amax * max(abs(xlo.value), abs(xhi.value)) >= (1 << 63):
+        raise CcmError(E_OVERFLOW, "matvec_float: the integer sums could leave int64")
     # with at most 31 significant bits kept, |x_q| <= 2^31 - 1 after rounding
     # is not guaranteed (2^31 itself can appear), so int32 only up to 30
     narrow = x_sig_bits is not None and x_sig_bits <= 30
-    xq, xlo, xhi = quantize(t, g, stream=stream, dtype=torch.int32 if narrow else torch.int64)
-    amax = max(abs(m.vmin), abs(m.vmax))
-    if m.cols * amax * max(abs(xlo), abs(xhi)) >= (1 << 63):
-        raise CcmError(E_OVERFLOW, "matvec_float: the integer sums could leave int64")
+    xq = torch.empty(t.shape, dtype=torch.int32 if narrow else torch.int64, device=t.device)
+    check(lib.ccm_quantize_checked(_ptr(t), _float_code(t), t.numel(), g, _ptr(xq),
+                                   _dtype_code(xq), _stream(stream)), "ccm_quantize_checked")
+    _keep(t, stream)
     y = matvec(m, xq, stream=stream)
     out = dequantize(y, m.frac_bits + g, torch.float64, stream=stream)
     _keep(xq, stream)

@@ -967,8 +967,21 @@ int ccm_header_decode_cm(const uint8_t in[64], ccm_desc *at) {
 
 // ---- floats in fixed point (Conclusion) ----------------------------------
 
-int ccm_float_absmax(const void *v, int32_t dtype, int64_t n, double *absmax, void *stream) {
-  if (!v || !absmax || n < 1 || (dtype != CCM_F32 && dtype != CCM_F64)) return CCM_E_INVAL;
+namespace {
+
+// The float whose ordered integer is o.
+double unordered(int64_t o) {
+  const int64_t b = o ^ ((o >> 63) & INT64_MAX);
+  double d;
+  std::memcpy(&d, &b, sizeof d);
+  return d;
+}
+
+// One pass over (or a sample of) n floats: their extremes, CCM_E_RANGE for any
+// NaN or infinity among them.
+int float_extremes(const void *v, int32_t dtype, int64_t n, bool sample, double *vmin,
+                   double *vmax, void *stream) {
+  if (!v || !vmin || !vmax || n < 1 || (dtype != CCM_F32 && dtype != CCM_F64)) return CCM_E_INVAL;
   hipStream_t s = (hipStream_t)stream;
   std::lock_guard<std::mutex> lk(g_mu);
   DeviceCtx *c = nullptr;
@@ -977,14 +990,101 @@ int ccm_float_absmax(const void *v, int32_t dtype, int64_t n, double *absmax, vo
   ccm::RangeSink sink;
   rc = next_sink(c, s, &sink);
   if (rc != CCM_OK) return rc;
-  CCM_HIP(ccm::launch_float_absmax(v, dtype, (uint64_t)n, sink, s));
+  if (sample)
+    CCM_HIP(ccm::launch_float_sample(v, dtype, (uint64_t)n, sink, s));
+  else
+    CCM_HIP(ccm::launch_float_range(v, dtype, (uint64_t)n, sink, s));
   ccm::RangeHost r;
   rc = read_range(c, s, false, &r);
   if (rc != CCM_OK) return rc;
-  if (r.vmax >= 0x7FF0000000000000ll) return CCM_E_RANGE;  // NaN or infinity
-  double a;
-  std::memcpy(&a, &r.vmax, sizeof a);
-  *absmax = a;
+  *vmin = unordered(r.vmin);
+  *vmax = unordered(r.vmax);
+  return std::isfinite(*vmin) && std::isfinite(*vmax) ? CCM_OK : CCM_E_RANGE;
+}
+
+}  // namespace
+
+int ccm_float_range(const void *v, int32_t dtype, int64_t n, double *vmin, double *vmax,
+                    void *stream) {
+  return float_extremes(v, dtype, n, false, vmin, vmax, stream);
+}
+
+int ccm_float_sample(const void *v, int32_t dtype, int64_t n, double *vmin, double *vmax,
+                     void *stream) {
+  return float_extremes(v, dtype, n, true, vmin, vmax, stream);
+}
+
+int ccm_float_absmax(const void *v, int32_t dtype, int64_t n, double *absmax, void *stream) {
+  if (!absmax) return CCM_E_INVAL;
+  double lo = 0, hi = 0;
+  const int rc = float_extremes(v, dtype, n, false, &lo, &hi, stream);
+  if (rc != CCM_OK) return rc;
+  *absmax = std::fabs(lo) > std::fabs(hi) ? std::fabs(lo) : std::fabs(hi);
+  return CCM_OK;
+}
+
+int ccm_quantized_range(double vmin, double vmax, int32_t frac_bits, int64_t *qmin,
+                        int64_t *qmax) {
+  if (!qmin || !qmax || frac_bits < -1200 || frac_bits > 1200 || !(vmin <= vmax) ||
+      std::isinf(vmin) || std::isinf(vmax))
+    return CCM_E_INVAL;
+  const double lo = std::ldexp(vmin, frac_bits), hi = std::ldexp(vmax, frac_bits);
+  if (!(std::fabs(lo) < 0x1p62) || !(std::fabs(hi) < 0x1p62)) return CCM_E_OVERFLOW;
+  *qmin = (int64_t)std::nearbyint(lo);
+  *qmax = (int64_t)std::nearbyint(hi);
+  return CCM_OK;
+}
+
+int ccm_quantize_checked(const void *v, int32_t dtype, int64_t n, int32_t frac_bits, void *q,
+                         int32_t qdtype, void *stream) {
+  if (!v || !q || n < 1 || (dtype != CCM_F32 && dtype != CCM_F64) ||
+      (qdtype != CCM_I32 && qdtype != CCM_I64) || frac_bits < -1200 || frac_bits > 1200)
+    return CCM_E_INVAL;
+  CCM_HIP(ccm::launch_quantize(v, dtype, (uint64_t)n, frac_bits, q, qdtype, ccm::RangeSink{},
+                               (hipStream_t)stream));
+  return CCM_OK;
+}
+
+int ccm_compress_fx_try(const void *v, int32_t dtype, int32_t frac_bits, int64_t rows,
+                        int64_t cols, int32_t bits, int32_t is_signed, void *payload,
+                        double *vmin, double *vmax, int32_t *fits, void *stream) {
+  if (!v || !payload || !vmin || !vmax || !fits || !shape_ok(rows, cols) ||
+      (dtype != CCM_F32 && dtype != CCM_F64) || frac_bits < -1200 || frac_bits > 1200 ||
+      bits < 1 || bits > (is_signed ? 64 : 63))
+    return CCM_E_INVAL;
+  const uint64_t n = (uint64_t)rows * (uint64_t)cols;
+  // quantized values stay below 2^62 in magnitude whatever the width
+  const double top = std::ldexp(1.0, is_signed ? bits - 1 : bits);
+  const double qhi = top > 0x1p62 ? 0x1p62 : top - 1.0;
+  const double qlo = is_signed ? (top > 0x1p62 ? -0x1p62 : -top) : 0.0;
+  hipStream_t s = (hipStream_t)stream;
+  std::lock_guard<std::mutex> lk(g_mu);
+  DeviceCtx *c = nullptr;
+  int rc = device_ctx(s, &c);
+  if (rc != CCM_OK) return rc;
+  ccm::RangeSink sink;
+  rc = next_sink(c, s, &sink);
+  if (rc != CCM_OK) return rc;
+  CCM_HIP(ccm::launch_compress_fx_range(v, dtype, n, frac_bits, bits, qlo, qhi,
+                                        (uint32_t *)payload, ccm::cap_words32(n, bits), sink, s));
+  ccm::RangeHost r;
+  rc = read_range(c, s, false, &r);  // published from a kernel of its own
+  if (rc != CCM_OK) return rc;
+  *vmin = unordered(r.vmin);
+  *vmax = unordered(r.vmax);
+  if (!std::isfinite(*vmin) || !std::isfinite(*vmax)) return CCM_E_RANGE;
+  *fits = r.flag ? 0 : 1;
+  return CCM_OK;
+}
+
+int ccm_decompress_fx(const ccm_desc *a, int32_t frac_bits, int32_t dtype, void *out,
+                      void *stream) {
+  int rc = check_desc(a, true);
+  if (rc != CCM_OK) return rc;
+  if (!out || (dtype != CCM_F32 && dtype != CCM_F64) || frac_bits < -2400 || frac_bits > 2400)
+    return CCM_E_INVAL;
+  CCM_HIP(ccm::launch_decompress_fx((const uint32_t *)a->payload, nelem(a), a->bits, a->is_signed,
+                                    frac_bits, dtype, out, (hipStream_t)stream));
   return CCM_OK;
 }
 

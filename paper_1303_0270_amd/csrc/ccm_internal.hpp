@@ -431,17 +431,27 @@ hipError_t launch_add_pack_range(PackedOperand a, PackedOperand b, uint64_t n, i
                                  hipStream_t s);
 
 hipError_t launch_fill_i64(int64_t *p, uint64_t n, int64_t v, hipStream_t s);
-// floats in fixed point: largest |v| (as the bit pattern of a double) into
-// slot's vmax; q = RNE(v 2^f) as int64 or int32 (q null: not written) with
-// q's range in slot (flag:
-// NaN or infinity; vmax INT64_MAX: some |v 2^f| >= 2^62 or q outside the
-// output type); out = q 2^-f (armed slots)
-hipError_t launch_float_absmax(const void *v, int dtype, uint64_t n, RangeSink sink,
+// Floats in fixed point.  Ranges of floats are integers that order like them
+// (b ^ ((b >> 63) & INT64_MAX) of a double's bits): any NaN or infinity leaves
+// the extremes at or past +-infinity's.  q = RNE(v 2^f) as int64 or int32 (q
+// null: not written) with q's range in the sink (flag: NaN or infinity; vmax
+// INT64_MAX: some |v 2^f| >= 2^62 or q outside the output type; null sink: the
+// values were checked before); out = q 2^-f.
+hipError_t launch_float_range(const void *v, int dtype, uint64_t n, RangeSink sink,
+                              hipStream_t s);
+hipError_t launch_float_sample(const void *v, int dtype, uint64_t n, RangeSink sink,
                                hipStream_t s);
 hipError_t launch_quantize(const void *v, int dtype, uint64_t n, int frac_bits, void *q,
                            int qdtype, RangeSink sink, hipStream_t s);
 hipError_t launch_dequantize(const int64_t *q, uint64_t n, int frac_bits, int dtype, void *out,
                              hipStream_t s);
+// Packing at a guessed width with the range of v (flag: some q did not fit
+// [qlo, qhi], the payload is void); q 2^-f as floats from the packed fields.
+hipError_t launch_compress_fx_range(const void *v, int dtype, uint64_t n, int frac_bits, int bits,
+                                    double qlo, double qhi, uint32_t *out, uint64_t cap32,
+                                    RangeSink sink, hipStream_t s);
+hipError_t launch_decompress_fx(const uint32_t *w, uint64_t n, int bits, int sgn, int frac_bits,
+                                int dtype, void *out, hipStream_t s);
 // packs RNE(v 2^f) at `bits` straight from n floats (values checked before)
 hipError_t launch_compress_fx(const void *v, int dtype, uint64_t n, int frac_bits, int bits,
                               uint32_t *out, uint64_t cap32, hipStream_t s);
