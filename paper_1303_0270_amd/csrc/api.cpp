@@ -1259,30 +1259,33 @@ uint64_t ccm_vlb_payload_capacity(uint64_t nbits) { return vlb_cap32(nbits) * 4u
 int ccm_vlb_compress_plan(const void *dense, int32_t dtype, int64_t rows, int64_t cols,
                           void *index, ccm_vlb_desc *out, void *stream) {
   if (!out || !index || !shape_ok(rows, cols)) return CCM_E_INVAL;
-  int64_t lo = 0, hi = 0;
-  int rc = ccm_range(dense, dtype, rows * cols, &lo, &hi, stream);
-  if (rc != CCM_OK) return rc;
-  int32_t bmax = 0, k = 0;
-  vlb_widths(lo, hi, &bmax, &k);
-  // group offsets within a row are 32-bit
-  if ((unsigned __int128)cols * (unsigned __int128)(k + bmax) >= ((unsigned __int128)1 << 32))
-    return CCM_E_UNSUPPORTED;
+  if (!dense || (dtype != CCM_I32 && dtype != CCM_I64)) return CCM_E_INVAL;
   hipStream_t s = (hipStream_t)stream;
   uint64_t *row_bit = (uint64_t *)index;
   uint32_t *grp = (uint32_t *)((char *)index + vlb_grp_offset(rows));
   std::lock_guard<std::mutex> lk(g_mu);
   DeviceCtx *c = nullptr;
-  rc = device_ctx(s, &c);
+  int rc = device_ctx(s, &c);
   if (rc != CCM_OK) return rc;
   ccm::RangeSink sink;
   rc = next_sink(c, s, &sink);
   if (rc != CCM_OK) return rc;
-  CCM_HIP(ccm::launch_vlb_sizes(dense, dtype, rows, cols, k, lo < 0 ? 1 : 0, grp, sink, s));
-  CCM_HIP(ccm::launch_vlb_scan(rows, cols, grp, row_bit, s));
-  uint64_t *h = c->words;
-  CCM_HIP(hipMemcpyAsync(h, row_bit + rows, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
-  ccm::RangeHost gr;
-  rc = read_range(c, s, true, &gr);  // synchronizes the stream
+  CCM_HIP(ccm::launch_vlb_stats(dense, dtype, rows, cols, grp, sink, s));
+  ccm::RangeHost r;
+  // the sums it writes beside the range are read by kernels that follow it
+  rc = read_range(c, s, false, &r);
+  if (rc != CCM_OK) return rc;
+  const int64_t lo = r.vmin, hi = r.vmax;
+  int32_t bmax = 0, k = 0;
+  vlb_widths(lo, hi, &bmax, &k);
+  // group offsets within a row are 32-bit
+  if ((unsigned __int128)cols * (unsigned __int128)(k + bmax) >= ((unsigned __int128)1 << 32))
+    return CCM_E_UNSUPPORTED;
+  rc = next_sink(c, s, &sink);
+  if (rc != CCM_OK) return rc;
+  CCM_HIP(ccm::launch_vlb_scan(rows, cols, k, lo < 0 ? 1 : 0, grp, row_bit, sink, s));
+  // published after the index is complete (its last kernel is one block)
+  rc = read_range(c, s, false, &r);
   if (rc != CCM_OK) return rc;
   out->rows = rows;
   out->cols = cols;
@@ -1290,9 +1293,9 @@ int ccm_vlb_compress_plan(const void *dense, int32_t dtype, int64_t rows, int64_
   out->vmax = hi;
   out->k = k;
   out->is_signed = lo < 0 ? 1 : 0;
-  out->nbits = *h;
+  out->nbits = (uint64_t)r.vmin;
   out->words = out->nbits / 64u + 1u;
-  out->gmax = (uint64_t)gr.vmax;
+  out->gmax = (uint64_t)r.vmax;
   out->payload = nullptr;
   out->index = index;
   return CCM_OK;

@@ -529,14 +529,15 @@ struct VlbView {
   uint64_t nbits;           // stream bits
 };
 uint64_t vlb_ngr(int64_t cols);
-// pass 1: grp[i][g] = bits of group g of row i (sum of k + b_e); the largest
-// folds into slot's vmax (armed slots)
-hipError_t launch_vlb_sizes(const void *dense, int dtype, int64_t rows, int64_t cols, int k,
-                            int sgn, uint32_t *grp, RangeSink sink, hipStream_t s);
-// pass 2: counts -> offsets within rows, row starts and the total in row_bit
-hipError_t launch_vlb_scan(int64_t rows, int64_t cols, uint32_t *grp, uint64_t *row_bit,
-                           hipStream_t s);
-// pass 3: the stream (zeroes cap32 words first)
+// pass 1: the range, and per group the sum of its elements' unsigned widths and,
+// 16 bits up, of their two's complement widths
+hipError_t launch_vlb_stats(const void *dense, int dtype, int64_t rows, int64_t cols,
+                            uint32_t *grp, RangeSink sink, hipStream_t s);
+// pass 2: those sums -> offsets within rows, row starts and the total in
+// row_bit; publishes the total (vmin) and the longest group's bits (vmax)
+hipError_t launch_vlb_scan(int64_t rows, int64_t cols, int k, int sgn, uint32_t *grp,
+                           uint64_t *row_bit, RangeSink sink, hipStream_t s);
+// pass 3: the stream, zeros from nbits to cap32 words
 hipError_t launch_vlb_pack(const void *dense, int dtype, const VlbView &a, uint32_t *out,
                            uint64_t cap32, uint64_t nbits, hipStream_t s);
 hipError_t launch_vlb_decode(const VlbView &a, int64_t *out, hipStream_t s);

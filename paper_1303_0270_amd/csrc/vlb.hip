@@ -16,13 +16,14 @@
 // length just read, so the walk is serial within a group and parallel across
 // groups.
 //
-// Encoding runs in three passes: group bit counts (sum of k + b_e), scans
-// (within rows, then over rows) that turn the counts into the index, and the
-// packing pass, where a block assembles the bits of 64 consecutive groups in
-// LDS (a half-wave per group places its pairs with a prefix sum of their
-// lengths) and writes them out: the words its stretch covers entirely with
-// plain stores, the two it shares with its neighbours with atomic ORs into
-// the zeroed payload.
+// Encoding reads the dense values twice.  The first pass gives the exact range
+// (hence k and the sign rule) and, per group, the sum of the element widths
+// under either sign rule; scans (within rows, then over rows) add k per
+// element and turn the sums into the index.  In the packing pass a block
+// assembles the bits of 128 consecutive groups in LDS (four elements a lane,
+// eight lanes a group, placed with a prefix sum of their lengths) and writes
+// them out: the words its stretch covers entirely with plain stores, the two
+// it shares with its neighbours with atomic ORs into words zeroed before.
 #include <hip/hip_runtime.h>
 
 #include "ccm_internal.hpp"
@@ -62,42 +63,77 @@ __device__ __forceinline__ uint64_t bits_at(const uint32_t *w, uint64_t p, int n
   return v & mask64(nb);
 }
 
-// ---- pass 1: bits per group --------------------------------------------
+// ---- four elements a lane -----------------------------------------------------
+//
+// Both passes over the dense values give lane t of a wave elements
+// 32g + 4(t % 8) .. + 3 of group t / 8: two (int64) or one (int32) 16-byte
+// loads that a wave's lanes lay side by side, a group's sums three shuffles
+// apart instead of five, and the work of placing a pair shared by four.
 
-// Half-wave h of a wave owns one group: lane l reads element 32g + l, and the
-// 32 lanes sum k + b_e.  The grid-stride step is a multiple of 32 and the
-// total a multiple of 32, so a group's lanes are always active together.
+constexpr int kQuad = 4;                      // elements per lane
+constexpr int kLanes = kVG / kQuad;           // lanes per group
+constexpr int kStepGroups = kVThreads / kLanes;  // groups a block takes per step
+
+// Elements j0 .. j0 + 3 of row i, clamped into the row (what lies past its end
+// is the caller's to drop): loads without branches, so that the compiler
+// issues all of a lane's before it waits for the first.  VEC: rows and quads
+// start on 16-byte boundaries and every quad lies wholly inside or outside.
+template <bool VEC, typename T>
+__device__ __forceinline__ void load_quad(const T *__restrict__ d, uint64_t i, int64_t j0,
+                                          int64_t cols, T (&v)[kQuad]) {
+  const T *p = d + i * (uint64_t)cols;
+  if constexpr (VEC) {
+    constexpr int N = kQuad * (int)sizeof(T) / 16;
+    const uint4 *p4 = reinterpret_cast<const uint4 *>(p + (j0 < cols ? j0 : 0));
+    uint4 r[N];
+#pragma unroll
+    for (int q = 0; q < N; ++q) r[q] = p4[q];
+#pragma unroll
+    for (int q = 0; q < kQuad; ++q) v[q] = reinterpret_cast<const T *>(r)[q];
+  } else {
+#pragma unroll
+    for (int q = 0; q < kQuad; ++q) v[q] = p[j0 + q < cols ? j0 + q : cols - 1];
+  }
+}
+
 template <typename T>
-__global__ __launch_bounds__(kVThreads) void k_vlb_sizes(const T *__restrict__ dense, int64_t rows,
-                                                         int64_t cols, int64_t ngr, int k, int sgn,
+bool quads_aligned(const T *d, int64_t cols) {
+  return (uintptr_t)d % 16 == 0 && cols % kQuad == 0;
+}
+
+// ---- pass 1: range, and element widths per group -------------------------------
+
+// grp[group] = sum of the unsigned widths | sum of the two's complement widths
+// << 16 (each at most 32 * 64).  The unsigned ones mean nothing in a matrix
+// with a negative value, which takes the others.  Bound by memory; the range
+// and the sums were a pass each before (206 + 280 us at 16384 x 8192 int64
+// against 220 here, 4.9 TB/s).
+template <bool VEC, typename T>
+__global__ __launch_bounds__(kVThreads) void k_vlb_stats(const T *__restrict__ dense, int64_t rows,
+                                                         int64_t cols, int64_t ngr,
                                                          uint32_t *__restrict__ grp,
                                                          RangeSink sink) {
-  const uint64_t total = (uint64_t)rows * (uint64_t)ngr * kVG;
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+  const uint64_t total = (uint64_t)rows * (uint64_t)ngr;
+  const uint64_t step = (uint64_t)gridDim.x * kStepGroups;
   // group gi = (row i, group g of the row), advanced by the grid step with
-  // one division up front (a 64-bit division per element would cost more
-  // than the element's own work)
-  const uint64_t gstep = stride >> 5;
-  const uint64_t di = gstep / (uint64_t)ngr, dg = gstep - di * (uint64_t)ngr;
-  uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  uint64_t i = (t >> 5) / (uint64_t)ngr, g = (t >> 5) - i * (uint64_t)ngr;
-  const int l = (int)(t & 31u);
-  uint32_t gmax = 0;
-  // kSizeSteps grid steps per iteration: their loads (unconditional, with
-  // clamped row and column) are all issued before any is used.  A step's
-  // validity is the same for the 32 lanes of a group (total and the step are
-  // multiples of 32), so the group's shuffles always run together.
-  constexpr int kSizeSteps = 4;
-  for (; t < total; t += kSizeSteps * stride) {
-    int64_t v[kSizeSteps];
-    bool live[kSizeSteps], valid[kSizeSteps];
+  // one division up front
+  const uint64_t di = step / (uint64_t)ngr, dg = step - di * (uint64_t)ngr;
+  uint64_t gi = (uint64_t)blockIdx.x * kStepGroups + threadIdx.x / kLanes;
+  uint64_t i = gi / (uint64_t)ngr, g = gi - i * (uint64_t)ngr;
+  const int sub = threadIdx.x % kLanes;
+  int64_t lo = INT64_MAX, hi = INT64_MIN;
+  // kSteps grid steps per iteration, their loads issued before any is used
+  constexpr int kSteps = 4;
+  for (; gi < total; gi += kSteps * step) {
+    T v[kSteps][kQuad];
+    int live[kSteps];
 #pragma unroll
-    for (int u = 0; u < kSizeSteps; ++u) {
-      valid[u] = t + u * stride < total;
-      const uint64_t j = g * kVG + (uint64_t)l;
-      live[u] = valid[u] && j < (uint64_t)cols;
-      const uint64_t ic = valid[u] ? i : (uint64_t)rows - 1;
-      v[u] = load_dense(dense, ic * (uint64_t)cols + (live[u] ? j : (uint64_t)cols - 1));
+    for (int u = 0; u < kSteps; ++u) {
+      const bool valid = gi + u * step < total;
+      const int64_t j0 = (int64_t)g * kVG + sub * kQuad;
+      const int64_t left = valid ? cols - j0 : 0;
+      live[u] = left >= kQuad ? kQuad : left > 0 ? (int)left : 0;
+      load_quad<VEC>(dense, valid ? i : 0, j0, cols, v[u]);
       g += dg;
       i += di;
       if (g >= (uint64_t)ngr) {
@@ -106,24 +142,33 @@ __global__ __launch_bounds__(kVThreads) void k_vlb_sizes(const T *__restrict__ d
       }
     }
 #pragma unroll
-    for (int u = 0; u < kSizeSteps; ++u) {
-      uint32_t nb = live[u] ? (uint32_t)(k + elem_width(v[u], sgn)) : 0u;
+    for (int u = 0; u < kSteps; ++u) {
+      uint32_t sum = 0;
 #pragma unroll
-      for (int m = 16; m >= 1; m >>= 1) nb += (uint32_t)__shfl_xor((int)nb, m, 32);
-      if (l == 0 && valid[u]) grp[(t + u * stride) >> 5] = nb;
-      gmax = nb > gmax ? nb : gmax;
+      for (int q = 0; q < kQuad; ++q) {
+        if (q < live[u]) {
+          const int64_t x = (int64_t)v[u][q];
+          lo = x < lo ? x : lo;
+          hi = x > hi ? x : hi;
+          const uint32_t L = (uint32_t)bitlen64((uint64_t)(x ^ (x >> 63)));
+          sum += (L > 1u ? L : 1u) + ((L + 1u) << 16);
+        }
+      }
+#pragma unroll
+      for (int m = kLanes / 2; m >= 1; m >>= 1) sum += (uint32_t)__shfl_xor((int)sum, m, kLanes);
+      if (sub == 0 && gi + u * step < total) grp[gi + u * step] = sum;
     }
   }
-  // the longest group (sizes the staging buffers of the matvec kernel)
-  block_range_commit(0, (int64_t)gmax, 0, sink);
+  block_range_commit(lo, hi, 0, sink);
 }
 
 // ---- pass 2: scans ----------------------------------------------------------
 
 // Inclusive block-wide scan of one value per thread (uint64), with the block
 // total.  Every thread must call it.
+template <int NT>
 __device__ __forceinline__ uint64_t block_scan_incl(uint64_t v, uint64_t *total) {
-  __shared__ uint64_t s_wave[kVThreads / 64];
+  __shared__ uint64_t s_wave[NT / 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
@@ -134,7 +179,7 @@ __device__ __forceinline__ uint64_t block_scan_incl(uint64_t v, uint64_t *total)
   __syncthreads();
   uint64_t before = 0, all = 0;
 #pragma unroll
-  for (int w = 0; w < kVThreads / 64; ++w) {
+  for (int w = 0; w < NT / 64; ++w) {
     const uint64_t s = s_wave[w];
     before += w < wave ? s : 0;
     all += s;
@@ -144,142 +189,241 @@ __device__ __forceinline__ uint64_t block_scan_incl(uint64_t v, uint64_t *total)
   return v + before;
 }
 
-// Row i's group counts become exclusive offsets from the row start; the row's
-// total goes to row_bit[i + 1] (pass 3 turns those into starts).
-__global__ __launch_bounds__(kVThreads) void k_vlb_row_scan(int64_t rows, int64_t ngr,
+// Row i's width sums (under the matrix's sign rule, k added per element) become
+// exclusive offsets from the row start; the row's total goes to row_bit[i + 1]
+// (the next kernel turns those into starts).  A wave per row, four groups a
+// lane and step: no barrier between rows.  The longest group, which sizes the
+// staging buffers of the other kernels, folds into the slots' maximum.
+__global__ __launch_bounds__(kVThreads) void k_vlb_row_scan(int64_t rows, int64_t cols,
+                                                            int64_t ngr, int k, int sgn,
                                                             uint32_t *__restrict__ grp,
-                                                            uint64_t *__restrict__ row_bit) {
-  for (int64_t i = blockIdx.x; i < rows; i += gridDim.x) {
+                                                            uint64_t *__restrict__ row_bit,
+                                                            RangeSink slots) {
+  constexpr int kWaves = kVThreads / 64;
+  const int lane = threadIdx.x & 63;
+  uint32_t gmax = 0;
+  for (int64_t i = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6); i < rows;
+       i += (int64_t)gridDim.x * kWaves) {
     uint32_t *gp = grp + (uint64_t)i * (uint64_t)ngr;
-    uint64_t carry = 0;
-    for (int64_t c0 = 0; c0 < ngr; c0 += kVThreads) {
-      const int64_t g = c0 + threadIdx.x;
-      const uint64_t v = g < ngr ? gp[g] : 0;
-      uint64_t tot = 0;
-      const uint64_t inc = block_scan_incl(v, &tot);
-      if (g < ngr) gp[g] = (uint32_t)(carry + inc - v);
-      carry += tot;
+    uint32_t carry = 0;  // a row holds fewer than 2^32 bits
+    for (int64_t c0 = 0; c0 < ngr; c0 += 4 * 64) {
+      const int64_t g0 = c0 + 4 * lane;
+      uint32_t v[4], sum = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] = gp[g0 + q < ngr ? g0 + q : ngr - 1];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int64_t n = cols - (g0 + q) * kVG;  // elements from this group on
+        v[q] = (sgn ? v[q] >> 16 : v[q] & 0xffffu) + (uint32_t)k * (uint32_t)(n < kVG ? n : kVG);
+        v[q] = g0 + q < ngr ? v[q] : 0u;
+        gmax = v[q] > gmax ? v[q] : gmax;
+        sum += v[q];
+      }
+      uint32_t inc = sum;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t o = (uint32_t)__shfl_up((int)inc, d, 64);
+        if (lane >= d) inc += o;
+      }
+      uint32_t at = carry + inc - sum;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (g0 + q < ngr) gp[g0 + q] = at;
+        at += v[q];
+      }
+      carry += (uint32_t)__shfl((int)inc, 63, 64);
     }
-    if (threadIdx.x == 0) row_bit[i + 1] = carry;
+    if (lane == 0) row_bit[i + 1] = carry;
   }
+  block_range_commit(INT64_MAX, (int64_t)gmax, 0, slots);
 }
 
-// row_bit[0] = 0 and row_bit[i + 1] = sum of the first i + 1 row totals.  One
-// block.
-__global__ __launch_bounds__(kVThreads) void k_vlb_rows_scan(int64_t rows,
-                                                             uint64_t *__restrict__ row_bit) {
+// row_bit[0] = 0 and row_bit[i + 1] = sum of the first i + 1 row totals, by one
+// block of 1024 threads that takes eight rows each at a time, read and written
+// side by side through LDS; then the total and the longest group are published
+// (vmin and vmax of the record).  16384 rows: 14 us (one row a thread and step
+// 45, eight read straight from memory 20).
+constexpr int kScanThreads = 1024, kScanPer = 8;
+__global__ __launch_bounds__(kScanThreads) void k_vlb_rows_scan(int64_t rows,
+                                                                uint64_t *__restrict__ row_bit,
+                                                                RangeSink sink) {
+  __shared__ uint64_t s_tot[kScanThreads * (kScanPer + 1)];
+  const int t = threadIdx.x;
   uint64_t carry = 0;
-  for (int64_t c0 = 0; c0 < rows; c0 += kVThreads) {
-    const int64_t i = c0 + threadIdx.x;
-    const uint64_t v = i < rows ? row_bit[i + 1] : 0;
-    uint64_t tot = 0;
-    const uint64_t inc = block_scan_incl(v, &tot);
-    if (i < rows) row_bit[i + 1] = carry + inc;
+  for (int64_t c0 = 0; c0 < rows; c0 += kScanThreads * kScanPer) {
+    uint64_t v[kScanPer], sum = 0, tot = 0;
+#pragma unroll
+    for (int q = 0; q < kScanPer; ++q) {
+      const int64_t i = c0 + q * kScanThreads + t;
+      v[q] = i < rows ? row_bit[i + 1] : 0;
+    }
+#pragma unroll
+    for (int q = 0; q < kScanPer; ++q) {
+      const int e = q * kScanThreads + t;
+      s_tot[e + e / kScanPer] = v[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kScanPer; ++q) {
+      v[q] = s_tot[t * (kScanPer + 1) + q];
+      sum += v[q];
+    }
+    uint64_t at = carry + block_scan_incl<kScanThreads>(sum, &tot) - sum;
+#pragma unroll
+    for (int q = 0; q < kScanPer; ++q) {
+      at += v[q];
+      s_tot[t * (kScanPer + 1) + q] = at;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kScanPer; ++q) {
+      const int e = q * kScanThreads + t;
+      if (c0 + e < rows) row_bit[c0 + e + 1] = s_tot[e + e / kScanPer];
+    }
     carry += tot;
+    __syncthreads();
   }
-  if (threadIdx.x == 0) row_bit[0] = 0;
+  if (t == 0) {
+    row_bit[0] = 0;
+    atomicMin((long long *)&sink.slot->vmin, (long long)carry);
+  }
+  __threadfence_system();  // the row starts, before the record
+  __syncthreads();
+  if (t < 64) range_publish(sink);
 }
 
 // ---- pass 3: packing -----------------------------------------------------------
 
-__global__ void k_zero_u32(uint32_t *p, uint64_t n) {
+// Zeroes the words the packing blocks share (the first word of each stretch of
+// kPackGroups groups) and everything from the last one to the capacity's end.
+constexpr int kPackGroups = 128;
+
+__global__ __launch_bounds__(kVThreads) void k_vlb_zero_shared(
+    int64_t ngr, uint64_t total, const uint64_t *__restrict__ row_bit,
+    const uint32_t *__restrict__ grp, uint64_t nbits, uint32_t *__restrict__ out, uint64_t cap32) {
+  const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) p[e] = 0;
+  const uint64_t stretches = (total + kPackGroups - 1) / kPackGroups;
+  for (uint64_t b = t; b < stretches; b += stride) {
+    const uint64_t gb = b * kPackGroups;
+    out[(row_bit[gb / (uint64_t)ngr] + grp[gb]) >> 5] = 0;
+  }
+  for (uint64_t q = (nbits >> 5) + t; q < cap32; q += stride) out[q] = 0;
 }
 
-// ORs the low nb (1..64) bits of val into an LDS bit span at bit pos (at
-// most three words; LDS atomics, since neighbouring lanes share words).
-__device__ __forceinline__ void lds_or_bits(uint32_t *span, uint32_t pos, uint64_t val, int nb) {
-  val &= mask64(nb);
-  const uint32_t q = pos >> 5, sh = pos & 31u;
-  const uint64_t lo = val << sh;
-  const uint32_t hi = sh ? (uint32_t)(val >> (64u - sh)) : 0u;
-  const int nw = (int)((sh + (uint32_t)nb + 31u) >> 5);
-  if ((uint32_t)lo) atomicOr(&span[q], (uint32_t)lo);
-  if (nw > 1 && (uint32_t)(lo >> 32)) atomicOr(&span[q + 1], (uint32_t)(lo >> 32));
-  if (nw > 2 && hi) atomicOr(&span[q + 2], hi);
-}
+// Appends n (1..32) bits x (no bits past n set) to a bit string in LDS: whole
+// words leave as they fill.  LDS atomics, since the first and last word of a
+// lane's bits belong to its neighbours too.
+struct BitAppender {
+  uint32_t *word;
+  uint64_t buf;
+  int used;
+  __device__ __forceinline__ void put(uint32_t x, int n) {
+    buf |= (uint64_t)x << used;
+    used += n;
+    if (used >= 32) {
+      atomicOr(word++, (uint32_t)buf);
+      buf >>= 32;
+      used -= 32;
+    }
+  }
+};
 
 // A block assembles the stream of kPackGroups consecutive groups (a
 // contiguous stretch of bits [S, E)) in LDS, then writes it out.
-//   * A half-wave per group: lane l reads element 32g + l (coalesced), takes
-//     its width b_e, and a 32-lane prefix sum of k + b_e places its pair
-//     (length field, then value) inside the group, which starts at the bit
-//     the index gives.  The pair is ORed into the LDS stretch.
+//   * Each lane loads its four quads of elements (32 groups apart) and their
+//     groups' start bits before placing any.  A quad's bits follow each other,
+//     so a prefix sum over the eight lanes of a group places four pairs at
+//     once, and the lane appends them through a 64-bit buffer: one LDS atomic
+//     per word instead of up to three for each length and each value.
 //   * Write-out: the words the stretch covers entirely are plain coalesced
 //     stores; its first and last words, shared with the neighbouring blocks,
-//     are atomic ORs into the zeroed payload.
-constexpr int kPackGroups = 64;
-
-template <typename T>
+//     are atomic ORs into words zeroed before.
+// Bound by vector instructions at short widths (about 25 an element).  16384 x
+// 8192 int64, bit-lengths Beta(1, 32): 295 us; a lane per element, with
+// the whole payload zeroed before (19 us), took 443.
+template <bool VEC, typename T>
 __global__ __launch_bounds__(kVThreads) void k_vlb_pack(const T *__restrict__ dense, int64_t rows,
                                                         int64_t cols, int64_t ngr, int k, int sgn,
                                                         const uint64_t *__restrict__ row_bit,
                                                         const uint32_t *__restrict__ grp,
-                                                        uint64_t nbits, int span_words,
+                                                        uint64_t nbits,
                                                         uint32_t *__restrict__ out) {
   extern __shared__ uint32_t span[];
   const uint64_t total = (uint64_t)rows * (uint64_t)ngr;
-  const int half = threadIdx.x >> 5, l = threadIdx.x & 31;
+  const int sub = threadIdx.x % kLanes;
   for (uint64_t gb = (uint64_t)blockIdx.x * kPackGroups; gb < total;
        gb += (uint64_t)gridDim.x * kPackGroups) {
     const uint64_t ge = gb + kPackGroups < total ? gb + kPackGroups : total;
-    // stretch [S, E) of groups gb .. ge - 1
-    const uint64_t ib = gb / (uint64_t)ngr;
-    const uint64_t S = row_bit[ib] + grp[gb];
-    uint64_t E;
-    if (ge < total) {
-      const uint64_t ie = ge / (uint64_t)ngr;
-      E = row_bit[ie] + grp[ge];
-    } else {
-      E = nbits;
-    }
-    const uint64_t q0 = S >> 5;
-    const int nwords = (int)(((E + 31u) >> 5) - q0);
-    for (int w = threadIdx.x; w < span_words; w += blockDim.x) span[w] = 0;
-    __syncthreads();
-    // This half-wave's groups of the stretch (at most kPackPer): their
-    // elements and start bits are requested first, with clamped addresses,
-    // then placed one group at a time.  (row, group) advance from one
-    // division per stretch.
-    constexpr int kPackPer = kPackGroups / (kVThreads / 32);
-    const uint64_t gi0 = gb + (uint64_t)half;
+    // (row, group) of this lane's first group; the others from it
+    constexpr int kPackPer = kPackGroups / kStepGroups;
+    const uint64_t gi0 = gb + threadIdx.x / kLanes;
     uint64_t i = gi0 / (uint64_t)ngr, g = gi0 - i * (uint64_t)ngr;
-    int64_t v[kPackPer];
+    T v[kPackPer][kQuad];
     uint64_t gstart[kPackPer];
-    bool live[kPackPer];
+    int live[kPackPer];
 #pragma unroll
     for (int u = 0; u < kPackPer; ++u) {
-      const uint64_t gi = gi0 + (uint64_t)u * (kVThreads / 32);
+      const uint64_t gi = gi0 + (uint64_t)u * kStepGroups;
+      const int64_t j0 = (int64_t)g * kVG + sub * kQuad;
       const bool valid = gi < ge;
-      const uint64_t j = g * kVG + (uint64_t)l;
-      live[u] = valid && j < (uint64_t)cols;
-      const uint64_t ic = valid ? i : (uint64_t)rows - 1;
-      v[u] = load_dense(dense, ic * (uint64_t)cols + (live[u] ? j : (uint64_t)cols - 1));
-      gstart[u] = row_bit[ic] + grp[valid ? gi : total - 1];
-      g += kVThreads / 32;
+      const int64_t left = valid ? cols - j0 : 0;
+      live[u] = left >= kQuad ? kQuad : left > 0 ? (int)left : 0;
+      const uint64_t ic = valid ? i : 0;
+      gstart[u] = row_bit[ic] + grp[valid ? gi : 0];
+      load_quad<VEC>(dense, ic, j0, cols, v[u]);
+      g += kStepGroups;
       while (g >= (uint64_t)ngr) {
         g -= (uint64_t)ngr;
         ++i;
       }
     }
+    // stretch [S, E) of groups gb .. ge - 1
+    const uint64_t S = row_bit[gb / (uint64_t)ngr] + grp[gb];
+    const uint64_t E = ge < total ? row_bit[ge / (uint64_t)ngr] + grp[ge] : nbits;
+    const uint64_t q0 = S >> 5;
+    const int nwords = (int)(((E + 31u) >> 5) - q0);
+    for (int w = threadIdx.x; w < nwords; w += blockDim.x) span[w] = 0;
+    __syncthreads();
 #pragma unroll
     for (int u = 0; u < kPackPer; ++u) {
-      // the same for the 32 lanes of a group, so its shuffles run together
-      if (gi0 + (uint64_t)u * (kVThreads / 32) >= ge) break;
-      const int b = live[u] ? elem_width(v[u], sgn) : 0;
-      const uint32_t len = live[u] ? (uint32_t)(k + b) : 0u;
-      // exclusive prefix sum over the 32 lanes of the group
+      int b[kQuad];
+      uint32_t len = 0;
+#pragma unroll
+      for (int q = 0; q < kQuad; ++q) {
+        b[q] = q < live[u] ? elem_width((int64_t)v[u][q], sgn) : 0;
+        len += q < live[u] ? (uint32_t)(k + b[q]) : 0u;
+      }
       uint32_t inc = len;
 #pragma unroll
-      for (int d = 1; d < 32; d <<= 1) {
-        const uint32_t o = (uint32_t)__shfl_up((int)inc, d, 32);
-        if (l >= d) inc += o;
+      for (int d = 1; d < kLanes; d <<= 1) {
+        const uint32_t o = (uint32_t)__shfl_up((int)inc, d, kLanes);
+        if (sub >= d) inc += o;
       }
-      const uint32_t pos = (uint32_t)(gstart[u] - q0 * 32u) + (inc - len);
       if (live[u]) {
-        lds_or_bits(span, pos, (uint64_t)b, k);                   // the length field
-        lds_or_bits(span, pos + (uint32_t)k, (uint64_t)v[u], b);  // then the value
+        const uint32_t pos = (uint32_t)(gstart[u] - q0 * 32u) + (inc - len);
+        BitAppender bits{span + (pos >> 5), 0, (int)(pos & 31u)};
+#pragma unroll
+        for (int q = 0; q < kQuad; ++q) {
+          if (q < live[u]) {
+            const uint64_t m = (uint64_t)(int64_t)v[u][q] & mask64(b[q]);
+            const uint32_t head = (uint32_t)b[q] | ((uint32_t)m << k);
+            const int n = k + b[q];
+            if (n <= 32) {
+              bits.put(head, n);
+            } else {
+              bits.put(head, 32);
+              const uint64_t rest = m >> (32 - k);
+              if (n <= 64) {
+                bits.put((uint32_t)rest, n - 32);
+              } else {
+                bits.put((uint32_t)rest, 32);
+                bits.put((uint32_t)(rest >> 32), n - 64);
+              }
+            }
+          }
+        }
+        if (bits.used && (uint32_t)bits.buf) atomicOr(bits.word, (uint32_t)bits.buf);
       }
     }
     __syncthreads();
@@ -766,33 +910,43 @@ unsigned vgrid(uint64_t work, uint64_t per_block, unsigned cap) {
 
 uint64_t vlb_ngr(int64_t cols) { return ((uint64_t)cols + kVG - 1) / kVG; }
 
-hipError_t launch_vlb_sizes(const void *dense, int dtype, int64_t rows, int64_t cols, int k,
-                            int sgn, uint32_t *grp, RangeSink sink, hipStream_t s) {
+hipError_t launch_vlb_stats(const void *dense, int dtype, int64_t rows, int64_t cols,
+                            uint32_t *grp, RangeSink sink, hipStream_t s) {
   const int64_t ngr = (int64_t)vlb_ngr(cols);
-  const unsigned grid = vgrid((uint64_t)rows * (uint64_t)ngr * kVG, kVThreads * 4, 4096);
-  if (dtype == CCM_I64)
-    k_vlb_sizes<int64_t><<<grid, kVThreads, 0, s>>>((const int64_t *)dense, rows, cols, ngr, k,
-                                                    sgn, grp, sink);
-  else
-    k_vlb_sizes<int32_t><<<grid, kVThreads, 0, s>>>((const int32_t *)dense, rows, cols, ngr, k,
-                                                    sgn, grp, sink);
+  const unsigned grid = vgrid((uint64_t)rows * (uint64_t)ngr, kStepGroups * 4, 4096);
+  if (dtype == CCM_I64) {
+    const int64_t *d = (const int64_t *)dense;
+    if (quads_aligned(d, cols))
+      k_vlb_stats<true><<<grid, kVThreads, 0, s>>>(d, rows, cols, ngr, grp, sink);
+    else
+      k_vlb_stats<false><<<grid, kVThreads, 0, s>>>(d, rows, cols, ngr, grp, sink);
+  } else {
+    const int32_t *d = (const int32_t *)dense;
+    if (quads_aligned(d, cols))
+      k_vlb_stats<true><<<grid, kVThreads, 0, s>>>(d, rows, cols, ngr, grp, sink);
+    else
+      k_vlb_stats<false><<<grid, kVThreads, 0, s>>>(d, rows, cols, ngr, grp, sink);
+  }
   return hipGetLastError();
 }
 
-hipError_t launch_vlb_scan(int64_t rows, int64_t cols, uint32_t *grp, uint64_t *row_bit,
-                           hipStream_t s) {
+hipError_t launch_vlb_scan(int64_t rows, int64_t cols, int k, int sgn, uint32_t *grp,
+                           uint64_t *row_bit, RangeSink sink, hipStream_t s) {
   const int64_t ngr = (int64_t)vlb_ngr(cols);
-  const unsigned grid = vgrid((uint64_t)rows, 1, 16384);
-  k_vlb_row_scan<<<grid, kVThreads, 0, s>>>(rows, ngr, grp, row_bit);
+  const unsigned grid = vgrid((uint64_t)rows, kVThreads / 64, 2048);
+  k_vlb_row_scan<<<grid, kVThreads, 0, s>>>(rows, cols, ngr, k, sgn, grp, row_bit,
+                                            RangeSink{sink.slot, nullptr, nullptr, 0});
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_vlb_rows_scan<<<1, kVThreads, 0, s>>>(rows, row_bit);
+  k_vlb_rows_scan<<<1, kScanThreads, 0, s>>>(rows, row_bit, sink);
   return hipGetLastError();
 }
 
 hipError_t launch_vlb_pack(const void *dense, int dtype, const VlbView &a, uint32_t *out,
                            uint64_t cap32, uint64_t nbits, hipStream_t s) {
-  k_zero_u32<<<vgrid(cap32, kVThreads * 8, 8192), kVThreads, 0, s>>>(out, cap32);
+  const uint64_t total = (uint64_t)a.rows * (uint64_t)a.ngr;
+  k_vlb_zero_shared<<<vgrid((total + kPackGroups - 1) / kPackGroups, kVThreads, 1024), kVThreads,
+                      0, s>>>(a.ngr, total, a.row_bit, a.grp, nbits, out, cap32);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // a stretch of kPackGroups groups spans at most kPackGroups * gmax bits
@@ -800,16 +954,24 @@ hipError_t launch_vlb_pack(const void *dense, int dtype, const VlbView &a, uint3
   const int span_words = (int)(((uint64_t)kPackGroups * a.gmax + 31u) / 32u + 2u);
   const size_t lds = (size_t)span_words * 4u;
   if (lds > 64 * 1024) return hipErrorInvalidValue;
-  const uint64_t total = (uint64_t)a.rows * (uint64_t)a.ngr;
   const unsigned grid = vgrid(total, kPackGroups, 65536);
-  if (dtype == CCM_I64)
-    k_vlb_pack<int64_t><<<grid, kVThreads, lds, s>>>((const int64_t *)dense, a.rows, a.cols,
-                                                     a.ngr, a.k, a.sgn, a.row_bit, a.grp, nbits,
-                                                     span_words, out);
-  else
-    k_vlb_pack<int32_t><<<grid, kVThreads, lds, s>>>((const int32_t *)dense, a.rows, a.cols,
-                                                     a.ngr, a.k, a.sgn, a.row_bit, a.grp, nbits,
-                                                     span_words, out);
+  if (dtype == CCM_I64) {
+    const int64_t *d = (const int64_t *)dense;
+    if (quads_aligned(d, a.cols))
+      k_vlb_pack<true><<<grid, kVThreads, lds, s>>>(d, a.rows, a.cols, a.ngr, a.k, a.sgn,
+                                                    a.row_bit, a.grp, nbits, out);
+    else
+      k_vlb_pack<false><<<grid, kVThreads, lds, s>>>(d, a.rows, a.cols, a.ngr, a.k, a.sgn,
+                                                     a.row_bit, a.grp, nbits, out);
+  } else {
+    const int32_t *d = (const int32_t *)dense;
+    if (quads_aligned(d, a.cols))
+      k_vlb_pack<true><<<grid, kVThreads, lds, s>>>(d, a.rows, a.cols, a.ngr, a.k, a.sgn,
+                                                    a.row_bit, a.grp, nbits, out);
+    else
+      k_vlb_pack<false><<<grid, kVThreads, lds, s>>>(d, a.rows, a.cols, a.ngr, a.k, a.sgn,
+                                                     a.row_bit, a.grp, nbits, out);
+  }
   return hipGetLastError();
 }
 
