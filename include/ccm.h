@@ -285,12 +285,12 @@ int ccm_result_desc(const ccm_result *r, void *payload, ccm_desc *out);
 
 /* A batch binds n compressed matrices (their descriptors are copied; the
  * payloads must stay valid) and an int32 or int64 x dtype.  Creating it
- * builds a work list of (matrix, row block) items ordered by width and size,
- * with per-width tile choices from a tuning table (JSON written by the
- * project's autotuner, {"widths": {"<b>": {"tile_rows": r,
- * "rows_in_flight": f}}}, f in {1, 2, 4}, capped at 4 for b <= 8, 2 for
- * b <= 16 and 1 above; NULL, an unreadable path or a missing width uses
- * built-in defaults), and copies it to device memory the batch owns. */
+ * builds a work list of (matrix, row block) items ordered by size and width,
+ * with per-width item rows from a tuning table (JSON written by the project's
+ * autotuner, {"widths": {"<b>": {"tile_rows": r}}}, other fields ignored; up
+ * to four times as many in large batches of small items; NULL, an unreadable
+ * path or a missing width uses built-in defaults), and copies it to device
+ * memory the batch owns. */
 typedef struct ccm_batch ccm_batch;
 
 int ccm_batch_create(const ccm_desc *as, int32_t n, int32_t xdtype, const char *tune_json,
@@ -325,7 +325,8 @@ int ccm_batch_ws_destroy(ccm_batch_ws *w);
 
 /* y_t = A_t x_t for the n matrices given (x int32), planned on the host and
  * run as one persistent launch on `stream`.  CCM_E_NOMEM if n or the work
- * list exceeds the workspace.  Async (one host-to-device table copy). */
+ * list (at the table's item rows) exceeds the workspace.  Async (one
+ * host-to-device table copy). */
 int ccm_batch_matvec_dyn(ccm_batch_ws *w, const ccm_desc *as, const void *const *xs,
                          int64_t *const *ys, int32_t n, void *stream);
 

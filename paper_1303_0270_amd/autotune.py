@@ -1,7 +1,6 @@
 """Autotuner for the batched matvec: per field width, picks the rows per work
-item ("tile_rows") and the rows each lane keeps in flight (1, 2 or 4) that give
-the fastest graph launch on a synthetic batch of that width, and writes the
-table read by ccm_batch_create.
+item ("tile_rows") that give the fastest graph launch on a synthetic batch of
+that width, and writes the table read by ccm_batch_create.
 
 usage: python -m paper_1303_0270_amd.autotune [--out PATH] [--widths 1-24]
        [--count 128] [--reps 7]
@@ -76,17 +75,16 @@ def main(argv=None):
         nbytes = sum(8 * m.words for m in mats)
         best = None
         for tile in TILE_ROWS:
-            for rif in ((1, 2, 4) if b <= 8 else (1, 2) if b <= 16 else (1,)):
-                path = os.path.join(tmpdir, f"t{b}_{tile}_{rif}.json")
-                with open(path, "w") as f:
-                    json.dump({"widths": {str(b): {"tile_rows": tile, "rows_in_flight": rif}}}, f)
-                t = time_batch(torch, ccm, mats, xs, ys, path, args.reps)
-                if best is None or t < best[0]:
-                    best = (t, tile, rif)
-        table["widths"][str(b)] = {"tile_rows": best[1], "rows_in_flight": best[2],
+            path = os.path.join(tmpdir, f"t{b}_{tile}.json")
+            with open(path, "w") as f:
+                json.dump({"widths": {str(b): {"tile_rows": tile}}}, f)
+            t = time_batch(torch, ccm, mats, xs, ys, path, args.reps)
+            if best is None or t < best[0]:
+                best = (t, tile)
+        table["widths"][str(b)] = {"tile_rows": best[1],
                                    "us": round(best[0] * 1e6, 1),
                                    "gbs": round(nbytes / best[0] / 1e9, 1)}
-        print(f"b={b:2d} tile_rows={best[1]:5d} rows_in_flight={best[2]} "
+        print(f"b={b:2d} tile_rows={best[1]:5d} "
               f"{best[0] * 1e6:8.1f} us {nbytes / best[0] / 1e9:7.1f} GB/s", flush=True)
         del mats, xs, ys
         torch.cuda.empty_cache()

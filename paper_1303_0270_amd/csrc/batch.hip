@@ -1,20 +1,26 @@
 // Batched matvec: y_t = A_t x_t for many SM-packed matrices of uneven shapes
 // and widths in one persistent kernel launch (optionally a captured HIP graph).
 //
-// Host planner (ccm_batch_create): every matrix is cut into items of at most
-// `tile_rows` rows; items are sorted by width, then by size (largest first),
-// so that a block keeps running one width's code and the big items start
-// early.  Per-width tile_rows and rows-in-flight come from a tuning table
-// (JSON written by the autotuner, or built-in defaults).
+// Host planner (ccm_batch_create): every matrix is cut into items of
+// `tile_rows` rows (a per-width tuning table, JSON written by the autotuner, or
+// built-in defaults; more rows for narrow matrices of a large batch), the items
+// sorted by size class, largest first, and by width within a class: the sizes
+// shrink towards the end, where the blocks have to finish together, and a block
+// still keeps running one width's code for most of its time.  (By width first,
+// the last items were the largest: 4096 matrices of 32..2048 squared, b = 1..24,
+// took 1452 us where this order takes 1416.)
 //
-// Kernel: persistent blocks pull items from an atomic counter.  For an item,
-// the block stages the matrix's x into LDS (zero-padded to whole groups,
-// int16-range check as in the single-matrix kernel), then each wave works on
-// rows.  A row of g groups is handled by L = next_pow2(g) lanes (at most 64),
-// so narrow matrices put several rows on one wave; each lane decodes one
-// group per row with the width's compile-time decoder (funnel-shifted by the
-// row's own bit offset) and the row sum is a segmented shuffle reduction over
-// its L lanes.  Widths above 32 use a runtime-width decoder.
+// Kernel: persistent blocks.  For an item, the block stages the digits of the
+// matrix's x in LDS, then each wave takes tiles of 16 rows through the matrix
+// cores (mv_tile.hpp).  Widths above 32, and payloads off a 16-byte boundary,
+// use a runtime-width decoder.
+//
+// Bound by memory, and in narrow widths by what an item costs besides (its
+// descriptors, x and the barriers).  2048 matrices of 32..2048 squared, in us,
+// with a lane per group of a row and sums by shuffles, and now:
+//   b = 1: 540, 140    b = 4: 595, 273    b = 8: 673, 466
+//   b = 12: 864, 670   b = 16: 1049, 842  b = 24: 1274, 1209 (5.5 TB/s)
+// and the 4096 of mixed widths 1610, 1366 (5.05 TB/s).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -28,14 +34,13 @@
 
 #include "ccm.h"
 #include "ccm_internal.hpp"
-#include "matvec_impl.hpp"
+#include "mv_tile.hpp"
 
 namespace ccm {
 namespace bt {
 
 constexpr int kThreads = 256;
 constexpr int kMaxCols = 8192;  // widest matrix a batch accepts (x is staged whole in LDS)
-constexpr int kPitch = kGroup + 4;
 
 struct Mat {
   const uint32_t *w;
@@ -49,191 +54,96 @@ struct Item {
   int32_t mat;
   int32_t row0;
   int32_t nrows;
-  int32_t rif;  // rows in flight per lane (1 or 2)
+  int32_t pad;
 };
 
-// Sum over aligned segments of L lanes (L a power of two); lane j%L == 0
-// holds the segment's total.
-__device__ __forceinline__ int64_t seg_sum(int64_t v, int L) {
-  uint64_t u = (uint64_t)v;
-  for (int m = 1; m < L; m <<= 1) u += (uint64_t)__shfl_xor((int64_t)u, m, 64);
-  return (int64_t)u;
-}
-
-// Dot product of one group held in w[0..B] (B + 1 words from the group's
-// first word), funnel-shifted by the row's bit offset s (0 leaves the words).
-template <int B, bool SGN, bool FAST>
-__device__ __forceinline__ uint64_t group_words_dot(uint32_t *w, int s, const int32_t *xg) {
-#pragma unroll
-  for (int k = 0; k < B; ++k) w[k] = __builtin_amdgcn_alignbit(w[k + 1], w[k], s);
-  if constexpr (FAST && B <= 16)
-    return mv::group_dot_small<B, SGN>(w, xg);
-  else
-    return mv::group_dot_wide<B, SGN, int32_t>(w, xg);
-}
-
-// Rows [row0, row0+nrows) of matrix m; x staged in xs.  FAST: every x of the
-// matrix is in int16 range (exact int32 runs, see the single-matrix kernel).
-// Each lane has RIF rows in flight: the words of all of them are requested
-// before any is decoded, with rows past the item clamped to its last row
-// (decoded and dropped), so the loads are unconditional and the compiler
-// waits for them together instead of one row at a time.
-template <int B, bool SGN, int RIF, bool FAST>
-__device__ __forceinline__ void item_rows(const Mat &m, int row0, int nrows, const int32_t *xs) {
-  const int ng = (int)((m.cols + kGroup - 1) / kGroup);
-  int L = 1;
-  while (L < ng && L < 64) L <<= 1;
-  const int sub_per_wave = 64 / L;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int sub = lane / L, j0 = lane % L;
-  const int rows_per_pass = (kThreads / 64) * sub_per_wave * RIF;
-  for (int base = 0; base < nrows; base += rows_per_pass) {
-    uint64_t acc[RIF];
-    int rr[RIF];
-#pragma unroll
-    for (int q = 0; q < RIF; ++q) {
-      acc[q] = 0;
-      rr[q] = base + ((wave * RIF + q) * sub_per_wave + sub);
-    }
-    for (int j = j0; j < ng; j += L) {
-      uint32_t w[RIF][B + 1];
-      int sh[RIF];
-#pragma unroll
-      for (int q = 0; q < RIF; ++q) {
-        const int64_t r = row0 + (rr[q] < nrows ? rr[q] : nrows - 1);
-        const uint64_t bit = ((uint64_t)r * (uint64_t)m.cols + (uint64_t)j * kGroup) * B;
-        const uint32_t *gp = m.w + (bit >> 5);
-        sh[q] = (int)(bit & 31u);
-#pragma unroll
-        for (int k = 0; k <= B; ++k) w[q][k] = gp[k];
-      }
-#pragma unroll
-      for (int q = 0; q < RIF; ++q) {
-        const uint64_t d = group_words_dot<B, SGN, FAST>(w[q], sh[q], xs + j * kPitch);
-        acc[q] += rr[q] < nrows ? d : 0u;
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < RIF; ++q) {
-      const int64_t tot = seg_sum((int64_t)acc[q], L);
-      if (j0 == 0 && rr[q] < nrows) m.y[row0 + rr[q]] = tot;
-    }
-  }
-}
-
 // Runtime-width rows (fields wider than 32 bits): one element per lane step.
-__device__ void item_rows_rt(const Mat &m, int row0, int nrows, const int32_t *xs) {
+__device__ void item_rows_rt(const Mat &m, int row0, int nrows) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int32_t *x = (const int32_t *)m.x;
   for (int rr = wave; rr < nrows; rr += kThreads / 64) {
     const int64_t r = row0 + rr;
     uint64_t acc = 0;
     for (int64_t c = lane; c < m.cols; c += 64) {
       const int64_t a = value_at(m.w, (uint64_t)(r * m.cols + c), m.bits, m.sgn);
-      acc += (uint64_t)a * (uint64_t)(int64_t)xs[(c >> 5) * kPitch + (c & 31)];
+      acc += (uint64_t)a * (uint64_t)(int64_t)x[c];
     }
     const int64_t tot = wave_sum((int64_t)acc);
     if (lane == 0) m.y[r] = tot;
   }
 }
 
-// Rows in flight per lane: up to 4 for widths to 8, 2 to 16, 1 above (the
-// words of every row in flight are held in registers, and one kernel holds
-// every width's code, so the widest case sets the register count).
-template <int B>
-constexpr int max_rif() {
-  return B <= 8 ? 4 : B <= 16 ? 2 : 1;
-}
-
-template <int B, bool SGN, bool FAST>
-__device__ __forceinline__ void item_width(const Mat &m, const Item &it, const int32_t *xs) {
-  if constexpr (max_rif<B>() >= 4) {
-    if (it.rif >= 4) {
-      item_rows<B, SGN, 4, FAST>(m, it.row0, it.nrows, xs);
-      return;
-    }
-  }
-  if constexpr (max_rif<B>() >= 2) {
-    if (it.rif >= 2) {
-      item_rows<B, SGN, 2, FAST>(m, it.row0, it.nrows, xs);
-      return;
-    }
-  }
-  item_rows<B, SGN, 1, FAST>(m, it.row0, it.nrows, xs);
-}
-
-template <bool SGN, bool FAST>
-__device__ __forceinline__ void dispatch(const Mat &m, const Item &it, const int32_t *xs) {
+__device__ __forceinline__ void dispatch(const Mat &m, const Item &it, const uint8_t *xd,
+                                         uint64_t xsum, uint8_t *bufs) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int ntile = (it.nrows + mt::kTileRows - 1) / mt::kTileRows;
+  const uint32_t flip = mt::top_flip(m.bits, m.sgn);
+  const uint64_t add = mt::tile_alpha(m.bits, m.sgn) * xsum;
+  const uint64_t cap = 4u * cap_words32((uint64_t)m.rows * (uint64_t)m.cols, m.bits);
   switch (m.bits) {
-#define CCM_B(b) \
-  case b:        \
-    item_width<b, SGN, FAST>(m, it, xs); \
+#define CCM_B(b)                                                                               \
+  case b:                                                                                      \
+    mt::tiles<b, int32_t>(m.w, cap, (int)m.cols, it.row0, (int64_t)it.row0 + it.nrows, wave,   \
+                          kThreads / 64, ntile, flip, xd, add,                                 \
+                          bufs + wave * mt::Unit<b>::bytes, m.y);                              \
     return;
-    CCM_B(1) CCM_B(2) CCM_B(3) CCM_B(4) CCM_B(5) CCM_B(6) CCM_B(7) CCM_B(8) CCM_B(9)
-    CCM_B(10) CCM_B(11) CCM_B(12) CCM_B(13) CCM_B(14) CCM_B(15) CCM_B(16) CCM_B(17)
-    CCM_B(18) CCM_B(19) CCM_B(20) CCM_B(21) CCM_B(22) CCM_B(23) CCM_B(24) CCM_B(25)
-    CCM_B(26) CCM_B(27) CCM_B(28) CCM_B(29) CCM_B(30) CCM_B(31) CCM_B(32)
+    CCM_WIDTH_CASES_32(CCM_B)
 #undef CCM_B
     default:
-      item_rows_rt(m, it.row0, it.nrows, xs);
       return;
   }
 }
 
-__global__ void k_counter_reset(int *counter) { *counter = 0; }
+__global__ void k_counter_reset(int *counter, int first) { *counter = first; }
 
-// Every block loops until the shared counter passes the item count; the exit
-// test is block-uniform (item index broadcast through LDS).  A block stops
-// at its first index past the end, so every block exits.
+// A block takes items blockIdx + r gridDim for the first `rounds` rounds, then
+// the next one by the counter: atomics on one address return one per 12 ns
+// whatever the items hold (35,000 items of 128 rows at b = 1: 440 us of them),
+// and by the second half of a sorted list there is still enough left to level
+// the blocks.  The mix of widths: all by the counter 1378 us, half 1366, three
+// quarters 1403, none 1438.
+//
+// The exit test is block-uniform (item indices from the counter are handed over
+// through LDS).  A block stops at its first index past the end, so every block
+// exits.
 __global__ __launch_bounds__(kThreads) void k_batch(const Mat *__restrict__ mats,
                                                     const Item *__restrict__ items, int nitems,
-                                                    int *counter) {
-  __shared__ __align__(16) int32_t xs[(kMaxCols / kGroup) * kPitch];
-  __shared__ int s_item;
+                                                    int *counter, int rounds, int buf_bytes) {
+  // the waves' buffers, then the digit rows of the widest matrix's x
+  extern __shared__ __align__(16) uint8_t lds[];
+  uint8_t *xd = lds + buf_bytes;
+  __shared__ int s_item[2];
+  __shared__ uint64_t s_sum[kThreads / 64];
   // The next item's index is requested when an item starts and read when it
   // ends, so the atomic's round trip overlaps the item's work.
   int next = 0;
-  if (threadIdx.x == 0) s_item = atomicAdd(counter, 1);
-  for (;;) {
-    __syncthreads();
-    const int it = s_item;
-    if (it >= nitems) break;
-    if (threadIdx.x == 0) next = atomicAdd(counter, 1);
+  int it = blockIdx.x;
+  for (int round = 1; it < nitems; ++round) {
+    if (round >= rounds && threadIdx.x == 0) next = atomicAdd(counter, 1);
     const Item item = items[it];
     const Mat m = mats[item.mat];
-    const int ng = (int)((m.cols + kGroup - 1) / kGroup);
-    const int32_t *x = (const int32_t *)m.x;
-    int small = 1;
-    // stage x with eight independent loads in flight per lane
-    for (int q0 = threadIdx.x; q0 < ng * kGroup; q0 += kThreads * 8) {
-      int32_t v[8];
+    if (m.bits <= 32 && (uintptr_t)m.w % 16 == 0) {
+      const uint64_t part = mt::stage_x<int32_t, kThreads>((const int32_t *)m.x, (int)m.cols,
+                                                           mt::spread_of(m.bits), xd);
+      const uint64_t ws = (uint64_t)wave_sum((int64_t)part);
+      if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = ws;
+      __syncthreads();
+      uint64_t xsum = 0;
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int q = q0 + u * kThreads;
-        v[u] = q < m.cols ? x[q] : 0;
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int q = q0 + u * kThreads;
-        if (q < ng * kGroup) {
-          xs[(q >> 5) * kPitch + (q & 31)] = v[u];
-          small &= (v[u] >= -32768 && v[u] <= 32767);
-        }
-      }
-    }
-    const bool fast = __syncthreads_and(small);
-    if (fast) {
-      if (m.sgn)
-        dispatch<true, true>(m, item, xs);
-      else
-        dispatch<false, true>(m, item, xs);
+      for (int v = 0; v < kThreads / 64; ++v) xsum += s_sum[v];
+      dispatch(m, item, xd, xsum, lds);
     } else {
-      if (m.sgn)
-        dispatch<true, false>(m, item, xs);
-      else
-        dispatch<false, false>(m, item, xs);
+      item_rows_rt(m, item.row0, item.nrows);
     }
-    __syncthreads();  // xs and s_item are rewritten by the next item
-    if (threadIdx.x == 0) s_item = next;
+    if (round < rounds) {
+      it += gridDim.x;
+      __syncthreads();  // xd is rewritten by the next item
+    } else {
+      // the other slot: slower waves may still be reading the last one
+      if (threadIdx.x == 0) s_item[round & 1] = next;
+      __syncthreads();
+      it = __builtin_amdgcn_readfirstlane(s_item[round & 1]);
+    }
   }
 }
 
@@ -247,6 +157,16 @@ __global__ __launch_bounds__(kThreads) void k_batch(const Mat *__restrict__ mats
 using ccm::bt::Item;
 using ccm::bt::Mat;
 
+// Launch shape of a batch whose widest matrix has `cols` columns: LDS for its
+// digit rows, and as many blocks as are resident with it.
+namespace {
+struct Shape {
+  int lds = 0, bufs = 0, grid = 0;
+  // rounds of items that the blocks take by their own index
+  int rounds(size_t items) const { return 1 + (int)(items / grid) / 2; }
+};
+}  // namespace
+
 struct ccm_batch {
   int n = 0;
   int32_t xdtype = CCM_I32;
@@ -257,7 +177,7 @@ struct ccm_batch {
   Mat *d_mats = nullptr;
   Item *d_items = nullptr;
   int *d_counter = nullptr;
-  int grid = 0;
+  Shape shape;
   hipStream_t cap_stream = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -268,18 +188,16 @@ namespace {
 
 struct TuneEntry {
   int tile_rows = 256;
-  int rif = 1;
 };
 
 // Defaults: small widths need more rows per item to amortize staging x.
 TuneEntry default_tune(int bits) {
   TuneEntry t;
   t.tile_rows = bits <= 4 ? 512 : bits <= 12 ? 256 : 128;
-  t.rif = bits <= 8 ? 4 : bits <= 16 ? 2 : 1;
   return t;
 }
 
-// Reads {"widths": {"<b>": {"tile_rows": r, "rows_in_flight": f}, ...}}; any
+// Reads {"widths": {"<b>": {"tile_rows": r}, ...}}, other fields ignored; any
 // parse problem leaves the defaults in place.
 void load_tune(const char *path, TuneEntry table[65]) {
   for (int b = 1; b <= 64; ++b) table[b] = default_tune(b);
@@ -303,8 +221,6 @@ void load_tune(const char *path, TuneEntry table[65]) {
       if (v > 0) *out = v;
     };
     field("\"tile_rows\"", &table[b].tile_rows);
-    field("\"rows_in_flight\"", &table[b].rif);
-    if (table[b].rif != 2 && table[b].rif != 4) table[b].rif = 1;
     if (table[b].tile_rows < 1) table[b].tile_rows = 1;
   }
 }
@@ -327,36 +243,63 @@ int check_batch_descs(const ccm_desc *as, int32_t n) {
   return CCM_OK;
 }
 
-// Work list: items of at most tile_rows rows, ordered by width then size.
-void plan_items(const std::vector<Mat> &mats, const TuneEntry *table, std::vector<Item> *items) {
+// Work list: items of tile_rows rows.  Where that gives every one of `blocks`
+// blocks four or more, an item of fewer than 64 KB takes up to four times the
+// rows: below that, what an item costs besides its payload shows (2048 matrices
+// of 32..2048 squared, items of 128 and 512 rows: b = 1 211 and 140 us, b = 8
+// 482 and 466, but b = 24 1209 and 1225; 64 matrices, which fill the blocks
+// barely once, 36 and 38 us at b = 4, 47 and 80 at b = 16).  Returns the number
+// of items of tile_rows rows, which bounds the list.
+int64_t plan_items(const std::vector<Mat> &mats, const TuneEntry *table, int blocks,
+                std::vector<Item> *items) {
   items->clear();
+  int64_t count = 0;
+  for (const Mat &d : mats)
+    count += (d.rows + table[d.bits].tile_rows - 1) / table[d.bits].tile_rows;
+  const int most = count >= 4 * (int64_t)blocks ? 4 : 1;
   for (size_t t = 0; t < mats.size(); ++t) {
     const Mat &d = mats[t];
-    const TuneEntry te = table[d.bits];
-    for (int64_t r = 0; r < d.rows; r += te.tile_rows) {
-      const int nr = (int)std::min<int64_t>(te.tile_rows, d.rows - r);
-      items->push_back(Item{(int32_t)t, (int32_t)r, nr, te.rif});
+    int64_t rows = table[d.bits].tile_rows;
+    const int64_t limit = rows * most;
+    while (rows < limit && (uint64_t)rows * d.cols * d.bits < (64u << 10) * 8u) rows *= 2;
+    for (int64_t r = 0; r < d.rows; r += rows) {
+      const int nr = (int)std::min<int64_t>(rows, d.rows - r);
+      items->push_back(Item{(int32_t)t, (int32_t)r, nr, 0});
     }
   }
+  auto bits_of = [&](const Item &x) {
+    return (uint64_t)x.nrows * (uint64_t)mats[x.mat].cols * (uint64_t)mats[x.mat].bits;
+  };
   std::stable_sort(items->begin(), items->end(), [&](const Item &x, const Item &y) {
     const Mat &a = mats[x.mat], &c = mats[y.mat];
+    const uint64_t sa = bits_of(x), sc = bits_of(y);
+    const int la = __builtin_clzll(sa), lc = __builtin_clzll(sc);  // size classes: powers of two
+    if (la != lc) return la < lc;
     if (a.bits != c.bits) return a.bits < c.bits;
-    const uint64_t sa = (uint64_t)x.nrows * a.cols, sc = (uint64_t)y.nrows * c.cols;
     return sa > sc;
   });
+  return count;
 }
 
-int resident_grid() {
+constexpr int kShapes = 4;
+Shape launch_shape(int64_t cols, int bits) {
+  Shape p;
+  for (int b = 1; b <= bits && b <= 32; ++b)
+    p.bufs = std::max(p.bufs, (ccm::bt::kThreads / 64) * ccm::mt::unit_bytes(b));
+  p.lds = p.bufs + ccm::mt::x_lds<int32_t>((int)cols);
+  (void)hipFuncSetAttribute(reinterpret_cast<const void *>(ccm::bt::k_batch),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
   int occ = 0, dev = 0, cus = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, ccm::bt::k_batch, ccm::bt::kThreads, 0) !=
-          hipSuccess ||
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, ccm::bt::k_batch, ccm::bt::kThreads,
+                                                   (size_t)p.lds) != hipSuccess ||
       occ < 1)
     occ = 1;
   (void)hipGetDevice(&dev);
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
       cus < 1)
     cus = 256;
-  return occ * cus;
+  p.grid = occ * cus;
+  return p;
 }
 
 }  // namespace
@@ -374,7 +317,7 @@ struct ccm_batch_ws {
   };
   int max_mats = 0;
   int64_t max_items = 0;
-  int grid = 0;
+  Shape shapes[kShapes];  // by the widest matrix: up to 1024, 2048, 4096, 8192 columns
   int next = 0;
   TuneEntry table[65];
   std::vector<Slot> slots;
@@ -417,7 +360,10 @@ int ccm_batch_create(const ccm_desc *as, int32_t n, int32_t xdtype, const char *
     b->packed_bytes += 8u * d.words;
     b->max_bits = std::max(b->max_bits, d.bits);
   }
-  plan_items(b->mats, table, &b->items);
+  int64_t max_cols = 1;
+  for (const Mat &m : b->mats) max_cols = std::max(max_cols, m.cols);
+  b->shape = launch_shape(max_cols, b->max_bits);
+  plan_items(b->mats, table, b->shape.grid, &b->items);
   rc = hip_status(hipMalloc(&b->d_mats, sizeof(Mat) * n));
   if (rc == CCM_OK) rc = hip_status(hipMalloc(&b->d_items, sizeof(Item) * b->items.size()));
   if (rc == CCM_OK) rc = hip_status(hipMalloc(&b->d_counter, 256));
@@ -426,7 +372,6 @@ int ccm_batch_create(const ccm_desc *as, int32_t n, int32_t xdtype, const char *
                               hipMemcpyHostToDevice));
   if (rc == CCM_OK) rc = hip_status(hipMemcpy(b->d_mats, b->mats.data(), sizeof(Mat) * n,
                                               hipMemcpyHostToDevice));
-  if (rc == CCM_OK) b->grid = resident_grid();
   if (rc == CCM_OK) rc = hip_status(hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking));
   if (rc != CCM_OK) {
     ccm_batch_destroy(b);
@@ -452,11 +397,12 @@ int ccm_batch_set_io(ccm_batch *b, const void *const *xs, int64_t *const *ys, vo
 }
 
 static int batch_enqueue(ccm_batch *b, hipStream_t s) {
-  ccm::bt::k_counter_reset<<<1, 1, 0, s>>>(b->d_counter);
+  const int rounds = b->shape.rounds(b->items.size());
+  ccm::bt::k_counter_reset<<<1, 1, 0, s>>>(b->d_counter, rounds * b->shape.grid);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_status(e);
-  ccm::bt::k_batch<<<b->grid, ccm::bt::kThreads, 0, s>>>(b->d_mats, b->d_items,
-                                                        (int)b->items.size(), b->d_counter);
+  ccm::bt::k_batch<<<b->shape.grid, ccm::bt::kThreads, b->shape.lds, s>>>(
+      b->d_mats, b->d_items, (int)b->items.size(), b->d_counter, rounds, b->shape.bufs);
   return hip_status(hipGetLastError());
 }
 
@@ -511,7 +457,8 @@ int ccm_batch_ws_create(int32_t max_mats, int64_t max_items, int32_t slots, cons
     if (rc == CCM_OK) rc = hip_status(hipMalloc((void **)&sl.d_counter, 256));
     if (rc == CCM_OK) rc = hip_status(hipEventCreateWithFlags(&sl.done, hipEventDisableTiming));
   }
-  if (rc == CCM_OK) w->grid = resident_grid();
+  for (int i = 0; rc == CCM_OK && i < kShapes; ++i)
+    w->shapes[i] = launch_shape(ccm::bt::kMaxCols >> (kShapes - 1 - i), 32);
   if (rc != CCM_OK) {
     free_ws(w);
     return rc;
@@ -541,8 +488,12 @@ int ccm_batch_matvec_dyn(ccm_batch_ws *w, const ccm_desc *as, const void *const 
     w->mats[t] = Mat{(const uint32_t *)d.payload, xs[t], ys[t], d.rows, d.cols, d.bits,
                      d.is_signed};
   }
-  plan_items(w->mats, w->table, &w->items);
-  if ((int64_t)w->items.size() > w->max_items) return CCM_E_NOMEM;
+  int64_t max_cols = 1;
+  for (const Mat &m : w->mats) max_cols = std::max(max_cols, m.cols);
+  int i = 0;
+  while (max_cols > (ccm::bt::kMaxCols >> (kShapes - 1 - i))) ++i;
+  const Shape &shape = w->shapes[i];
+  if (plan_items(w->mats, w->table, shape.grid, &w->items) > w->max_items) return CCM_E_NOMEM;
   ccm_batch_ws::Slot &sl = w->slots[w->next];
   w->next = (w->next + 1) % (int)w->slots.size();
   if (sl.used) {
@@ -557,11 +508,12 @@ int ccm_batch_matvec_dyn(ccm_batch_ws *w, const ccm_desc *as, const void *const 
     rc = hip_status(hipMemcpyAsync(sl.d_items, sl.h_items, sizeof(Item) * w->items.size(),
                                    hipMemcpyHostToDevice, s));
   if (rc != CCM_OK) return rc;
-  ccm::bt::k_counter_reset<<<1, 1, 0, s>>>(sl.d_counter);
+  const int rounds = shape.rounds(w->items.size());
+  ccm::bt::k_counter_reset<<<1, 1, 0, s>>>(sl.d_counter, rounds * shape.grid);
   rc = hip_status(hipGetLastError());
   if (rc != CCM_OK) return rc;
-  ccm::bt::k_batch<<<w->grid, ccm::bt::kThreads, 0, s>>>(sl.d_mats, sl.d_items,
-                                                        (int)w->items.size(), sl.d_counter);
+  ccm::bt::k_batch<<<shape.grid, ccm::bt::kThreads, shape.lds, s>>>(
+      sl.d_mats, sl.d_items, (int)w->items.size(), sl.d_counter, rounds, shape.bufs);
   rc = hip_status(hipGetLastError());
   if (rc != CCM_OK) return rc;
   rc = hip_status(hipEventRecord(sl.done, s));
