@@ -248,16 +248,107 @@ __global__ __launch_bounds__(256) void k_digit_rows_wide(const uint32_t *__restr
   }
 }
 
-// Digits of B^T (out row n holds column n of B), through an LDS tile of 128 k x
-// 64 n per limb and block: each lane first decodes one group (32 consecutive n
-// of one row k of B, read as the group's words), then 4 lanes per n gather
-// their 32 k each from the tile and write the 128 bytes of out's row n as
-// 16-byte stores.  cadd (may be null, else zero before the launch): cadd[n] +=
-// alpha times the sum of column n's values.
-constexpr int kCtK = 128, kCtN = 64, kCtPitch = kCtN + 4;  // tile pitch in bytes
+// cadd[n] += alpha (sum + live beta), from the sums of the four lanes of n
+__device__ __forceinline__ void commit_col(uint64_t sum, int kq, int64_t n, int64_t N, int64_t live,
+                                           uint64_t alpha, uint64_t beta,
+                                           int64_t *__restrict__ cadd) {
+  sum += (uint64_t)__shfl_xor((long long)sum, 1, 64);
+  sum += (uint64_t)__shfl_xor((long long)sum, 2, 64);
+  if (kq == 0 && n < N)
+    atomicAdd((unsigned long long *)&cadd[n],
+              (unsigned long long)(alpha * (sum + (uint64_t)live * beta)));
+}
 
-// The second half of both kernels: digit i of the block's tile to out, with
-// the sum of this lane's 32 digits.
+// Digits of B^T (out row n holds column n of B), through an LDS tile per limb of
+// 128 k x TN n (256, 128 or 64 by the number of limbs, 33 KB in all):
+//   * each lane decodes groups (32 consecutive n of one row k of B, read as the
+//     group's words): at 4 bits a row's 256 fields are a whole line, where 64 of
+//     them left each line to four blocks, on four XCDs;
+//   * a lane turns 4 n x 32 k of a limb around, four words at a time (eight byte
+//     permutes instead of sixteen byte reads), and writes two 16-byte chunks per
+//     n: lane kq of four takes the 16 k from 16 kq and from 64 + 16 kq, whose rows
+//     then lie 16 banks apart (the four lanes and their 16 n-quads fill the 64).
+// cadd (may be null, else zero before the launch): cadd[n] += alpha times the sum
+// of column n's values.
+// Bound by memory: packed words in, L bytes an element out.  8192 x 8192 at 4
+// bits: 27 us, 42 with tiles of 64 n read back by bytes.
+constexpr int kCtK = 128;
+// n of a tile; `wide`: as many as the LDS budget gives.
+constexpr int ct_cols(int limbs, bool wide) {
+  return !wide || limbs > 2 ? 64 : limbs == 2 ? 128 : 256;
+}
+
+template <int B, int TN>
+__global__ __launch_bounds__(256) void k_digit_cols(const uint32_t *__restrict__ w, uint64_t cap,
+                                                    int sgn, int64_t K, int64_t N, int64_t ldk,
+                                                    Limbs L, int8_t *__restrict__ out,
+                                                    uint64_t alpha, uint64_t beta,
+                                                    int64_t *__restrict__ cadd) {
+  constexpr int LB = (B + 7) / 8, kPitch = TN / 4 + 1;  // words
+  __shared__ uint32_t tile[LB][kCtK * kPitch];
+  const int64_t nb = (int64_t)blockIdx.x * TN, kb = (int64_t)blockIdx.y * kCtK;
+  constexpr int G = TN / 32;
+#pragma unroll 1
+  for (int r = 0; r < kCtK * G / 256; ++r) {
+    const int t = r * 256 + threadIdx.x;
+    const int kl = t / G, g = t % G;
+    const int64_t k = kb + kl, n0 = nb + 32 * g;
+    uint32_t o[LB][8];
+    if (k < K && n0 < N) {
+      group_digits<B>(w, cap, ((uint64_t)k * (uint64_t)N + (uint64_t)n0) * B, sgn,
+                      N - n0 < 32 ? (int)(N - n0) : 32, o);
+    } else {
+#pragma unroll
+      for (int i = 0; i < LB; ++i)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) o[i][q] = 0;
+    }
+#pragma unroll
+    for (int i = 0; i < LB; ++i)
+#pragma unroll
+      for (int q = 0; q < 8; ++q) tile[i][kl * kPitch + 8 * g + q] = o[i][q];
+  }
+  __syncthreads();
+  const int kq = threadIdx.x & 3, quad = (threadIdx.x >> 2) % (TN / 4);
+  const int i = (threadIdx.x >> 2) / (TN / 4);  // limb
+  const int64_t n = nb + 4 * quad;
+  if (i >= LB || n >= N) return;
+  int sum[4] = {0, 0, 0, 0};
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int k0 = 64 * h + 16 * kq;
+    uint32_t o[4][4];  // [n][four k]
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      uint32_t r[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) r[j] = tile[i][(k0 + 4 * q + j) * kPitch + quad];
+      o[0][q] = limb::bytes4<0>(r);
+      o[1][q] = limb::bytes4<1>(r);
+      o[2][q] = limb::bytes4<2>(r);
+      o[3][q] = limb::bytes4<3>(r);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      if (n + v < N)
+        *reinterpret_cast<uint4 *>(out + stacked_row(n + v, i, N, L) * ldk + kb + k0) =
+            make_uint4(o[v][0], o[v][1], o[v][2], o[v][3]);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) sum[v] = sum4(o[v][q], sum[v]);
+    }
+  }
+  if (!cadd) return;
+  const int64_t live = i == 0 ? (K - kb < kCtK ? K - kb : kCtK) : 0;
+#pragma unroll
+  for (int v = 0; v < 4; ++v)
+    commit_col((uint64_t)(int64_t)sum[v] << (8 * i), kq, n + v, N, live, alpha, beta, cadd);
+}
+
+// The tile of k_digit_cols_wide: 128 k x 64 n, pitch in bytes.
+constexpr int kCtN = 64, kCtPitch = kCtN + 4;
+
+// Digit i of the block's tile to out, a byte at a time, with the sum of this
+// lane's 32 digits.
 __device__ __forceinline__ int store_digit_cols(const uint8_t *tile, int64_t n, int nl, int kq,
                                                 int i, int64_t N, int64_t kb, int64_t ldk, Limbs L,
                                                 int8_t *__restrict__ out) {
@@ -277,61 +368,8 @@ __device__ __forceinline__ int store_digit_cols(const uint8_t *tile, int64_t n, 
   return t;
 }
 
-// cadd[n] += alpha (sum + live beta), from the sums of the four lanes of n
-__device__ __forceinline__ void commit_col(uint64_t sum, int kq, int64_t n, int64_t N, int64_t live,
-                                           uint64_t alpha, uint64_t beta,
-                                           int64_t *__restrict__ cadd) {
-  sum += (uint64_t)__shfl_xor((long long)sum, 1, 64);
-  sum += (uint64_t)__shfl_xor((long long)sum, 2, 64);
-  if (kq == 0 && n < N)
-    atomicAdd((unsigned long long *)&cadd[n],
-              (unsigned long long)(alpha * (sum + (uint64_t)live * beta)));
-}
-
-template <int B>
-__global__ __launch_bounds__(256) void k_digit_cols(const uint32_t *__restrict__ w, uint64_t cap,
-                                                    int sgn, int64_t K, int64_t N, int64_t ldk,
-                                                    Limbs L, int8_t *__restrict__ out,
-                                                    uint64_t alpha, uint64_t beta,
-                                                    int64_t *__restrict__ cadd) {
-  constexpr int LB = (B + 7) / 8;
-  __shared__ __align__(16) uint8_t tile[LB][kCtK * kCtPitch];
-  const int64_t nb = (int64_t)blockIdx.x * kCtN, kb = (int64_t)blockIdx.y * kCtK;
-  const int t = threadIdx.x;
-  {
-    const int kl = t >> 1, half = t & 1;
-    const int64_t k = kb + kl, n0 = nb + 32 * half;
-    uint32_t o[LB][8];
-    if (k < K && n0 < N) {
-      group_digits<B>(w, cap, ((uint64_t)k * (uint64_t)N + (uint64_t)n0) * B, sgn,
-                      N - n0 < 32 ? (int)(N - n0) : 32, o);
-    } else {
-#pragma unroll
-      for (int i = 0; i < LB; ++i)
-#pragma unroll
-        for (int q = 0; q < 8; ++q) o[i][q] = 0;
-    }
-#pragma unroll
-    for (int i = 0; i < LB; ++i) {
-      uint32_t *row = reinterpret_cast<uint32_t *>(tile[i] + kl * kCtPitch + 32 * half);
-#pragma unroll
-      for (int q = 0; q < 8; ++q) row[q] = o[i][q];
-    }
-  }
-  __syncthreads();
-  const int nl = t >> 2, kq = t & 3;
-  const int64_t n = nb + nl;
-  uint64_t sum = 0;
-  if (n < N) {
-#pragma unroll
-    for (int i = 0; i < LB; ++i)
-      sum += (uint64_t)(int64_t)store_digit_cols(tile[i], n, nl, kq, i, N, kb, ldk, L, out)
-             << (8 * i);
-  }
-  if (cadd) commit_col(sum, kq, n, N, K - kb < kCtK ? K - kb : kCtK, alpha, beta, cadd);
-}
-
-// As k_digit_cols for fields of 33..64 bits, one limb of the tile at a time.
+// As k_digit_cols for fields of 33..64 bits: a limb of the tile at a time, each
+// byte from its own field, four lanes to an n and 32 k.
 __global__ __launch_bounds__(256) void k_digit_cols_wide(const uint32_t *__restrict__ w, int bits,
                                                          int sgn, int64_t K, int64_t N,
                                                          int64_t ldk, Limbs L,
@@ -386,16 +424,27 @@ hipError_t launch_digit_cols(const uint32_t *w, int bits, int sgn, int64_t K, in
                              int64_t ldk, Limbs L, int8_t *out, uint64_t alpha, uint64_t beta,
                              int64_t *cadd, hipStream_t s) {
   const uint64_t cap = cap_words32((uint64_t)K * (uint64_t)N, bits);
-  const dim3 grid((unsigned)((N + kCtN - 1) / kCtN), (unsigned)(ldk / kCtK));
+  auto grid = [&](int tn) {
+    return dim3((unsigned)((N + tn - 1) / tn), (unsigned)(ldk / kCtK));
+  };
+  // Wide tiles where they still give every CU two blocks: in us 42 (64 n) against
+  // 27 (256) for 8192 x 8192 at 4 bits, but 6.8 against 9.1 (128) for 2000 x
+  // 1801 at 10 bits and 3.8 against 6.6 for 10001 x 33 at 6.
+  const int tw = ct_cols(limb::limbs_of(bits), true);
+  const bool wide = (N + tw - 1) / tw * (ldk / kCtK) >= 512;
   switch (bits) {
 #define CCM_DIGIT_COLS(b)                                                                     \
-  case b:                                                                                     \
-    k_digit_cols<b><<<grid, 256, 0, s>>>(w, cap, sgn, K, N, ldk, L, out, alpha, beta, cadd);  \
-    break;
+  case b: {                                                                                   \
+    constexpr int narrow_n = ct_cols((b + 7) / 8, false), wide_n = ct_cols((b + 7) / 8, true); \
+    auto k = wide ? k_digit_cols<b, wide_n> : k_digit_cols<b, narrow_n>;                      \
+    k<<<grid(wide ? wide_n : narrow_n), 256, 0, s>>>(w, cap, sgn, K, N, ldk, L, out, alpha,   \
+                                                     beta, cadd);                             \
+    break;                                                                                    \
+  }
     CCM_WIDTH_CASES_32(CCM_DIGIT_COLS)
 #undef CCM_DIGIT_COLS
     default:
-      k_digit_cols_wide<<<grid, 256, 0, s>>>(w, bits, sgn, K, N, ldk, L, out, alpha, beta, cadd);
+      k_digit_cols_wide<<<grid(kCtN), 256, 0, s>>>(w, bits, sgn, K, N, ldk, L, out, alpha, beta, cadd);
   }
   return hipGetLastError();
 }
