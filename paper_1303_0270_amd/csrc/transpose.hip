@@ -164,9 +164,30 @@ hipError_t launch_compress_cm(const void *dense, int dtype, int64_t rows, int64_
   return hipGetLastError();
 }
 
+hipError_t launch_matvec_t_small(const uint32_t *, int64_t, int64_t, int, int, const void *, int,
+                                 int64_t *, hipStream_t);
+
+// Where a lane per element is the faster way (matvec_small.hip): the row walk
+// below pays for its rings and for the fold of 32 sums a lane whatever the size.
+// In us, int32 and int64 x over 16 and 40 bits, at b = 4, 10, 24, 40, before and
+// with it:
+//   256 x 256: 13.5 10.8 17.4 24.4, 20.8 14.5 18.7 24.6; all 3.6.
+//   492 x 666: 13.1 11.2 17.6 24.5, 20.3 15.0 19.1 24.8; 3.8 to 4.0, 4.2 to 5.0.
+//   1400 x 1400: 14.3 12.5 19.1 26.9, 21.5 16.3 20.5 27.1; 7.2 to 9.5, 8.9 to 12.2.
+//   128 x 20000: 11.8 11.3 17.7 25.6, 19.0 15.1 19.1 25.9; 4.4 to 7.0, 4.9 to 7.7.
+// A block takes its rows 512 at a time, 1.5 us each: 2562 x 95 11 to 12 against 12
+// to 30 with int32 x, but 13 against 12 to 30 with int64; 4000 x 250 16 against 14
+// to 42; and 100 x 100000 is even.
+static bool small_matvec_t(int64_t rows, int64_t cols, int xdtype) {
+  if (rows > (xdtype == CCM_I32 ? 2560 : 1536)) return false;
+  return (uint64_t)rows * (uint64_t)cols <= (rows <= 512 ? 3ull << 20 : 1ull << 21);
+}
+
 hipError_t launch_matvec_t(const uint32_t *w, int64_t rows, int64_t cols, int bits, int sgn,
                            const void *x, int xdtype, int64_t *y, int64_t *part,
                            uint64_t part_words, hipStream_t s) {
+  if (small_matvec_t(rows, cols, xdtype))
+    return launch_matvec_t_small(w, rows, cols, bits, sgn, x, xdtype, y, s);
   if (bits <= 16)
     return mvt::launch_t_widths_1(w, rows, cols, bits, sgn, x, xdtype, y, part, part_words, s);
   if (bits <= 32)
