@@ -11,6 +11,7 @@
 // max|B| < 2^63) makes every partial sum exact.
 #include "ccm_internal.hpp"
 #include "gemm_limb.hpp"
+#include "mv_tile.hpp"
 #include "group_codec.hpp"
 
 namespace ccm {
@@ -269,7 +270,8 @@ __device__ __forceinline__ void commit_col(uint64_t sum, int kq, int64_t n, int6
 //     n: lane kq of four takes the 16 k from 16 kq and from 64 + 16 kq, whose rows
 //     then lie 16 banks apart (the four lanes and their 16 n-quads fill the 64).
 // cadd (may be null, else zero before the launch): cadd[n] += alpha times the sum
-// of column n's values.
+// of column n's values.  tiles > 0 (one digit): out in chunk tiles for `tiles`
+// blocks of 16 columns instead of rows (gemm_narrow.hpp).
 // Bound by memory: packed words in, L bytes an element out.  8192 x 8192 at 4
 // bits: 27 us, 42 with tiles of 64 n read back by bytes.
 constexpr int kCtK = 128;
@@ -283,7 +285,7 @@ __global__ __launch_bounds__(256) void k_digit_cols(const uint32_t *__restrict__
                                                     int sgn, int64_t K, int64_t N, int64_t ldk,
                                                     Limbs L, int8_t *__restrict__ out,
                                                     uint64_t alpha, uint64_t beta,
-                                                    int64_t *__restrict__ cadd) {
+                                                    int64_t *__restrict__ cadd, int tiles) {
   constexpr int LB = (B + 7) / 8, kPitch = TN / 4 + 1;  // words
   __shared__ uint32_t tile[LB][kCtK * kPitch];
   const int64_t nb = (int64_t)blockIdx.x * TN, kb = (int64_t)blockIdx.y * kCtK;
@@ -330,9 +332,11 @@ __global__ __launch_bounds__(256) void k_digit_cols(const uint32_t *__restrict__
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
+      const int64_t at = LB == 1 && tiles
+                             ? limb::chunk_tile(n + v, kb + k0, tiles)
+                             : stacked_row(n + v, i, N, L) * ldk + kb + k0;
       if (n + v < N)
-        *reinterpret_cast<uint4 *>(out + stacked_row(n + v, i, N, L) * ldk + kb + k0) =
-            make_uint4(o[v][0], o[v][1], o[v][2], o[v][3]);
+        *reinterpret_cast<uint4 *>(out + at) = make_uint4(o[v][0], o[v][1], o[v][2], o[v][3]);
 #pragma unroll
       for (int q = 0; q < 4; ++q) sum[v] = sum4(o[v][q], sum[v]);
     }
@@ -422,7 +426,7 @@ hipError_t launch_digit_rows(const uint32_t *w, int bits, int sgn, int64_t M, in
 
 hipError_t launch_digit_cols(const uint32_t *w, int bits, int sgn, int64_t K, int64_t N,
                              int64_t ldk, Limbs L, int8_t *out, uint64_t alpha, uint64_t beta,
-                             int64_t *cadd, hipStream_t s) {
+                             int64_t *cadd, int tiles, hipStream_t s) {
   const uint64_t cap = cap_words32((uint64_t)K * (uint64_t)N, bits);
   auto grid = [&](int tn) {
     return dim3((unsigned)((N + tn - 1) / tn), (unsigned)(ldk / kCtK));
@@ -438,7 +442,7 @@ hipError_t launch_digit_cols(const uint32_t *w, int bits, int sgn, int64_t K, in
     constexpr int narrow_n = ct_cols((b + 7) / 8, false), wide_n = ct_cols((b + 7) / 8, true); \
     auto k = wide ? k_digit_cols<b, wide_n> : k_digit_cols<b, narrow_n>;                      \
     k<<<grid(wide ? wide_n : narrow_n), 256, 0, s>>>(w, cap, sgn, K, N, ldk, L, out, alpha,   \
-                                                     beta, cadd);                             \
+                                                     beta, cadd, tiles);                      \
     break;                                                                                    \
   }
     CCM_WIDTH_CASES_32(CCM_DIGIT_COLS)
@@ -508,7 +512,8 @@ bool narrow_b(int abits, int bbits, int bsgn, int64_t N) {
 
 // The narrow-B product: digits of B^T, the partial sums of the parts of K.
 struct SkinnyLayout {
-  int nb;  // 32-column blocks (0: not for this product)
+  int nb;     // 32-column blocks (0: not for this product)
+  int waves;  // of a block of 16 rows (gemm_narrow.hpp; 0: gemm_skinny.hpp)
   int splits;
   int64_t ldk, kper;
   uint64_t part_at, total;
@@ -525,11 +530,28 @@ SkinnyLayout skinny_layout(int abits, int asgn, int bbits, int bsgn, int64_t M, 
   p.nb = N <= 32 ? 1 : N <= 64 || la > 2 ? 2 : 4;
   const int64_t groups = (N + 32 * p.nb - 1) / (32 * p.nb);
   p.ldk = padded_k(K);
+  const int64_t nk = p.ldk / limb::kBK;
+  int64_t rows = (M + limb::kSkRows - 1) / limb::kSkRows * groups;
+  int64_t slots = 4 * limb::sk_stage(abits, p.nb) <= 158 * 1024 ? 512 : 256;
   p.part_at = up256((uint64_t)N * (uint64_t)p.ldk);
+  // Up to 64 columns in blocks of 16 rows (gemm_narrow.hpp), if the digits of whole
+  // blocks of 16 columns fit the room.  us a plan, blocks of 128 rows / of 16, 17 x 6
+  // bits: 1000 x 1000 x 33 32 / 25, 3000 x 3000 x 33 37 / 28, 500 x 20000 x 33 49 /
+  // 32, 16000 x 4000 x 64 64 / 55, 10000 x 10001 x 33 83 / 81 (and without the sum of
+  // the parts); past 48 columns the digits of B weigh as much as a large A, read
+  // once per 16 rows: 10000 x 10001 x 64 86 / 89, 8192 x 8192 x 64 64 / 56.
+  const uint64_t tiled = up256((uint64_t)((N + 15) / 16 * 16) * (uint64_t)p.ldk);
+  const uint64_t abytes = (uint64_t)M * (uint64_t)K / 8 * (uint64_t)abits;
+  if ((N <= 48 || (N <= 64 && abytes <= 160u << 20)) && (!room || tiled <= room)) {
+    p.part_at = tiled;
+    rows = (M + 15) / 16;
+    p.waves = rows >= 512 ? 4 : 8;
+    slots = 2048 / p.waves;
+    const int64_t most = rows * (nk / p.waves);  // a step for every wave of a part
+    slots = slots < most ? slots : most;
+  }
   // parts of K until the blocks fill the chip once (two blocks per CU where
   // the LDS holds them)
-  const int64_t rows = (M + limb::kSkRows - 1) / limb::kSkRows * groups, nk = p.ldk / limb::kBK;
-  const int64_t slots = 4 * limb::sk_stage(abits, p.nb) <= 158 * 1024 ? 512 : 256;
   int64_t splits = rows < slots ? slots / rows : 1;
   splits = splits < nk ? splits : nk;
   const uint64_t one = 8u * (uint64_t)M * (uint64_t)N;
@@ -566,7 +588,7 @@ hipError_t launch_narrow(const SkinnyLayout &p, const uint32_t *aw, int abits, i
                          int out32, void *C, char *extra, RangeSink sink, hipStream_t s) {
   limb::SkinnyArgs a;
   hipError_t e = launch_digit_cols(bw, bbits, bsgn, K, N, p.ldk, Limbs{1, 1}, (int8_t *)extra, 0,
-                                   0, nullptr, s);
+                                   0, nullptr, p.waves ? (int)((N + 15) / 16) : 0, s);
   if (e != hipSuccess) return e;
   a.aw = aw;
   a.cap_bytes = 4u * cap_words32((uint64_t)M * (uint64_t)K, abits);
@@ -579,15 +601,24 @@ hipError_t launch_narrow(const SkinnyLayout &p, const uint32_t *aw, int abits, i
   a.kper = p.kper;
   a.splits = p.splits;
   a.part = (int64_t *)(extra + p.part_at);
-  a.alpha = limb::digit_offset(abits, asgn);
+  a.alpha = p.waves ? mt::tile_alpha(abits, asgn) : limb::digit_offset(abits, asgn);
   a.C = C;
   a.out32 = out32;
   a.sink = sink;
-  switch (limb::limbs_of(abits)) {
-    case 1: e = limb::launch_skinny_1(a, abits, p.nb, s); break;
-    case 2: e = limb::launch_skinny_2(a, abits, p.nb, s); break;
-    case 3: e = limb::launch_skinny_3(a, abits, p.nb, s); break;
-    default: e = limb::launch_skinny_4(a, abits, p.nb, s);
+  if (p.waves) {
+    switch (limb::limbs_of(abits)) {
+      case 1: e = limb::launch_narrow_1(a, abits, p.waves, s); break;
+      case 2: e = limb::launch_narrow_2(a, abits, p.waves, s); break;
+      case 3: e = limb::launch_narrow_3(a, abits, p.waves, s); break;
+      default: e = limb::launch_narrow_4(a, abits, p.waves, s);
+    }
+  } else {
+    switch (limb::limbs_of(abits)) {
+      case 1: e = limb::launch_skinny_1(a, abits, p.nb, s); break;
+      case 2: e = limb::launch_skinny_2(a, abits, p.nb, s); break;
+      case 3: e = limb::launch_skinny_3(a, abits, p.nb, s); break;
+      default: e = limb::launch_skinny_4(a, abits, p.nb, s);
+    }
   }
   if (e != hipSuccess || p.splits == 1) return e;
   const uint64_t mn = (uint64_t)M * (uint64_t)N;
@@ -610,7 +641,7 @@ hipError_t launch_limbs(const uint32_t *aw, int abits, int asgn, const uint32_t 
   hipError_t e = launch_digit_rows(aw, abits, asgn, M, K, p.ldk, p.A, a8, p.beta, radd, cadd, N,
                                    s);
   if (e != hipSuccess) return e;
-  e = launch_digit_cols(bw, bbits, bsgn, K, N, p.ldk, p.B, b8, p.alpha, p.beta, cadd, s);
+  e = launch_digit_cols(bw, bbits, bsgn, K, N, p.ldk, p.B, b8, p.alpha, p.beta, cadd, 0, s);
   if (e != hipSuccess) return e;
   const int64_t ar = limb_rows(M, p.A.n), br = limb_rows(N, p.B.n);
   for (int i0 = 0; i0 < p.A.n; i0 += p.A.chunk)

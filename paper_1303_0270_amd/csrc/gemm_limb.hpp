@@ -363,6 +363,17 @@ hipError_t launch_skinny_1(const SkinnyArgs &p, int abits, int nb, hipStream_t s
 hipError_t launch_skinny_2(const SkinnyArgs &p, int abits, int nb, hipStream_t s);
 hipError_t launch_skinny_3(const SkinnyArgs &p, int abits, int nb, hipStream_t s);
 hipError_t launch_skinny_4(const SkinnyArgs &p, int abits, int nb, hipStream_t s);
+// ... of at most 64 columns (gemm_narrow.hpp); the digits of B in chunk tiles:
+// byte offset of digits k .. k + 15 (k a multiple of 16) of column n, for `blocks`
+// blocks of 16 columns.  1 KB per K step, block and MFMA of the step (k / 16 % 2),
+// then 16 bytes per lane (16 (k / 32 % 4) + n % 16).
+__host__ __device__ inline int64_t chunk_tile(int64_t n, int64_t k, int blocks) {
+  return ((k / kBK * blocks + n / 16) * 2 + k / 16 % 2) * 1024 + (k / 32 % 4 * 16 + n % 16) * 16;
+}
+hipError_t launch_narrow_1(const SkinnyArgs &p, int abits, int waves, hipStream_t s);
+hipError_t launch_narrow_2(const SkinnyArgs &p, int abits, int waves, hipStream_t s);
+hipError_t launch_narrow_3(const SkinnyArgs &p, int abits, int waves, hipStream_t s);
+hipError_t launch_narrow_4(const SkinnyArgs &p, int abits, int waves, hipStream_t s);
 
 // One pass over a chunk of la limbs of A and lb of B (la, lb <= 3, or 4 with
 // at most 2 on the other side); OT int32 (out32) or int64.

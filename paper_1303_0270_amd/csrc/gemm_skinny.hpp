@@ -1,4 +1,5 @@
-// C = A B for a narrow B (a served request's product): A is read once, packed,
+// C = A B for a B of 65 to 256 columns, or 49 and more by a large A (narrower ones:
+// gemm_narrow.hpp; also those whose scratch has no room for it): A is read once, packed,
 // and its digits are made in registers on the way into the matrix cores.
 //
 // With few columns of C the product is bound by reading A, not by the

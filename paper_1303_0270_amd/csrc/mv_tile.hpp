@@ -58,7 +58,7 @@ __device__ __forceinline__ uint32_t top_flip(int bits, int sgn) {
   const uint32_t f = sgn ? (t == 8 ? 0u : 1u << (t - 1)) : (t == 8 ? 0x80u : 0u);
   return f * 0x01010101u;
 }
-__device__ __forceinline__ uint64_t tile_alpha(int bits, int sgn) {
+__host__ __device__ inline uint64_t tile_alpha(int bits, int sgn) {
   const int L = limb::limbs_of(bits), t = bits - 8 * (L - 1);
   uint64_t a = 0;
   for (int i = 0; i + 1 < L; ++i) a += 128ull << (8 * i);
@@ -67,12 +67,13 @@ __device__ __forceinline__ uint64_t tile_alpha(int bits, int sgn) {
   return a;
 }
 
-// Digits of 32 fields of B <= 32 bits from their aligned words.
-template <int B>
+// Digits of 32 fields of B <= 32 bits from their aligned words; SPREAD: in the
+// order of spread_of(B), otherwise as they follow each other.
+template <int B, bool SPREAD = true>
 __device__ __forceinline__ void tile_digits(const uint32_t *ww, uint32_t flip,
                                             uint32_t (&o)[(B + 7) / 8][8]) {
   constexpr int L = (B + 7) / 8;
-  if constexpr (B == 1 || B == 2 || B == 4) {
+  if constexpr (SPREAD && spread_of(B) > 1) {
     constexpr int S = 8 / B;
     constexpr uint32_t mask = B == 1 ? 0x01010101u : B == 2 ? 0x03030303u : 0x0f0f0f0fu;
 #pragma unroll
