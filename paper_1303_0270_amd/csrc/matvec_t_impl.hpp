@@ -126,6 +126,19 @@ __device__ __forceinline__ void wait_rows(int m) {
   }
 }
 
+// Widths whose groups lie a multiple of 16 words apart: the lanes' words, one of
+// every group at a time, share 4 LDS banks or fewer.  There a row's 16-byte
+// vectors are permuted on the way into LDS (vector v at swz(v), its own inverse)
+// and read back whole, 16 lanes from at least 8 places.  16384 x 8192, a word at a
+// time and so, us: b = 16 125 and 70 (int64 x 128 and 92), 32 449 and 102, 48 349
+// and 151, 64 451 and 198.  At b = 8 and 24 int32 x gained 1 to 3% and int64 x lost
+// 4 to 11%.
+template <int B>
+constexpr bool by_vectors() {
+  return B % 16 == 0;
+}
+__device__ __forceinline__ int swz(int v) { return v ^ ((v >> 4) & 15); }
+
 template <int B, bool SGN, typename XT>
 __global__ __launch_bounds__(64 * waves<B>()) void k_matvec_t(const uint32_t *__restrict__ w,
                                                        int64_t rows, int64_t cols,
@@ -166,7 +179,7 @@ __global__ __launch_bounds__(64 * waves<B>()) void k_matvec_t(const uint32_t *__
     uint4 *dst = mybuf + (size_t)buf * NL * 64;
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
-      int v = i * 64 + lane;
+      int v = by_vectors<B>() ? swz(i * 64 + lane) : i * 64 + lane;
       v = v < nvec ? v : nvec - 1;  // a fixed count per lane; extra copies repeat the last
       __builtin_amdgcn_global_load_lds((const void *)(src + v),
                                        (__attribute__((address_space(3))) void *)(dst + i * 64),
@@ -263,10 +276,36 @@ __global__ __launch_bounds__(64 * waves<B>()) void k_matvec_t(const uint32_t *__
       // (bit / 32) % 4 + b lane of the copy, at the row's bit offset
       const uint32_t *buf = (const uint32_t *)(mybuf + (size_t)cur * NL * 64);
       const uint32_t off = (uint32_t)bit & 31u;
-      const uint32_t *gw = buf + (((uint32_t)(bit >> 5)) & 3u) + lane * B;
+      const int first = (int)((uint32_t)(bit >> 5) & 3u);
       uint32_t wd[B + 1];
+      if constexpr (by_vectors<B>()) {
+        constexpr int NV = B / 4 + 1;
+        uint32_t q[4 * NV];
 #pragma unroll
-      for (int k = 0; k <= B; ++k) wd[k] = gw[k];
+        for (int j = 0; j < NV; ++j) {
+          const uint4 t = reinterpret_cast<const uint4 *>(buf)[swz(lane * (B / 4) + j)];
+          q[4 * j] = t.x;
+          q[4 * j + 1] = t.y;
+          q[4 * j + 2] = t.z;
+          q[4 * j + 3] = t.w;
+        }
+        auto take = [&](auto at) {
+#pragma unroll
+          for (int k = 0; k <= B; ++k) wd[k] = q[k + decltype(at)::value];
+        };
+        if (first == 0)  // the same for the wave
+          take(std::integral_constant<int, 0>{});
+        else if (first == 1)
+          take(std::integral_constant<int, 1>{});
+        else if (first == 2)
+          take(std::integral_constant<int, 2>{});
+        else
+          take(std::integral_constant<int, 3>{});
+      } else {
+        const uint32_t *gw = buf + first + lane * B;
+#pragma unroll
+        for (int k = 0; k <= B; ++k) wd[k] = gw[k];
+      }
       uint32_t al[B];
 #pragma unroll
       for (int k = 0; k < B; ++k) al[k] = __builtin_amdgcn_alignbit(wd[k + 1], wd[k], off);
