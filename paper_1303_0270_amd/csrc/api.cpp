@@ -607,7 +607,7 @@ static bool matmul_layout(const ccm_desc *a, const ccm_desc *b, MatmulPlan *p) {
   const uint64_t c = (p->out32 ? 4u : 8u) * (uint64_t)a->rows * (uint64_t)b->cols;
   p->c_bytes = (c + 255u) / 256u * 256u;
   uint64_t fast = ccm::matmul_fast_bytes(a->bits, a->is_signed, b->bits, b->is_signed, a->rows,
-                                         a->cols, b->cols, p->i8);
+                                         a->cols, b->cols, p->i8, p->out32);
   if (!p->i8 && fast > kMaxDigitBytes) fast = 0;
   p->total = p->c_bytes + fast;
   p->least = p->i8 ? p->total : p->c_bytes;

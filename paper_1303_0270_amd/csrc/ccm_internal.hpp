@@ -510,7 +510,7 @@ hipError_t launch_compress_cm(const void *dense, int dtype, int64_t rows, int64_
 // matrix cores, otherwise it runs in int64 on the vector units.  i8: both
 // operands' values fit int8 and K*max|A|*max|B| < 2^31.
 uint64_t matmul_fast_bytes(int abits, int asgn, int bbits, int bsgn, int64_t M, int64_t K,
-                           int64_t N, int i8);
+                           int64_t N, int i8, int out32);
 hipError_t launch_matmul(const uint32_t *aw, int abits, int asgn, const uint32_t *bw,
                          int bbits, int bsgn, int64_t M, int64_t K, int64_t N, int i8, int out32,
                          void *scratch, uint64_t c_bytes, uint64_t scratch_bytes, RangeSink sink,

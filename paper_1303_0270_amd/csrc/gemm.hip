@@ -707,9 +707,13 @@ static bool small_product(int abits, int bbits, int bsgn, int64_t M, int64_t K, 
 }
 
 uint64_t matmul_fast_bytes(int abits, int asgn, int bbits, int bsgn, int64_t M, int64_t K,
-                           int64_t N, int i8) {
+                           int64_t N, int i8, int out32) {
   const int64_t ldk = padded_k(K);
   if (small_product(abits, bbits, bsgn, M, K, N)) return 0;
+  // Six digits and a C that fits int32: outer products of signed operands (a field
+  // of b bits may hold no magnitude past 2^(b-2), so 17 by 17 bits can stay below
+  // 2^31) and products by a matrix of zeros.
+  if (out32 && limb::limbs_of(abits) + limb::limbs_of(bbits) >= 6) return 0;
   // int32 sums of K digit products, and the launches' grid limits
   if ((ldk >= (1 << 17) && !i8) || ldk / kCtK > 65535 || M > 0x7fffffffll ||
       (N + 63) / 64 > 0x7fffffffll)
@@ -725,7 +729,7 @@ hipError_t launch_matmul(const uint32_t *aw, int abits, int asgn, const uint32_t
                          int bbits, int bsgn, int64_t M, int64_t K, int64_t N, int i8, int out32,
                          void *scratch, uint64_t c_bytes, uint64_t scratch_bytes, RangeSink sink,
                          hipStream_t s) {
-  const uint64_t fast = matmul_fast_bytes(abits, asgn, bbits, bsgn, M, K, N, i8);
+  const uint64_t fast = matmul_fast_bytes(abits, asgn, bbits, bsgn, M, K, N, i8, out32);
   if (fast && scratch_bytes >= c_bytes && scratch_bytes - c_bytes >= fast) {
     const SkinnyLayout n = narrow_layout(abits, asgn, bbits, bsgn, M, K, N, i8);
     const bool aligned = (uintptr_t)aw % 16 == 0;  // 16-byte copies of the payload itself

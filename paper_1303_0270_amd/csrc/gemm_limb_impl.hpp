@@ -32,7 +32,7 @@ hipError_t launch_pass_la(const GemmArgs &p, int lb, int out32, hipStream_t s) {
       return out32 ? launch_one<1, 1, int32_t, true>(p, s) : launch_one<1, 1, int64_t, true>(p, s);
     }
   }
-  // six limbs or more: max|A| max|B| >= 2^32, so C is never int32
+  // Six limbs or more are never asked for an int32 C (matmul_fast_bytes).
 #define CCM_LB(n)                                                                \
   if (lb == n) {                                                                 \
     if constexpr (LA + n < 6) {                                                  \
