@@ -380,6 +380,11 @@ __device__ inline void block_range_commit(int64_t lo, int64_t hi, int flag, cons
 // Launchers (each returns the launch's hipError_t)
 // ---------------------------------------------------------------------------
 
+// HIP launches fewer than 2^32 threads in a dimension.
+inline bool launch_fits(uint64_t blocks, uint64_t threads) {
+  return blocks <= 0x7fffffffull && blocks * threads < (1ull << 32);
+}
+
 // Arms the slots (and, for passes the host waits for, their count of full
 // slots; full may be null).
 hipError_t launch_range_init(RangeSlot *slot, uint32_t *full, hipStream_t s);

@@ -25,7 +25,8 @@ __global__ __launch_bounds__(kThreads) void k_gemm_generic(
     int bbits, int bsgn, int64_t M, int64_t K, int64_t N, OT *__restrict__ C, RangeSink sink) {
   __shared__ ET As[kTK][kTM + 1];  // As[k][m]
   __shared__ ET Bs[kTK][kTN + 1];  // Bs[k][n]
-  const int64_t m0 = (int64_t)blockIdx.y * kTM, n0 = (int64_t)blockIdx.x * kTN;
+  const int64_t gx = (N + kTN - 1) / kTN;
+  const int64_t m0 = blockIdx.x / gx * kTM, n0 = blockIdx.x % gx * kTN;
   const int tid = threadIdx.x;
   const int tm = (tid / 16) * 4, tn = (tid % 16) * 4;
   int64_t acc[4][4];
@@ -83,7 +84,10 @@ template <typename ET>
 hipError_t launch_generic(const uint32_t *aw, int abits, int asgn, const uint32_t *bw,
                           int bbits, int bsgn, int64_t M, int64_t K, int64_t N, int out32,
                           void *scratch, RangeSink sink, hipStream_t s) {
-  dim3 grid((unsigned)((N + kTN - 1) / kTN), (unsigned)((M + kTM - 1) / kTM));
+  // in one dimension: a second one ends at 65535 blocks, 4.2 million rows
+  const uint64_t tiles = (uint64_t)((N + kTN - 1) / kTN) * (uint64_t)((M + kTM - 1) / kTM);
+  if (!launch_fits(tiles, kThreads)) return hipErrorInvalidValue;
+  const unsigned grid = (unsigned)tiles;
   if (out32)
     k_gemm_generic<ET, int32_t><<<grid, kThreads, 0, s>>>(aw, abits, asgn, bw, bbits, bsgn, M,
                                                           K, N, (int32_t *)scratch, sink);
@@ -565,6 +569,27 @@ SkinnyLayout skinny_layout(int abits, int asgn, int bbits, int bsgn, int64_t M, 
   return p;
 }
 
+// Whether the launches of the two ways fit HIP's limits.
+bool narrow_launches(const SkinnyLayout &p, int64_t M, int64_t N) {
+  const uint64_t rows = p.waves ? 16 : limb::kSkRows, threads = p.waves ? 64 * p.waves : 512;
+  return launch_fits(((uint64_t)M + rows - 1) / rows, threads) &&
+         launch_fits(((uint64_t)N + 63) / 64, 256);
+}
+
+// Blocks of a pass over la x lb digits.
+uint64_t limb_tiles(int la, int lb, int64_t M, int64_t N) {
+  const int64_t tm = limb::tile_rows(la), tn = limb::tile_cols(la, lb);
+  return (uint64_t)((M + tm - 1) / tm) * (uint64_t)((N + tn - 1) / tn);
+}
+
+bool limbs_launch(const LimbLayout &p, int64_t M, int64_t N) {
+  bool ok = launch_fits((uint64_t)M, 256) && launch_fits(((uint64_t)N + 63) / 64, 256);
+  for (int la : {p.A.n < p.A.chunk ? p.A.n : p.A.chunk, p.A.n % p.A.chunk})
+    for (int lb : {p.B.n < p.B.chunk ? p.B.n : p.B.chunk, p.B.n % p.B.chunk})
+      ok = ok && (!la || !lb || launch_fits(limb_tiles(la, lb, M, N), 512));
+  return ok;
+}
+
 // C = the sum over the parts, and C's range.
 template <typename OT>
 __global__ __launch_bounds__(256) void k_sum_parts(const int64_t *__restrict__ part, int splits,
@@ -714,15 +739,12 @@ uint64_t matmul_fast_bytes(int abits, int asgn, int bbits, int bsgn, int64_t M, 
   // of b bits may hold no magnitude past 2^(b-2), so 17 by 17 bits can stay below
   // 2^31) and products by a matrix of zeros.
   if (out32 && limb::limbs_of(abits) + limb::limbs_of(bbits) >= 6) return 0;
-  // int32 sums of K digit products, and the launches' grid limits
-  if ((ldk >= (1 << 17) && !i8) || ldk / kCtK > 65535 || M > 0x7fffffffll ||
-      (N + 63) / 64 > 0x7fffffffll)
-    return 0;
-  if (!i8) {
-    const SkinnyLayout n = narrow_layout(abits, asgn, bbits, bsgn, M, K, N, i8);
-    if (n.nb) return n.total;
-  }
-  return limb_layout(abits, asgn, bbits, bsgn, M, K, N).total;
+  if ((ldk >= (1 << 17) && !i8) || ldk / kCtK > 65535) return 0;  // int32 sums, grid rows
+  const LimbLayout p = limb_layout(abits, asgn, bbits, bsgn, M, K, N);
+  const SkinnyLayout n = narrow_layout(abits, asgn, bbits, bsgn, M, K, N, i8);
+  const bool narrow = n.nb && narrow_launches(n, M, N);
+  if (!i8 && n.nb) return narrow ? n.total : 0;
+  return narrow || limbs_launch(p, M, N) ? p.total : 0;
 }
 
 hipError_t launch_matmul(const uint32_t *aw, int abits, int asgn, const uint32_t *bw,
@@ -733,10 +755,11 @@ hipError_t launch_matmul(const uint32_t *aw, int abits, int asgn, const uint32_t
   if (fast && scratch_bytes >= c_bytes && scratch_bytes - c_bytes >= fast) {
     const SkinnyLayout n = narrow_layout(abits, asgn, bbits, bsgn, M, K, N, i8);
     const bool aligned = (uintptr_t)aw % 16 == 0;  // 16-byte copies of the payload itself
-    if (n.nb && aligned)
+    if (n.nb && aligned && narrow_launches(n, M, N))
       return launch_narrow(n, aw, abits, asgn, bw, bbits, bsgn, M, K, N, out32, scratch,
                            (char *)scratch + c_bytes, sink, s);
-    if (!n.nb || i8)  // otherwise the scratch is the narrow product's
+    // the scratch of a narrow product past int8 is that form's alone
+    if ((!n.nb || i8) && limbs_launch(limb_layout(abits, asgn, bbits, bsgn, M, K, N), M, N))
       return launch_limbs(aw, abits, asgn, bw, bbits, bsgn, M, K, N, out32, scratch,
                           (char *)scratch + c_bytes, sink, s);
   }

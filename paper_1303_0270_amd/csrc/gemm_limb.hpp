@@ -322,9 +322,14 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm_limb(GemmArgs p) {
   if (p.sink.slot) block_range_commit((int64_t)lo, (int64_t)hi, 0, p.sink);
 }
 
+// Rows and columns of C per block of a pass over la x lb limbs.
+constexpr int tile_rows(int la) { return la == 1 ? 256 : la == 2 ? 128 : 64; }
+constexpr int tile_cols(int la, int lb) { return lb == 1 ? 256 : lb == 2 || la == 3 ? 128 : 64; }
+
 template <int LA, int LB, int FM, int FN, int WGM, int WGN, typename OT, bool CORR>
 hipError_t launch_tile(const GemmArgs &p, hipStream_t s) {
   constexpr int BM = 32 * FM * WGM, BN = 32 * FN * WGN;
+  static_assert(BM / LA == tile_rows(LA) && BN / LB == tile_cols(LA, LB), "tile");
   constexpr size_t lds = 2u * (size_t)(BM + BN) * kBK;
   const int64_t ntile = ((p.N + BN / LB - 1) / (BN / LB)) * ((p.M + BM / LA - 1) / (BM / LA));
   if (ntile > 0x7fffffffll) return hipErrorInvalidValue;
