@@ -207,9 +207,9 @@ int ccm_matvec(const ccm_desc *a, const void *x, int32_t xdtype, int64_t *y, voi
  * K * max|A| * max|B| >= 2^63 (max|M| = max(|min|, |max|) from the headers;
  * an O(1) conservative bound), so every entry fits in int64.  Products run
  * on the int8 matrix cores with exact integer accumulation, operands wider
- * than a byte as several base-256 digits per value; K of 2^17 or more (unless
- * every value fits int8 and K * max|A| * max|B| < 2^31) goes through an exact
- * int64 path.
+ * than a byte as several base-256 digits per value; short sums, and K of 2^17
+ * or more (unless every value fits int8 and K * max|A| * max|B| < 2^31), go
+ * through an exact int64 path.
  *   scratch_bytes: device scratch the two calls take (dense C at 4 or 8 bytes
  *     per entry, the operands' digits with K padded to a multiple of 128, and
  *     8 bytes per row and column).

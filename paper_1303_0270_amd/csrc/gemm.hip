@@ -1,8 +1,8 @@
 // C = A B on SM-packed operands, exact, written densely into scratch with the
 // exact range of C (the max-reduction pass that fixes C's width).  Products
 // run on the matrix cores (gemm_limb.hpp) over operands decoded here; the
-// generic path below takes what that path cannot: K of 2^17 or more, and a
-// scratch that holds no more than C.
+// generic path below takes what that path cannot (K of 2^17 or more, and a
+// scratch that holds no more than C) and short sums (matmul_fast_bytes).
 //
 // Generic path (any widths): 64x64 output tiles per 256-lane block, K in
 // chunks of 32.  Each chunk of A (64x32) and B (32x64) is decoded from the
@@ -721,20 +721,63 @@ static SkinnyLayout narrow_layout(int abits, int asgn, int bbits, int bsgn, int6
   return skinny_layout(abits, asgn, bbits, bsgn, M, K, N, room);
 }
 
-// Products the one launch of the int64 path finishes before the digit kernels
-// and the GEMM would have run one after the other: few K chunks, one wave of
-// its 64 x 64 blocks.  us a product at 12 x 10 bits, int64 path / digits: 32^3
-// 36 / 47, 64^3 42 / 50, 128^3 51 / 51, 200^3 65 / 52.  A narrow B has one
-// kernel less to wait for: 6 x 4 bits 32^3 37 / 38, 64^3 43 / 41.
-static bool small_product(int abits, int bbits, int bsgn, int64_t M, int64_t K, int64_t N) {
-  return K <= 96 && M <= (1 << 20) && N <= (1 << 20) && M * N <= (1 << 20) &&
-         !narrow_b(abits, bbits, bsgn, N);
+// Operands that fit in 32 bits are staged as int32 by the int64 path (products
+// stay exact in int64); wider ones as int64.
+static bool staged32(int abits, int asgn, int bbits, int bsgn) {
+  return (abits < 32 || (abits == 32 && asgn)) && (bbits < 32 || (bbits == 32 && bsgn));
+}
+
+// Which way is the faster one: estimates of a plan's time in us, fitted to 3962
+// products of M up to 2^20, N up to 4096 and K up to 10000 at nine pairs of widths,
+// each timed both ways.  The int64 path walks K in chunks of 32, a block per 64 x
+// 64 outputs; digits cost their launches, a block per row of A, tiles that a thin
+// product leaves empty, and K padded to 128, so they lose where K is short (more
+// so the taller A is) and win past it: 12 x 12 bits, int64 path / digits, 10000 x
+// K x 10 at K = 97, 200, 1000 38 / 46, 53 / 49, 180 / 59; 10^5 x K x 10 at K = 200,
+// 1000 116 / 194, 452 / 261; 2^20 x 16 x 16 159 / 1606; 10000 x K x 4096 at K = 32,
+// 64, 128 115 / 165, 181 / 166, 322 / 169.  What the estimates choose takes at most
+// 1.1 times as long as the int64 path, and 1.05 times as long as the faster way but
+// for 58 of the products (up to 1.5 times).
+static double int64_us(bool staged, int64_t M, int64_t K, int64_t N, double c_us) {
+  const double tiles = (double)((M + kTM - 1) / kTM) * (double)((N + kTN - 1) / kTN);
+  const double past = tiles > 128 ? tiles - 128 : 0;
+  return 16 + (double)((K + kTK - 1) / kTK) * (staged ? 4.85 + 0.0068 * past : 7.6 + 0.0185 * past) +
+         0.6 * c_us;
+}
+
+static double narrow_us(const SkinnyLayout &p, int la, int64_t M, int64_t N) {
+  const double m = (double)M, steps = (double)(p.ldk / limb::kBK);
+  if (p.waves) {
+    const double nb = (double)((N + 15) / 16);
+    return 21.2 + 0.06 * steps +
+           m * (3.9e-5 + 7.9e-5 * nb + steps * la * (1.1e-5 + 1.57e-6 * nb));
+  }
+  const double nb = (double)((N + 31) / 32);
+  return 27.9 + 0.23 * steps +
+         m * (7.9e-5 + 3.6e-6 * (double)N + steps * la * (5.6e-6 + 6.7e-6 * nb));
+}
+
+static double limbs_us(const LimbLayout &p, int64_t M, int64_t N, double c_us) {
+  const double steps = (double)(p.ldk / limb::kBK);
+  double us = 21 + (double)M * (0.62 + 0.38 * p.A.n) * 1e-3 - c_us;
+  for (int i = 0; i < p.A.n; i += p.A.chunk)
+    for (int j = 0; j < p.B.n; j += p.B.chunk) {
+      const int la = p.A.n - i < p.A.chunk ? p.A.n - i : p.A.chunk;
+      const int lb = p.B.n - j < p.B.chunk ? p.B.n - j : p.B.chunk;
+      // a wave stores its part of the block's tile, less what lies past C
+      const bool tall = lb >= 3 && la < 3;
+      const double wm = limb::tile_rows(la) / (tall ? 4 : 2);
+      const double wn = limb::tile_cols(la, lb) / (tall ? 2 : 4);
+      const double store = 21. / 8192 * (M < wm ? M : wm) * wn * (0.4 + (N < wn ? 0.6 * N / wn : 0.6));
+      const double turns = (double)limb_tiles(la, lb, M, N) / 256;
+      us += (turns > 1 ? turns : 1) * (5.7 + store + 1.7 * steps) + 1.9 * c_us;  // C read and written
+    }
+  return us;
 }
 
 uint64_t matmul_fast_bytes(int abits, int asgn, int bbits, int bsgn, int64_t M, int64_t K,
                            int64_t N, int i8, int out32) {
   const int64_t ldk = padded_k(K);
-  if (small_product(abits, bbits, bsgn, M, K, N)) return 0;
   // Six digits and a C that fits int32: outer products of signed operands (a field
   // of b bits may hold no magnitude past 2^(b-2), so 17 by 17 bits can stay below
   // 2^31) and products by a matrix of zeros.
@@ -743,8 +786,15 @@ uint64_t matmul_fast_bytes(int abits, int asgn, int bbits, int bsgn, int64_t M, 
   const LimbLayout p = limb_layout(abits, asgn, bbits, bsgn, M, K, N);
   const SkinnyLayout n = narrow_layout(abits, asgn, bbits, bsgn, M, K, N, i8);
   const bool narrow = n.nb && narrow_launches(n, M, N);
-  if (!i8 && n.nb) return narrow ? n.total : 0;
-  return narrow || limbs_launch(p, M, N) ? p.total : 0;
+  if (i8) {
+    // one launch against three, for one wave of the int64 path's blocks
+    if (!n.nb && K <= 96 && M <= (1 << 20) && N <= (1 << 20) && M * N <= (1 << 20)) return 0;
+    return narrow || limbs_launch(p, M, N) ? p.total : 0;
+  }
+  const double c_us = (out32 ? 4. : 8.) * (double)M * (double)N / 5e6;  // C at 5 TB/s
+  const double other = int64_us(staged32(abits, asgn, bbits, bsgn), M, K, N, c_us);
+  if (n.nb) return narrow && narrow_us(n, p.A.n, M, N) <= other ? n.total : 0;
+  return limbs_launch(p, M, N) && limbs_us(p, M, N, c_us) <= other ? p.total : 0;
 }
 
 hipError_t launch_matmul(const uint32_t *aw, int abits, int asgn, const uint32_t *bw,
@@ -763,10 +813,7 @@ hipError_t launch_matmul(const uint32_t *aw, int abits, int asgn, const uint32_t
       return launch_limbs(aw, abits, asgn, bw, bbits, bsgn, M, K, N, out32, scratch,
                           (char *)scratch + c_bytes, sink, s);
   }
-  // Operands that fit in 32 bits are staged as int32 (products stay exact in
-  // int64); wider ones as int64.
-  const bool narrow = (abits < 32 || (abits == 32 && asgn)) && (bbits < 32 || (bbits == 32 && bsgn));
-  if (narrow)
+  if (staged32(abits, asgn, bbits, bsgn))
     return launch_generic<int32_t>(aw, abits, asgn, bw, bbits, bsgn, M, K, N, out32, scratch,
                                    sink, s);
   return launch_generic<int64_t>(aw, abits, asgn, bw, bbits, bsgn, M, K, N, out32, scratch,
