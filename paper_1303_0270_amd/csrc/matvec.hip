@@ -19,9 +19,10 @@ hipError_t launch_matvec_small(const uint32_t *, int64_t, int64_t, int, int, con
 // Where an element per lane is the faster way (matvec_small.hip).  Measured
 // against the kernels below, in us at b = 4, 10, 16, 24, 40 (int32 x over 31
 // bits unless noted):
-//   * up to 128 columns, any number of rows: 8192 x 128 8.9 9.0 4.5 5.0 6.7
-//     against 3.6; 300000 x 128 210 239 77 78 168 against 62 to 65; past it
-//     20 to 50% is lost at b >= 16 (100000 x 300 30, 31 against 47).
+//   * up to 128 columns, as many rows as a launch of a wave a row holds (2^26):
+//     8192 x 128 8.9 9.0 4.5 5.0 6.7 against 3.6; 300000 x 128 210 239 77 78 168
+//     against 62 to 65; past 128 columns 20 to 50% is lost at b >= 16 (100000 x
+//     300 30, 31 against 47).
 //   * up to 2^20 elements: 256 x 256 7.9 6.7 3.5 3.8 4.4 against 3.5, int64 x
 //     8.8 9.5 6.3 4.7 5.1 against 3.5; 1000 x 1003 5.1 6.1 3.9 4.5 4.9 against
 //     3.5.  Below b = 16 up to 1.5 * 2^20 (1200 x 1200 5.0 5.9 against 4.7, but
@@ -30,7 +31,7 @@ hipError_t launch_matvec_small(const uint32_t *, int64_t, int64_t, int, int, con
 //     at b > 16, up to 512 rows and 2^22 elements: 128 x 16384 at b = 24, 31, 40
 //     20 31 23 against 6.2, 300 x 10000 13 21 17 against 9 to 11.
 static bool small_matvec(int64_t rows, int64_t cols, int bits, int xdtype) {
-  if (cols <= 128) return rows <= 0x7fffffffll;
+  if (cols <= 128) return launch_fits(((uint64_t)rows + 3) / 4, 256);  // four rows a block
   const uint64_t n = (uint64_t)rows * (uint64_t)cols;  // below 2^63 in a valid descriptor
   if (cols <= 16384 && n <= (bits < 16 ? 3ull << 19 : 1ull << 20)) return true;
   return xdtype == CCM_I32 && bits > 16 && rows <= 512 && cols <= 32768 && n <= 1ull << 22;
