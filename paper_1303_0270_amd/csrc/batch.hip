@@ -57,19 +57,61 @@ struct Item {
   int32_t pad;
 };
 
-// Runtime-width rows (fields wider than 32 bits): one element per lane step.
-__device__ void item_rows_rt(const Mat &m, int row0, int nrows) {
+// x as it is, eight loads in flight per lane.
+__device__ __forceinline__ void stage_words(const int32_t *__restrict__ x, int cols, int32_t *xs) {
+  for (int c0 = threadIdx.x; c0 < cols; c0 += kThreads * 8) {
+    int32_t v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = x[c0 + u * kThreads < cols ? c0 + u * kThreads : cols - 1];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (c0 + u * kThreads < cols) xs[c0 + u * kThreads] = v[u];
+  }
+}
+
+// Rows of fields wider than 32 bits, at a runtime width: an element per lane, x
+// from LDS, two elements in flight (64 columns apart, or of two rows where a row has
+// no more than that).  Bound by the loads' latency.  us, x from memory and one
+// element at a time, and so, at 40 bits: 8 of 100000 x 16 252 and 142, 8 of 100000 x
+// 128 523 and 349, 4000 of 4 x 4000 424 and 162.
+__device__ void item_rows_rt(const Mat &m, int row0, int nrows, const int32_t *x) {
+  constexpr int kWaves = kThreads / 64;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int32_t *x = (const int32_t *)m.x;
-  for (int rr = wave; rr < nrows; rr += kThreads / 64) {
-    const int64_t r = row0 + rr;
-    uint64_t acc = 0;
-    for (int64_t c = lane; c < m.cols; c += 64) {
-      const int64_t a = value_at(m.w, (uint64_t)(r * m.cols + c), m.bits, m.sgn);
-      acc += (uint64_t)a * (uint64_t)(int64_t)x[c];
+  const int cols = (int)m.cols, left = 64 - m.bits;
+  const mt::global_ptr<uint32_t> w = mt::as_global(m.w);
+  const int dr = cols <= 64 ? kWaves : 0, dc = cols <= 64 ? 0 : 64;
+  for (int rr = wave; rr < nrows; rr += kWaves + dr) {
+    uint64_t acc[2] = {0, 0};
+    for (int c0 = lane; c0 - lane < cols; c0 += 64 + dc) {
+      uint32_t lo[2], mid[2], hi[2], s[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int c = c0 + u * dc < cols ? c0 + u * dc : cols - 1;
+        const int r = rr + u * dr < nrows ? rr + u * dr : nrows - 1;
+        const uint64_t bit =
+            ((uint64_t)(row0 + r) * (uint64_t)cols + (uint64_t)c) * (uint64_t)m.bits;
+        s[u] = (uint32_t)bit & 31u;
+        lo[u] = w[bit >> 5];
+        mid[u] = w[(bit >> 5) + 1];
+        hi[u] = w[(bit >> 5) + 2];
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        if (c0 + u * dc < cols) {
+          const uint64_t f = ((uint64_t)__builtin_amdgcn_alignbit(mid[u], lo[u], s[u]) |
+                              (uint64_t)__builtin_amdgcn_alignbit(hi[u], mid[u], s[u]) << 32)
+                             << left;
+          const uint64_t a = m.sgn ? (uint64_t)((int64_t)f >> left) : f >> left;
+          acc[u] += a * (uint64_t)(int64_t)x[c0 + u * dc];
+        }
+      }
     }
-    const int64_t tot = wave_sum((int64_t)acc);
-    if (lane == 0) m.y[r] = tot;
+    if (!dr) acc[0] += acc[1];
+    const int64_t tot = wave_sum((int64_t)acc[0]);
+    if (lane == 0) m.y[(int64_t)row0 + rr] = tot;
+    if (rr + dr >= nrows || !dr) continue;
+    const int64_t next = wave_sum((int64_t)acc[1]);
+    if (lane == 0) m.y[(int64_t)row0 + rr + dr] = next;
   }
 }
 
@@ -133,7 +175,10 @@ __global__ __launch_bounds__(kThreads) void k_batch(const Mat *__restrict__ mats
       for (int v = 0; v < kThreads / 64; ++v) xsum += s_sum[v];
       dispatch(m, item, xd, xsum, lds);
     } else {
-      item_rows_rt(m, item.row0, item.nrows);
+      int32_t *xs = reinterpret_cast<int32_t *>(xd);  // five digit rows hold more
+      stage_words((const int32_t *)m.x, (int)m.cols, xs);
+      __syncthreads();
+      item_rows_rt(m, item.row0, item.nrows, xs);
     }
     if (round < rounds) {
       it += gridDim.x;
@@ -157,8 +202,9 @@ __global__ __launch_bounds__(kThreads) void k_batch(const Mat *__restrict__ mats
 using ccm::bt::Item;
 using ccm::bt::Mat;
 
-// Launch shape of a batch whose widest matrix has `cols` columns: LDS for its
-// digit rows, and as many blocks as are resident with it.
+// Launch shape of a batch whose widest matrix has `cols` columns and whose fields
+// have the `widths` (bit b: b bits) among those up to 32: LDS for the digit rows of
+// x and the waves' buffers, and as many blocks as are resident with it.
 namespace {
 struct Shape {
   int lds = 0, bufs = 0, grid = 0;
@@ -248,8 +294,9 @@ int check_batch_descs(const ccm_desc *as, int32_t n) {
 // rows: below that, what an item costs besides its payload shows (2048 matrices
 // of 32..2048 squared, items of 128 and 512 rows: b = 1 211 and 140 us, b = 8
 // 482 and 466, but b = 24 1209 and 1225; 64 matrices, which fill the blocks
-// barely once, 36 and 38 us at b = 4, 47 and 80 at b = 16).  Returns the number
-// of items of tile_rows rows, which bounds the list.
+// barely once, 36 and 38 us at b = 4, 47 and 80 at b = 16).  Fields past 32 bits
+// are decoded one by one, next to which an item costs little: theirs stay within
+// 128 rows.  Returns the number of items of tile_rows rows, which bounds the list.
 int64_t plan_items(const std::vector<Mat> &mats, const TuneEntry *table, int blocks,
                 std::vector<Item> *items) {
   items->clear();
@@ -261,7 +308,9 @@ int64_t plan_items(const std::vector<Mat> &mats, const TuneEntry *table, int blo
     const Mat &d = mats[t];
     int64_t rows = table[d.bits].tile_rows;
     const int64_t limit = rows * most;
-    while (rows < limit && (uint64_t)rows * d.cols * d.bits < (64u << 10) * 8u) rows *= 2;
+    while (rows < limit && (uint64_t)rows * d.cols * d.bits < (64u << 10) * 8u &&
+           (d.bits <= 32 || rows <= 64))
+      rows *= 2;
     for (int64_t r = 0; r < d.rows; r += rows) {
       const int nr = (int)std::min<int64_t>(rows, d.rows - r);
       items->push_back(Item{(int32_t)t, (int32_t)r, nr, 0});
@@ -282,10 +331,11 @@ int64_t plan_items(const std::vector<Mat> &mats, const TuneEntry *table, int blo
 }
 
 constexpr int kShapes = 4;
-Shape launch_shape(int64_t cols, int bits) {
+Shape launch_shape(int64_t cols, uint64_t widths) {
   Shape p;
-  for (int b = 1; b <= bits && b <= 32; ++b)
-    p.bufs = std::max(p.bufs, (ccm::bt::kThreads / 64) * ccm::mt::unit_bytes(b));
+  for (int b = 1; b <= 32; ++b)
+    if (widths >> b & 1u)
+      p.bufs = std::max(p.bufs, (ccm::bt::kThreads / 64) * ccm::mt::unit_bytes(b));
   p.lds = p.bufs + ccm::mt::x_lds<int32_t>((int)cols);
   (void)hipFuncSetAttribute(reinterpret_cast<const void *>(ccm::bt::k_batch),
                             hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
@@ -362,7 +412,9 @@ int ccm_batch_create(const ccm_desc *as, int32_t n, int32_t xdtype, const char *
   }
   int64_t max_cols = 1;
   for (const Mat &m : b->mats) max_cols = std::max(max_cols, m.cols);
-  b->shape = launch_shape(max_cols, b->max_bits);
+  uint64_t widths = 0;
+  for (const Mat &m : b->mats) widths |= m.bits <= 32 ? 1ull << m.bits : 0u;
+  b->shape = launch_shape(max_cols, widths);
   plan_items(b->mats, table, b->shape.grid, &b->items);
   rc = hip_status(hipMalloc(&b->d_mats, sizeof(Mat) * n));
   if (rc == CCM_OK) rc = hip_status(hipMalloc(&b->d_items, sizeof(Item) * b->items.size()));
@@ -458,7 +510,7 @@ int ccm_batch_ws_create(int32_t max_mats, int64_t max_items, int32_t slots, cons
     if (rc == CCM_OK) rc = hip_status(hipEventCreateWithFlags(&sl.done, hipEventDisableTiming));
   }
   for (int i = 0; rc == CCM_OK && i < kShapes; ++i)
-    w->shapes[i] = launch_shape(ccm::bt::kMaxCols >> (kShapes - 1 - i), 32);
+    w->shapes[i] = launch_shape(ccm::bt::kMaxCols >> (kShapes - 1 - i), ~0ull);
   if (rc != CCM_OK) {
     free_ws(w);
     return rc;
