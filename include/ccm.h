@@ -288,9 +288,9 @@ int ccm_result_desc(const ccm_result *r, void *payload, ccm_desc *out);
  * builds a work list of (matrix, row block) items ordered by size and width,
  * with per-width item rows from a tuning table (JSON written by the project's
  * autotuner, {"widths": {"<b>": {"tile_rows": r}}}, other fields ignored; up
- * to four times as many in large batches of small items; NULL, an unreadable
- * path or a missing width uses built-in defaults), and copies it to device
- * memory the batch owns. */
+ * to four times as many in large batches of small items, down to a sixteenth
+ * in small ones of wide matrices; NULL, an unreadable path or a missing width
+ * uses built-in defaults), and copies it to device memory the batch owns. */
 typedef struct ccm_batch ccm_batch;
 
 int ccm_batch_create(const ccm_desc *as, int32_t n, int32_t xdtype, const char *tune_json,
@@ -324,7 +324,8 @@ int ccm_batch_ws_create(int32_t max_mats, int64_t max_items, int32_t slots,
 int ccm_batch_ws_destroy(ccm_batch_ws *w);
 
 /* y_t = A_t x_t for the n matrices given (x int32), planned on the host and
- * run as one persistent launch on `stream`.  CCM_E_NOMEM if n or the work
+ * run as one persistent launch on `stream` (matrices of a few long rows in a
+ * second one).  CCM_E_NOMEM if n or the work
  * list (at the table's item rows) exceeds the workspace.  Async (one
  * host-to-device table copy). */
 int ccm_batch_matvec_dyn(ccm_batch_ws *w, const ccm_desc *as, const void *const *xs,

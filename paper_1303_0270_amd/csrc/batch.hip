@@ -1,9 +1,11 @@
 // Batched matvec: y_t = A_t x_t for many SM-packed matrices of uneven shapes
-// and widths in one persistent kernel launch (optionally a captured HIP graph).
+// and widths in one persistent kernel launch (optionally a captured HIP graph;
+// matrices of a few long rows of wide fields in a second one, k_batch_few).
 //
 // Host planner (ccm_batch_create): every matrix is cut into items of
 // `tile_rows` rows (a per-width tuning table, JSON written by the autotuner, or
-// built-in defaults; more rows for narrow matrices of a large batch), the items
+// built-in defaults; more rows for narrow matrices of a large batch, fewer for
+// wide ones of a small batch), the items
 // sorted by size class, largest first, and by width within a class: the sizes
 // shrink towards the end, where the blocks have to finish together, and a block
 // still keeps running one width's code for most of its time.  (By width first,
@@ -34,6 +36,7 @@
 
 #include "ccm.h"
 #include "ccm_internal.hpp"
+#include "matvec_impl.hpp"
 #include "mv_tile.hpp"
 
 namespace ccm {
@@ -115,10 +118,18 @@ __device__ void item_rows_rt(const Mat &m, int row0, int nrows, const int32_t *x
   }
 }
 
+// 2^this waves share a tile in an item of so many rows: one tile or two leave no
+// wave without work (16 x 8000 at 24 bits: 26 us, 54 by one wave).
+__device__ __forceinline__ int share_of(int nrows) {
+  static_assert(kThreads == 256, "four waves");
+  return nrows <= mt::kTileRows ? 2 : nrows <= 2 * mt::kTileRows ? 1 : 0;
+}
+
+// parts: 16 sums per wave, for an item whose tiles are shared.
 __device__ __forceinline__ void dispatch(const Mat &m, const Item &it, const uint8_t *xd,
-                                         uint64_t xsum, uint8_t *bufs) {
+                                         uint64_t xsum, uint8_t *bufs, uint64_t *parts) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int ntile = (it.nrows + mt::kTileRows - 1) / mt::kTileRows;
+  const int64_t ntile = ((int64_t)it.nrows + mt::kTileRows - 1) / mt::kTileRows;
   const uint32_t flip = mt::top_flip(m.bits, m.sgn);
   const uint64_t add = mt::tile_alpha(m.bits, m.sgn) * xsum;
   const uint64_t cap = 4u * cap_words32((uint64_t)m.rows * (uint64_t)m.cols, m.bits);
@@ -127,7 +138,8 @@ __device__ __forceinline__ void dispatch(const Mat &m, const Item &it, const uin
   case b:                                                                                      \
     mt::tiles<b, int32_t>(m.w, cap, (int)m.cols, it.row0, (int64_t)it.row0 + it.nrows, wave,   \
                           kThreads / 64, ntile, flip, xd, add,                                 \
-                          bufs + wave * mt::Unit<b>::bytes, m.y);                              \
+                          bufs + wave * mt::Unit<b>::bytes, m.y, share_of(it.nrows),           \
+                          parts + wave * mt::kTileRows);                                       \
     return;
     CCM_WIDTH_CASES_32(CCM_B)
 #undef CCM_B
@@ -155,7 +167,7 @@ __global__ __launch_bounds__(kThreads) void k_batch(const Mat *__restrict__ mats
   extern __shared__ __align__(16) uint8_t lds[];
   uint8_t *xd = lds + buf_bytes;
   __shared__ int s_item[2];
-  __shared__ uint64_t s_sum[kThreads / 64];
+  __shared__ uint64_t s_sum[kThreads / 64], s_part[kThreads / 64 * mt::kTileRows];
   // The next item's index is requested when an item starts and read when it
   // ends, so the atomic's round trip overlaps the item's work.
   int next = 0;
@@ -173,7 +185,17 @@ __global__ __launch_bounds__(kThreads) void k_batch(const Mat *__restrict__ mats
       uint64_t xsum = 0;
 #pragma unroll
       for (int v = 0; v < kThreads / 64; ++v) xsum += s_sum[v];
-      dispatch(m, item, xd, xsum, lds);
+      dispatch(m, item, xd, xsum, lds, s_part);
+      if (const int share = share_of(item.nrows)) {
+        __syncthreads();
+        if ((int)threadIdx.x < item.nrows) {
+          const int tile = threadIdx.x / mt::kTileRows, row = threadIdx.x % mt::kTileRows;
+          uint64_t sum = mt::tile_alpha(m.bits, m.sgn) * xsum;
+          for (int v = 0; v < 1 << share; ++v)
+            sum += s_part[((tile << share) + v) * mt::kTileRows + row];
+          m.y[(int64_t)item.row0 + threadIdx.x] = (int64_t)sum;
+        }
+      }
     } else {
       int32_t *xs = reinterpret_cast<int32_t *>(xd);  // five digit rows hold more
       stage_words((const int32_t *)m.x, (int)m.cols, xs);
@@ -190,6 +212,67 @@ __global__ __launch_bounds__(kThreads) void k_batch(const Mat *__restrict__ mats
       it = __builtin_amdgcn_readfirstlane(s_item[round & 1]);
     }
   }
+}
+
+// Few long rows of wide fields: a tile of 16 rows decodes as much for one of them as
+// for sixteen.  A block takes a matrix, a wave a row at a time, a lane a group of 32
+// fields; x in LDS with a lane's 32 values on 36 words.  us, 4000 of 1 x 4000 and 4 x
+// 4000, in tiles and so: 24 bits 164 and 28, 168 and 44; 32 bits 217 and 30, 236 and
+// 63.  At 16 bits and below the tiles are no slower.
+constexpr int kFewRows = 8, kFewCols = 1024, kPitch = kGroup + 4;
+
+template <int B, bool SGN>
+__device__ __forceinline__ void few_rows(const Mat &m, const int32_t *xs) {
+  const int lane = threadIdx.x & 63, ng = (int)((m.cols + kGroup - 1) / kGroup);
+  const mt::global_ptr<uint32_t> w = mt::as_global(m.w);
+  for (int r = threadIdx.x >> 6; r < (int)m.rows; r += kThreads / 64) {
+    const uint64_t bit = (uint64_t)r * (uint64_t)m.cols * B;
+    const int sh = (int)(bit & 31u);
+    uint64_t acc = 0;
+    for (int j = lane; j < ng; j += 64) {
+      uint32_t ww[B + 1];
+#pragma unroll
+      for (int k = 0; k <= B; ++k) ww[k] = w[(bit >> 5) + (uint64_t)j * B + k];
+#pragma unroll
+      for (int k = 0; k < B; ++k) ww[k] = __builtin_amdgcn_alignbit(ww[k + 1], ww[k], sh);
+      acc += mv::group_dot_wide<B, SGN, int32_t>(ww, xs + j * kPitch);
+    }
+    const int64_t sum = wave_sum((int64_t)acc);
+    if (lane == 0) m.y[r] = sum;
+  }
+}
+
+__global__ __launch_bounds__(kThreads) void k_batch_few(const Mat *__restrict__ mats,
+                                                        const Item *__restrict__ items) {
+  __shared__ __align__(16) int32_t xs[kMaxCols / kGroup * kPitch];
+  const Mat m = mats[items[blockIdx.x].mat];
+  const int cols = (int)m.cols, padded = (cols + kGroup - 1) / kGroup * kGroup;
+  const mt::global_ptr<int32_t> x = mt::as_global((const int32_t *)m.x);
+  for (int c0 = threadIdx.x; c0 < padded; c0 += kThreads * 8) {
+    int32_t v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = x[c0 + u * kThreads < cols ? c0 + u * kThreads : cols - 1];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int c = c0 + u * kThreads;
+      if (c < padded) xs[(c >> 5) * kPitch + (c & 31)] = c < cols ? v[u] : 0;
+    }
+  }
+  __syncthreads();
+  switch (2 * m.bits + (m.sgn ? 1 : 0)) {
+#define CCM_FEW(b)                                          \
+  case 2 * b: few_rows<b, false>(m, xs); return;            \
+  case 2 * b + 1: few_rows<b, true>(m, xs); return;
+    CCM_FEW(17) CCM_FEW(18) CCM_FEW(19) CCM_FEW(20) CCM_FEW(21) CCM_FEW(22) CCM_FEW(23)
+    CCM_FEW(24) CCM_FEW(25) CCM_FEW(26) CCM_FEW(27) CCM_FEW(28) CCM_FEW(29) CCM_FEW(30)
+    CCM_FEW(31) CCM_FEW(32)
+#undef CCM_FEW
+    default: return;
+  }
+}
+
+inline bool takes_few(const Mat &m) {
+  return m.rows <= kFewRows && m.cols >= kFewCols && m.bits > 16 && m.bits <= 32;
 }
 
 }  // namespace bt
@@ -223,6 +306,7 @@ struct ccm_batch {
   Mat *d_mats = nullptr;
   Item *d_items = nullptr;
   int *d_counter = nullptr;
+  int few = 0;  // matrices that k_batch_few takes
   Shape shape;
   hipStream_t cap_stream = nullptr;
   hipGraph_t graph = nullptr;
@@ -296,17 +380,38 @@ int check_batch_descs(const ccm_desc *as, int32_t n) {
 // 482 and 466, but b = 24 1209 and 1225; 64 matrices, which fill the blocks
 // barely once, 36 and 38 us at b = 4, 47 and 80 at b = 16).  Fields past 32 bits
 // are decoded one by one, next to which an item costs little: theirs stay within
-// 128 rows.  Returns the number of items of tile_rows rows, which bounds the list.
-int64_t plan_items(const std::vector<Mat> &mats, const TuneEntry *table, int blocks,
+// 128 rows.  Where the list leaves blocks idle, items of more than kHalveCols
+// columns of wide fields, whose tiles a wave walks for long, are halved up to four
+// times (128 rows: to 16, which the waves of a block then share), as long as that
+// gives no block more than one item and the list has `room`: 1 of 300 x 8192 at 24
+// bits 94 and 26 us, 20 of 300 x 8000 96 and 42.
+struct Plan {
+  int64_t count;  // items of tile_rows rows: what a workspace has to hold
+  int few;        // matrices for k_batch_few, one item each at the end of the list
+};
+constexpr int64_t kHalveCols = 3000;
+
+Plan plan_items(const std::vector<Mat> &mats, const TuneEntry *table, int blocks, int64_t room,
                 std::vector<Item> *items) {
   items->clear();
-  int64_t count = 0;
-  for (const Mat &d : mats)
-    count += (d.rows + table[d.bits].tile_rows - 1) / table[d.bits].tile_rows;
-  const int most = count >= 4 * (int64_t)blocks ? 4 : 1;
+  auto rows_of = [&](const Mat &d, int halved) {
+    const int64_t rows = table[d.bits].tile_rows, tile = ccm::mt::kTileRows;
+    const bool fixed = halved == 0 || rows <= tile || d.cols <= kHalveCols || d.bits <= 16;
+    return fixed ? rows : std::max(rows >> halved, tile);
+  };
+  auto count_of = [&](int halved) {
+    int64_t n = 0;
+    for (const Mat &d : mats) n += (d.rows - 1) / rows_of(d, halved) + 1;
+    return n;
+  };
+  Plan plan{count_of(0), 0};
+  const int most = plan.count >= 4 * (int64_t)blocks ? 4 : 1;
+  int halved = 0;
+  while (halved < 4 && count_of(halved + 1) <= std::min<int64_t>(blocks, room)) ++halved;
   for (size_t t = 0; t < mats.size(); ++t) {
     const Mat &d = mats[t];
-    int64_t rows = table[d.bits].tile_rows;
+    if (ccm::bt::takes_few(d)) continue;
+    int64_t rows = rows_of(d, halved);
     const int64_t limit = rows * most;
     while (rows < limit && (uint64_t)rows * d.cols * d.bits < (64u << 10) * 8u &&
            (d.bits <= 32 || rows <= 64))
@@ -327,7 +432,28 @@ int64_t plan_items(const std::vector<Mat> &mats, const TuneEntry *table, int blo
     if (a.bits != c.bits) return a.bits < c.bits;
     return sa > sc;
   });
-  return count;
+  for (size_t t = 0; t < mats.size(); ++t)
+    if (ccm::bt::takes_few(mats[t])) {
+      items->push_back(Item{(int32_t)t, 0, (int32_t)mats[t].rows, 0});
+      ++plan.few;
+    }
+  return plan;
+}
+
+// The kernels of a planned list whose tables are on the device.
+hipError_t launch_items(const Shape &shape, const Mat *mats, const Item *items, int64_t n, int few,
+                        int *counter, hipStream_t s) {
+  const int64_t tiled = n - few;
+  if (tiled) {
+    const int rounds = shape.rounds((size_t)tiled);
+    ccm::bt::k_counter_reset<<<1, 1, 0, s>>>(counter, rounds * shape.grid);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    ccm::bt::k_batch<<<shape.grid, ccm::bt::kThreads, shape.lds, s>>>(
+        mats, items, (int)tiled, counter, rounds, shape.bufs);
+  }
+  if (few) ccm::bt::k_batch_few<<<few, ccm::bt::kThreads, 0, s>>>(mats, items + tiled);
+  return hipGetLastError();
 }
 
 constexpr int kShapes = 4;
@@ -415,7 +541,7 @@ int ccm_batch_create(const ccm_desc *as, int32_t n, int32_t xdtype, const char *
   uint64_t widths = 0;
   for (const Mat &m : b->mats) widths |= m.bits <= 32 ? 1ull << m.bits : 0u;
   b->shape = launch_shape(max_cols, widths);
-  plan_items(b->mats, table, b->shape.grid, &b->items);
+  b->few = plan_items(b->mats, table, b->shape.grid, INT64_MAX, &b->items).few;
   rc = hip_status(hipMalloc(&b->d_mats, sizeof(Mat) * n));
   if (rc == CCM_OK) rc = hip_status(hipMalloc(&b->d_items, sizeof(Item) * b->items.size()));
   if (rc == CCM_OK) rc = hip_status(hipMalloc(&b->d_counter, 256));
@@ -449,13 +575,8 @@ int ccm_batch_set_io(ccm_batch *b, const void *const *xs, int64_t *const *ys, vo
 }
 
 static int batch_enqueue(ccm_batch *b, hipStream_t s) {
-  const int rounds = b->shape.rounds(b->items.size());
-  ccm::bt::k_counter_reset<<<1, 1, 0, s>>>(b->d_counter, rounds * b->shape.grid);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return hip_status(e);
-  ccm::bt::k_batch<<<b->shape.grid, ccm::bt::kThreads, b->shape.lds, s>>>(
-      b->d_mats, b->d_items, (int)b->items.size(), b->d_counter, rounds, b->shape.bufs);
-  return hip_status(hipGetLastError());
+  return hip_status(launch_items(b->shape, b->d_mats, b->d_items, (int64_t)b->items.size(), b->few,
+                                 b->d_counter, s));
 }
 
 int ccm_batch_matvec(ccm_batch *b, int32_t use_graph, void *stream) {
@@ -545,7 +666,8 @@ int ccm_batch_matvec_dyn(ccm_batch_ws *w, const ccm_desc *as, const void *const 
   int i = 0;
   while (max_cols > (ccm::bt::kMaxCols >> (kShapes - 1 - i))) ++i;
   const Shape &shape = w->shapes[i];
-  if (plan_items(w->mats, w->table, shape.grid, &w->items) > w->max_items) return CCM_E_NOMEM;
+  const Plan plan = plan_items(w->mats, w->table, shape.grid, w->max_items, &w->items);
+  if (plan.count > w->max_items) return CCM_E_NOMEM;
   ccm_batch_ws::Slot &sl = w->slots[w->next];
   w->next = (w->next + 1) % (int)w->slots.size();
   if (sl.used) {
@@ -560,13 +682,8 @@ int ccm_batch_matvec_dyn(ccm_batch_ws *w, const ccm_desc *as, const void *const 
     rc = hip_status(hipMemcpyAsync(sl.d_items, sl.h_items, sizeof(Item) * w->items.size(),
                                    hipMemcpyHostToDevice, s));
   if (rc != CCM_OK) return rc;
-  const int rounds = shape.rounds(w->items.size());
-  ccm::bt::k_counter_reset<<<1, 1, 0, s>>>(sl.d_counter, rounds * shape.grid);
-  rc = hip_status(hipGetLastError());
-  if (rc != CCM_OK) return rc;
-  ccm::bt::k_batch<<<shape.grid, ccm::bt::kThreads, shape.lds, s>>>(
-      sl.d_mats, sl.d_items, (int)w->items.size(), sl.d_counter, rounds, shape.bufs);
-  rc = hip_status(hipGetLastError());
+  rc = hip_status(launch_items(shape, sl.d_mats, sl.d_items, (int64_t)w->items.size(), plan.few,
+                               sl.d_counter, s));
   if (rc != CCM_OK) return rc;
   rc = hip_status(hipEventRecord(sl.done, s));
   sl.used = (rc == CCM_OK);

@@ -199,8 +199,8 @@ constexpr int unit_bytes(int b) {
   }
 }
 
-// y of the tiles t0, t0 + tstep, ... < ntile (rows row0 + 16 t.., below row_end)
-// of one wave, over the staged columns of the matrix.
+// y of the tiles of one wave of `waves` (tile t: rows row0 + 16 t.., below row_end;
+// ntile of them, dealt in turn), over the staged columns of the matrix.
 //   * Rows are read through LDS (buf: a unit of the wave's own): lanes that own a
 //     group each would touch 64 lines with every load, and the waves of a CU
 //     evict each other's lines before the next load comes back to them (4096
@@ -210,15 +210,18 @@ constexpr int unit_bytes(int b) {
 //   * A unit's words go to registers at once, and the next unit's copies are in
 //     flight while they are decoded.  Two buffers in turn cost resident blocks:
 //     1516 us, one buffer 1452.  No barrier: the buffer is the wave's own.
+//   * 2^share waves can share a tile, its units dealt among them: each leaves its
+//     rows' sums in part (LDS, 16 of the wave's own) for the caller to add.
 // add: alpha times the sum of x.  w on a 16-byte boundary, of cap_bytes.
 template <int B, typename XT>
 __device__ __forceinline__ void tiles(const uint32_t *__restrict__ w, uint64_t cap_bytes,
-                                      int cols, int64_t row0, int64_t row_end, int64_t t0,
-                                      int64_t tstep, int64_t ntile, uint32_t flip,
+                                      int cols, int64_t row0, int64_t row_end, int wave,
+                                      int waves, int64_t ntile, uint32_t flip,
                                       const uint8_t *xd, uint64_t add, uint8_t *buf,
-                                      int64_t *__restrict__ y) {
+                                      int64_t *__restrict__ y, int share, uint64_t *part) {
   typedef Unit<B> U;
   constexpr int L = (B + 7) / 8, D = x_digits<XT>(), CH = U::chunks;
+  const int t0 = wave >> share, u0 = wave & ((1 << share) - 1);
   if (t0 >= ntile) return;
   // opaque: in a kernel that holds every width's code in a loop, what depends
   // on the lane alone would be computed for all of them before it (and spilled)
@@ -286,13 +289,21 @@ __device__ __forceinline__ void tiles(const uint32_t *__restrict__ w, uint64_t c
 #pragma unroll
     for (int i = 0; i < L; ++i) acc[i] = v4i{0, 0, 0, 0};
     const int64_t r = row0 + t * kTileRows + 4 * h + n;
-    if (n < 4 && r < row_end) y[r] = (int64_t)(mine + add);
+    if (share) {
+      if (n < 4) part[4 * h + n] = mine;
+    } else if (n < 4 && r < row_end) {
+      y[r] = (int64_t)(mine + add);
+    }
   };
 
   int64_t t = t0, ts = t0;  // tile being decoded, tile being copied
-  int u = 0;
+  int u = u0;
+  if (u0 >= nunit) {  // a narrow tile shared by more waves than it has units
+    if (n < 4) part[4 * h + n] = 0;
+    return;
+  }
   enter(ts);
-  stage(0);
+  stage(u0);
   // this lane's row of tile t: its funnel shift and its first word in a unit
   int sh = 0, word = 0;
   auto place = [&]() {
@@ -310,10 +321,10 @@ __device__ __forceinline__ void tiles(const uint32_t *__restrict__ w, uint64_t c
 #pragma unroll
       for (int k = 0; k <= B; ++k) ww[q][k] = aw[word + q * 4 * B + k];
     // the next unit's copies, while this one is decoded
-    int un = u + 1;
-    if (un == nunit) {
-      un = 0;
-      ts += tstep;
+    int un = u + (1 << share);
+    if (un >= nunit) {
+      un = u0;
+      ts += waves >> share;
       if (ts < ntile) enter(ts);
     }
     const bool more = ts < ntile;
@@ -338,7 +349,7 @@ __device__ __forceinline__ void tiles(const uint32_t *__restrict__ w, uint64_t c
         }
       }
     }
-    if (un == 0) finish(t);
+    if (un == u0) finish(t);
     if (!more) break;
     if (ts != t) {
       t = ts;
