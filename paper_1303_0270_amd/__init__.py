@@ -408,21 +408,33 @@ def matmul_scratch_least(a: CMatrix, b: CMatrix) -> int:
 
 def matmul_plan(a: CMatrix, b: CMatrix, scratch: torch.Tensor | None = None, stream=None):
     """Range pass of C = A B: computes C into scratch and returns (C, scratch), C
-    allocated at its final width but not yet packed."""
+    allocated at its final width but not yet packed.  A scratch of
+    matmul_scratch_least bytes or more is used as it is; without one the full
+    size is allocated, or the least where memory does not hold that and C."""
     _row_major(a, "matmul")
     _row_major(b, "matmul")
     if a.cols != b.rows:
         raise CcmError(E_SHAPE, "matmul")
-    need = matmul_scratch_bytes(a, b)
-    if need == 0:
-        # invalid descriptors or the overflow bound: let the plan report which
-        need = 8
-    if scratch is None or scratch.numel() < need:
-        scratch = torch.empty(need, dtype=torch.uint8, device=a.payload.device)
-    d = Desc()
-    check(lib.ccm_matmul_plan(ctypes.byref(a.desc), ctypes.byref(b.desc), ctypes.byref(d),
-                              _ptr(scratch), scratch.numel(), _stream(stream)), "ccm_matmul_plan")
-    return CMatrix(d, device=a.payload.device), scratch
+    dev = a.payload.device
+
+    def plan(scratch):
+        d = Desc()
+        check(lib.ccm_matmul_plan(ctypes.byref(a.desc), ctypes.byref(b.desc), ctypes.byref(d),
+                                  _ptr(scratch), scratch.numel(), _stream(stream)),
+              "ccm_matmul_plan")
+        return CMatrix(d, device=dev), scratch
+
+    # 8 for 0: invalid descriptors or the overflow bound; the plan reports which
+    if scratch is not None and scratch.numel() >= (matmul_scratch_least(a, b) or 8):
+        return plan(scratch)
+    need = matmul_scratch_bytes(a, b) or 8
+    try:
+        return plan(torch.empty(need, dtype=torch.uint8, device=dev))
+    except torch.cuda.OutOfMemoryError:
+        least = matmul_scratch_least(a, b) or 8
+        if least == need:
+            raise
+    return plan(torch.empty(least, dtype=torch.uint8, device=dev))
 
 
 def matmul_pack(a: CMatrix, b: CMatrix, c: CMatrix, scratch: torch.Tensor, stream=None):
@@ -513,7 +525,7 @@ def matmul_capacity(a: CMatrix, b: CMatrix) -> int:
 def matmul_async(a: CMatrix, b: CMatrix, scratch: torch.Tensor | None = None,
                  ws: torch.Tensor | None = None, payload: torch.Tensor | None = None,
                  host: torch.Tensor | None = None, stream=None) -> Pending:
-    """C = A B with no host wait (ccm_matmul_async)."""
+    """C = A B with no host wait (ccm_matmul_async).  scratch: as in matmul_plan."""
     _row_major(a, "matmul")
     _row_major(b, "matmul")
     if a.cols != b.rows:
@@ -523,10 +535,13 @@ def matmul_async(a: CMatrix, b: CMatrix, scratch: torch.Tensor | None = None,
     if cap == 0 or need == 0:
         raise CcmError(E_OVERFLOW, "matmul: operands past the overflow bound")
     dev = a.payload.device
-    if scratch is None or scratch.numel() < need:
-        scratch = torch.empty(need, dtype=torch.uint8, device=dev)
     if payload is None or payload.numel() < cap:
         payload = torch.empty(cap, dtype=torch.uint8, device=dev)
+    if scratch is None or scratch.numel() < matmul_scratch_least(a, b):
+        try:
+            scratch = torch.empty(need, dtype=torch.uint8, device=dev)
+        except torch.cuda.OutOfMemoryError:
+            scratch = torch.empty(matmul_scratch_least(a, b), dtype=torch.uint8, device=dev)
     ws = async_ws(dev) if ws is None else ws
     check(lib.ccm_matmul_async(ctypes.byref(a.desc), ctypes.byref(b.desc), _ptr(payload),
                                payload.numel(), _ptr(scratch), scratch.numel(), _ptr(ws),
