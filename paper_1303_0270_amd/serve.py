@@ -5,8 +5,8 @@ over time.  The loop runs continuous batching on a few HIP streams:
 
 * admission: a request is admitted when a slot is free (at most `max_inflight`
   requests admitted and not finished) and its memory footprint (x and y, or B,
-  the result at its bound width and the matmul scratch) fits in the arena left
-  after the pool;
+  the result at its bound width and the least matmul scratch) fits in the arena
+  left after the pool;
 * every admitted matvec not yet launched goes into the next batched launch
   (one persistent kernel over all of them, ccm_batch_matvec_dyn) on the next
   free stream -- matrices wider than the batched kernel's x staging take the
@@ -27,7 +27,8 @@ over time.  The loop runs continuous batching on a few HIP streams:
   passes of the loop, so a host-side stall shows in the statistics;
 * the loop allocates no device memory: every result buffer (y of each
   matvec, the payload and workspace of each matmul) and one matmul scratch
-  per stream are carved out of a few tensors before the first request, so
+  per stream (the full size as far as the streams' shares of the arena go, the
+  least otherwise) are carved out of a few tensors before the first request, so
   that no block the caching allocator does not hold yet can mean a hipMalloc
   inside the loop (a run that still allocated there once showed a 6 ms
   stall of the loop at 95 % load; its cause was not isolated).
@@ -130,7 +131,9 @@ class Server:
         views of one int64 tensor for the matvec results, of one byte tensor
         (256-byte aligned slices) for the matmul payloads and workspaces, and
         one scratch per stream (a stream runs its matmuls in order, so each
-        reuses it).  Returns the per-stream scratch list."""
+        reuses it): what the largest product takes, but no more than a stream's
+        share of the arena unless its least is.  Returns the per-stream scratch
+        list."""
         dev = torch.device("cuda")
         mv = [r for r in reqs if r.kind == "mv"]
         mm = [r for r in reqs if r.kind != "mv"]
@@ -144,7 +147,9 @@ class Server:
             return (n + 255) // 256 * 256
         wsb = int(lib.ccm_async_ws_bytes())
         caps = [matmul_capacity(self.pool[r.mat], r.b) for r in mm]
-        need = max([matmul_scratch_bytes(self.pool[r.mat], r.b) for r in mm], default=0)
+        full = max([matmul_scratch_bytes(self.pool[r.mat], r.b) for r in mm], default=0)
+        least = max([matmul_scratch_least(self.pool[r.mat], r.b) for r in mm], default=0)
+        need = max(least, min(full, self.arena // len(self.streams)))
         blob = torch.empty(max(1, sum(up(c) + up(wsb) for c in caps)), dtype=torch.uint8,
                            device=dev)
         off = 0
