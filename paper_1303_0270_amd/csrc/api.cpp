@@ -1272,15 +1272,18 @@ int ccm_vlb_compress_plan(const void *dense, int32_t dtype, int64_t rows, int64_
   if (rc != CCM_OK) return rc;
   CCM_HIP(ccm::launch_vlb_stats(dense, dtype, rows, cols, grp, sink, s));
   ccm::RangeHost r;
-  // the sums it writes beside the range are read by kernels that follow it
+  // The sums it writes beside the range are read by kernels that follow it; a call
+  // that ends here waits for them (the record may be there before the last store).
   rc = read_range(c, s, false, &r);
   if (rc != CCM_OK) return rc;
   const int64_t lo = r.vmin, hi = r.vmax;
   int32_t bmax = 0, k = 0;
   vlb_widths(lo, hi, &bmax, &k);
   // group offsets within a row are 32-bit
-  if ((unsigned __int128)cols * (unsigned __int128)(k + bmax) >= ((unsigned __int128)1 << 32))
+  if ((unsigned __int128)cols * (unsigned __int128)(k + bmax) >= ((unsigned __int128)1 << 32)) {
+    CCM_HIP(hipStreamSynchronize(s));
     return CCM_E_UNSUPPORTED;
+  }
   rc = next_sink(c, s, &sink);
   if (rc != CCM_OK) return rc;
   CCM_HIP(ccm::launch_vlb_scan(rows, cols, k, lo < 0 ? 1 : 0, grp, row_bit, sink, s));
