@@ -136,10 +136,9 @@ __device__ __forceinline__ void dispatch(const Mat &m, const Item &it, const uin
   switch (m.bits) {
 #define CCM_B(b)                                                                               \
   case b:                                                                                      \
-    mt::tiles<b, int32_t>(m.w, cap, (int)m.cols, it.row0, (int64_t)it.row0 + it.nrows, wave,   \
-                          kThreads / 64, ntile, flip, xd, add,                                 \
-                          bufs + wave * mt::Unit<b>::bytes, m.y, share_of(it.nrows),           \
-                          parts + wave * mt::kTileRows);                                       \
+    mt::tiles<b>(m.w, cap, (int)m.cols, it.row0, (int64_t)it.row0 + it.nrows, wave,            \
+                 kThreads / 64, ntile, flip, xd, add, bufs + wave * mt::Unit<b>::bytes, m.y,   \
+                 share_of(it.nrows), parts + wave * mt::kTileRows);                            \
     return;
     CCM_WIDTH_CASES_32(CCM_B)
 #undef CCM_B
@@ -177,8 +176,8 @@ __global__ __launch_bounds__(kThreads) void k_batch(const Mat *__restrict__ mats
     const Item item = items[it];
     const Mat m = mats[item.mat];
     if (m.bits <= 32 && (uintptr_t)m.w % 16 == 0) {
-      const uint64_t part = mt::stage_x<int32_t, kThreads>((const int32_t *)m.x, (int)m.cols,
-                                                           mt::spread_of(m.bits), xd);
+      const uint64_t part = mt::stage_x<kThreads>((const int32_t *)m.x, (int)m.cols,
+                                                  mt::spread_of(m.bits), xd);
       const uint64_t ws = (uint64_t)wave_sum((int64_t)part);
       if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = ws;
       __syncthreads();
@@ -462,7 +461,7 @@ Shape launch_shape(int64_t cols, uint64_t widths) {
   for (int b = 1; b <= 32; ++b)
     if (widths >> b & 1u)
       p.bufs = std::max(p.bufs, (ccm::bt::kThreads / 64) * ccm::mt::unit_bytes(b));
-  p.lds = p.bufs + ccm::mt::x_lds<int32_t>((int)cols);
+  p.lds = p.bufs + ccm::mt::x_lds((int)cols);
   (void)hipFuncSetAttribute(reinterpret_cast<const void *>(ccm::bt::k_batch),
                             hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
   int occ = 0, dev = 0, cus = 0;

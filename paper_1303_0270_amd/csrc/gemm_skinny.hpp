@@ -226,7 +226,9 @@ hipError_t launch_skinny_one(const SkinnyArgs &p, hipStream_t s) {
 
 template <int B>
 hipError_t launch_skinny_b(const SkinnyArgs &p, int nb, hipStream_t s) {
-  if (nb == 1) return launch_skinny_one<B, 1>(p, s);
+  if constexpr (B <= 8) {  // up to 32 columns: int8 pairs with no room for chunk tiles
+    if (nb == 1) return launch_skinny_one<B, 1>(p, s);
+  }
   if (nb == 2) return launch_skinny_one<B, 2>(p, s);
   if constexpr (B <= 16) {
     if (nb == 4) return launch_skinny_one<B, 4>(p, s);

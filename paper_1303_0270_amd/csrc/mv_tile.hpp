@@ -10,8 +10,8 @@
 //   * A field's digits are those of the products on matrix cores
 //     (gemm_limb.hpp), signed fields as unsigned ones with the top bit flipped:
 //     a = alpha + sum_i d_i 256^i, d_i in [-128, 127], L = ceil(b / 8) digits.
-//   * x is staged in LDS as D digit rows (D = 4 for int32 x, 8 for int64): lower
-//     digits byte - 128, the top one the signed top byte, and a row of ones:
+//   * x (int32) is staged in LDS as D = 4 digit rows: lower digits byte - 128, the
+//     top one the signed top byte, and a row of ones:
 //     x_k = X0 + sum_n e_n(k) 256^n with X0 = 128 sum_{n < D-1} 256^n.  Past the
 //     last column every row is zero, whatever the fields read there.
 //   * v_mfma_i32_16x16x64_i8 multiplies 16 rows of A by these D + 1 columns (of
@@ -112,18 +112,11 @@ __device__ __forceinline__ void tile_digits(const uint32_t *ww, uint32_t flip,
 __host__ __device__ constexpr int x_pitch(int cols) {
   return (cols + kStep - 1) / kStep * kStep + 16;
 }
-template <typename XT>
-constexpr int x_digits() {
-  return (int)sizeof(XT);
-}
-template <typename XT>
-constexpr int x_lds(int cols) {
-  return (x_digits<XT>() + 1) * x_pitch(cols);
-}
-template <typename XT>
+constexpr int kXDigits = 4;
+constexpr int x_lds(int cols) { return (kXDigits + 1) * x_pitch(cols); }
 constexpr uint64_t x_offset() {
   uint64_t a = 0;
-  for (int n = 0; n + 1 < x_digits<XT>(); ++n) a += 128ull << (8 * n);
+  for (int n = 0; n + 1 < kXDigits; ++n) a += 128ull << (8 * n);
   return a;
 }
 
@@ -131,15 +124,15 @@ constexpr uint64_t x_offset() {
 // this thread's share of their sum (mod 2^64).  A thread makes one word (four
 // columns) of every digit row at a time, `UNR` of them with their loads in
 // flight together.
-template <typename XT, int NT>
-__device__ __forceinline__ uint64_t stage_x(const XT *__restrict__ xp, int cols, int spread,
+template <int NT>
+__device__ __forceinline__ uint64_t stage_x(const int32_t *__restrict__ xp, int cols, int spread,
                                             uint8_t *lds) {
-  constexpr int D = x_digits<XT>(), UNR = 2;
-  const global_ptr<XT> x = as_global(xp);
+  constexpr int D = kXDigits, UNR = 2;
+  const global_ptr<int32_t> x = as_global(xp);
   const int pitch = x_pitch(cols), nw = (pitch - 16) / 4;
   uint64_t sum = 0;
   for (int t0 = threadIdx.x; t0 < nw; t0 += NT * UNR) {
-    XT v[UNR][4];
+    int32_t v[UNR][4];
     uint32_t ones[UNR];
 #pragma unroll
     for (int u = 0; u < UNR; ++u) {
@@ -158,16 +151,14 @@ __device__ __forceinline__ uint64_t stage_x(const XT *__restrict__ xp, int cols,
       const int t = t0 + u * NT;
       if (t >= nw) break;
       const uint32_t live = ones[u] * 0xffu;
-      uint32_t lo[4], hi[4];
+      uint32_t b[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        lo[i] = (uint32_t)v[u][i];
-        hi[i] = (uint32_t)((uint64_t)(int64_t)v[u][i] >> 32);
+        b[i] = (uint32_t)v[u][i];
         if (ones[u] >> (8 * i) & 1u) sum += (uint64_t)(int64_t)v[u][i];
       }
-      uint32_t w[8] = {limb::bytes4<0>(lo), limb::bytes4<1>(lo), limb::bytes4<2>(lo),
-                       limb::bytes4<3>(lo), limb::bytes4<0>(hi), limb::bytes4<1>(hi),
-                       limb::bytes4<2>(hi), limb::bytes4<3>(hi)};
+      const uint32_t w[D] = {limb::bytes4<0>(b), limb::bytes4<1>(b), limb::bytes4<2>(b),
+                             limb::bytes4<3>(b)};
 #pragma unroll
       for (int n = 0; n < D; ++n)
         *reinterpret_cast<uint32_t *>(lds + n * pitch + 4 * t) =
@@ -213,14 +204,14 @@ constexpr int unit_bytes(int b) {
 //   * 2^share waves can share a tile, its units dealt among them: each leaves its
 //     rows' sums in part (LDS, 16 of the wave's own) for the caller to add.
 // add: alpha times the sum of x.  w on a 16-byte boundary, of cap_bytes.
-template <int B, typename XT>
+template <int B>
 __device__ __forceinline__ void tiles(const uint32_t *__restrict__ w, uint64_t cap_bytes,
                                       int cols, int64_t row0, int64_t row_end, int wave,
                                       int waves, int64_t ntile, uint32_t flip,
                                       const uint8_t *xd, uint64_t add, uint8_t *buf,
                                       int64_t *__restrict__ y, int share, uint64_t *part) {
   typedef Unit<B> U;
-  constexpr int L = (B + 7) / 8, D = x_digits<XT>(), CH = U::chunks;
+  constexpr int L = (B + 7) / 8, D = kXDigits, CH = U::chunks;
   const int t0 = wave >> share, u0 = wave & ((1 << share) - 1);
   if (t0 >= ntile) return;
   // opaque: in a kernel that holds every width's code in a loop, what depends
@@ -231,7 +222,7 @@ __device__ __forceinline__ void tiles(const uint32_t *__restrict__ w, uint64_t c
   const int pitch = x_pitch(cols);
   const int nstep = (cols + kStep - 1) / kStep, nunit = (nstep + U::steps - 1) / U::steps;
   const uint8_t *xrow = xd + (n < D ? n : D) * pitch + 32 * h;
-  const uint64_t weight = n < D ? 1ull << (8 * n) : n == D ? x_offset<XT>() : 0;
+  const uint64_t weight = n < D ? 1ull << (8 * n) : n == D ? x_offset() : 0;
 
   // first bit of row r of tile t; rows past the end repeat the last one (their
   // results are not stored)
