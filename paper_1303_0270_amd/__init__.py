@@ -211,8 +211,10 @@ def _compress_onepass(t: torch.Tensor, code: int, s) -> CMatrix:
 
 
 def compress(dense: torch.Tensor, stream=None, order: str = "C") -> CMatrix:
-    """SM-compress a 2-D int32/int64 device tensor (range pass, then packing),
-    unravelled by row (order "C") or by column (order "F")."""
+    """SM-compress a 2-D int32/int64 device tensor, unravelled by row (order "C")
+    or by column (order "F"): a range pass, then packing; large tensors by row are
+    packed in the first pass already, at the width of a sample, and packed again
+    only where that is not the width of them all."""
     t = _device_tensor(dense, "dense")
     if t.dim() != 2:
         raise ValueError("2-D tensor expected")
