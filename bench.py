@@ -250,7 +250,8 @@ def summarize_trace(stats_csv, out_path, bench_json=None, cmd="", title="", note
 
     rows = list(csv.DictReader(open(stats_csv)))
     title = title or "Kernel times: one benchmark step over the 16384 x 16384 bandwidth sweep"
-    note = note or ("A step runs width + compress, matvec, add (asynchronous, one pass, the exact range "
+    note = note or ("A step runs compress (one pass at the width of a sample, the exact range reduced "
+                    "on the way), matvec, add (asynchronous, one pass, the exact range "
                     "folded into the pack), scale by 7, "
                     "decompress and 1000 gets over the twelve sweep matrices (k in "
                     "{1,3,7,12,17,31}, unsigned and signed); the dense int32 comparison, the read "
@@ -514,7 +515,7 @@ def main():
 
     ops = {"matvec": {"ms_per_sweep": round(tot_t / len(phases) * 1e3, 3),
                       "alg_gbs": round(value, 1)}}
-    ops["compress"] = op_stats("compress", lambda c, a: 16 * n * n + 8 * a.words)
+    ops["compress"] = op_stats("compress", lambda c, a: 8 * n * n + 8 * a.words)
     if not args.profile:
         ops["add"] = op_stats("add", lambda c, a: 8 * (a.words + c["B"].words + c["sum"].words))
         ops["scale"] = op_stats("scale", lambda c, a: 8 * (a.words + c["scaled"].words))
